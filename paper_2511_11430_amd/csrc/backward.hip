@@ -30,6 +30,9 @@
 // weights; inside, each role takes its own core.  The kernel carries 4 pi (g, h, k) and
 // scales by 1/(4 pi) at the end.  Per-particle sums are FP32 tile partials folded into two-sum
 // pairs (VPM_F32C) or plain FP64 (VPM_F64).
+//
+// Bound by VALU issue.  Sets too small to fill the chip with a particle per lane (below about
+// 262144) give several lanes to a particle, each taking a slice of every staged tile (split_lp).
 #include <hip/hip_runtime.h>
 
 #include "device_math.h"
@@ -154,15 +157,22 @@ struct Bwd {
         acc[2] += sr * rz;
     }
 
+    // Staged tile: l[0] = (x, y, z, 1/sigma), l[1] = (Gamma, cut), with role B l[2] = ub_q and,
+    // with stretching seeds, l[3] = Sb_q, l[4] = Sb_q x Gamma_q.
+    static constexpr int kArr = RB ? (STR ? 5 : 3) : 2;
+
+    // This lane's slice of a tile: the particles first, first + step, ...  self: the tile index of
+    // the lane's own particle (CHECK).
     template <bool CHECK, bool NEAR>
-    static __device__ __forceinline__ void tile(const V4<T>* l0, const V4<T>* l1, const V4<T>* l2, const V4<T>* l3,
-                                                const V4<T>* l4, int cnt, int64_t j0, int64_t p, const T (&xp)[3],
-                                                const T (&gp)[3], const T (&up)[3], const T (&sp)[3],
-                                                const T (&ep)[3], T isig_p, T cut_p, T (&acc)[kN]) {
+    static __device__ __forceinline__ void tile(const V4<T> (*l)[WG], int first, int step, int cnt, int self,
+                                                const T (&xp)[3], const T (&gp)[3], const T (&up)[3],
+                                                const T (&sp)[3], const T (&ep)[3], T isig_p, T cut_p,
+                                                T (&acc)[kN]) {
+        const V4<T>*l2 = l[RB ? 2 : 0], *l3 = l[kArr == 5 ? 3 : 0], *l4 = l[kArr == 5 ? 4 : 0];
 #pragma unroll 2
-        for (int jj = 0; jj < cnt; ++jj) {
-            const V4<T> q0 = l0[jj];  // x_q, 1/sigma_q
-            const V4<T> q1 = l1[jj];  // Gamma_q, cut_q
+        for (int jj = first; jj < cnt; jj += step) {
+            const V4<T> q0 = l[0][jj];  // x_q, 1/sigma_q
+            const V4<T> q1 = l[1][jj];  // Gamma_q, cut_q
             const T rx = xp[0] - q0.x, ry = xp[1] - q0.y, rz = xp[2] - q0.z;
             const T s2 = rx * rx + ry * ry + rz * rz;
             const T rinv = rsqrt_fast(s2);
@@ -186,7 +196,7 @@ struct Bwd {
                     }
                 }
             }
-            if (CHECK && j0 + jj == p) gA = hA = kA = gB = hB = kB = T(0);
+            if (CHECK && jj == self) gA = hA = kA = gB = hB = kB = T(0);
             if constexpr (!NEAR && !CHECK && RA && RB) {
                 // Outside every core both roles share (g, h, k): add the roles' terms before
                 // multiplying by the weights.
@@ -270,22 +280,50 @@ struct Bwd {
     }
 };
 
+// A value moved between lanes by a DPP control; lanes the move does not reach keep their own.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_move(float v) {
+    const int i = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double v) {
+    const int64_t b = __double_as_longlong(v);
+    const int lo = int(uint32_t(b)), hi = int(uint32_t(uint64_t(b) >> 32));
+    const uint32_t l2 = uint32_t(__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false));
+    const uint32_t h2 = uint32_t(__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false));
+    return __longlong_as_double(int64_t((uint64_t(h2) << 32) | l2));
+}
+// Minimum of v[0..2] and maximum of v[3..6] over a wavefront, valid in lane 63: row shifts by 1,
+// 2, 4 and 8, then the two row broadcasts (lane 15 of rows 0 and 2 into the next row, lane 31
+// into rows 2 and 3).  One register move per step where a shuffle goes through the LDS unit.
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ void minmax_step(T (&v)[7]) {
+#pragma unroll
+    for (int c = 0; c < 7; ++c) {
+        const T o = dpp_move<CTRL, ROWS>(v[c]);
+        v[c] = c < 3 ? fmin(v[c], o) : fmax(v[c], o);
+    }
+}
+template <typename T>
+__device__ __forceinline__ void wave_minmax_last(T (&v)[7]) {
+    minmax_step<0x111, 0xf>(v);  // row_shr:1
+    minmax_step<0x112, 0xf>(v);  // row_shr:2
+    minmax_step<0x114, 0xf>(v);  // row_shr:4
+    minmax_step<0x118, 0xf>(v);  // row_shr:8
+    minmax_step<0x142, 0xa>(v);  // row_bcast:15
+    minmax_step<0x143, 0xc>(v);  // row_bcast:31
+}
+
 // Workgroup bounding box (v[0..2] min, v[3..5] max) and largest cut (v[6]): a shuffle
 // reduction per wavefront, then LDS.  Ends with a barrier; every thread gets the result.
 template <typename T>
 __device__ __forceinline__ void box_reduce(T (&v)[7], T* scratch) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-        for (int c = 0; c < 7; ++c) {
-            const T o = __shfl_xor(v[c], off, 64);
-            v[c] = c < 3 ? fmin(v[c], o) : fmax(v[c], o);
-        }
-    }
+    wave_minmax_last(v);
     const int wave = threadIdx.x >> 6;
     const int nwave = (blockDim.x + 63) >> 6;
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
+    if ((threadIdx.x & 63) == 63) {
 #pragma unroll
         for (int c = 0; c < 7; ++c) scratch[wave * 7 + c] = v[c];
     }
@@ -300,17 +338,17 @@ __device__ __forceinline__ void box_reduce(T (&v)[7], T* scratch) {
 
 // One workgroup's lane block blk of a lane set [lb, lb + nl) against the loop set
 // [ob, ob + no) (indices into the arrays of a; with a.self both sets are the same range).
+// The block holds P = 2^lp particles (lp <= 6, or P = WG): the workgroup's lanes form WG / P
+// slices that share each staged tile (lane tid: particle tid mod P, slice tid / P, which takes
+// the tile's particles slice, slice + WG / P, ...).  The slices' sums are added in FP64 at the
+// end, by shuffles within a wavefront and through LDS across wavefronts, in a fixed order.
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
 __device__ __forceinline__ void backward_body(const BwdArgs& a, int64_t blk, int64_t lb, int64_t nl, int64_t ob,
-                                              int64_t no) {
+                                              int64_t no, int lp) {
     using B = Bwd<T, WG, RA, RB, STR, SYM>;
     constexpr int kN = B::kN;
     constexpr bool kComp = B::kComp;
-    __shared__ V4<T> l0[WG];                    // (x, y, z, 1/sigma)
-    __shared__ V4<T> l1[WG];                    // (Gamma, cut)
-    __shared__ V4<T> l2[RB ? WG : 1];           // ub_q
-    __shared__ V4<T> l3[(RB && STR) ? WG : 1];  // Sb_q
-    __shared__ V4<T> l4[(RB && STR) ? WG : 1];  // Sb_q x Gamma_q
+    __shared__ V4<T> l[B::kArr][WG];
     __shared__ T box[7 * (WG / 64)];
     // the set bases are folded into the pointers (null pointers stay null)
     auto at = [](const void* q, int64_t base) { return q ? static_cast<const T*>(q) + base : nullptr; };
@@ -326,8 +364,10 @@ __device__ __forceinline__ void backward_body(const BwdArgs& a, int64_t blk, int
     const T* __restrict__ sbo = at(a.sbo, ob);
     const T far2 = T(Prec<T>::kFarRho2);
     const int tid = threadIdx.x;
-    const int64_t pb0 = blk * WG;
-    const int64_t p = pb0 + tid;
+    const int np = 1 << lp;
+    const int slice = tid >> lp, nslice = WG >> lp;
+    const int64_t pb0 = blk << lp;
+    const int64_t p = pb0 + (tid & (np - 1));
     const bool valid = p < nl;
     const int64_t pp = valid ? p : pb0;
 
@@ -382,21 +422,21 @@ __device__ __forceinline__ void backward_body(const BwdArgs& a, int64_t blk, int
         }
         v1.w = SYM ? T(0.5) * far2 * sq * sq : (RA ? far2 * sq * sq : T(0));
         if (tid < cnt) {
-            l0[tid] = v0;
-            l1[tid] = v1;
-            if (RB) {
+            l[0][tid] = v0;
+            l[1][tid] = v1;
+            if constexpr (RB) {
                 V4<T> v2;
                 v2.x = ubo[jl]; v2.y = ubo[a.ldo + jl]; v2.z = ubo[2 * a.ldo + jl]; v2.w = T(0);
-                l2[tid] = v2;
-                if (STR) {
+                l[2][tid] = v2;
+                if constexpr (STR) {
                     V4<T> v3, v4;
                     v3.x = sbo[jl]; v3.y = sbo[a.ldo + jl]; v3.z = sbo[2 * a.ldo + jl]; v3.w = T(0);
                     v4.x = v3.y * v1.z - v3.z * v1.y;
                     v4.y = v3.z * v1.x - v3.x * v1.z;
                     v4.z = v3.x * v1.y - v3.y * v1.x;
                     v4.w = T(0);
-                    l3[tid] = v3;
-                    l4[tid] = v4;
+                    l[3][tid] = v3;
+                    l[4][tid] = v4;
                 }
             }
         }
@@ -411,31 +451,72 @@ __device__ __forceinline__ void backward_body(const BwdArgs& a, int64_t blk, int
         }
         const T reach = SYM ? tb[6] + bb[6] : fmax(tb[6], bb[6]);
         const bool near = d2 < reach;
-        const bool diag = a.self && (j0 < pb0 + WG) && (pb0 < j0 + cnt);
+        const bool diag = a.self && (j0 < pb0 + np) && (pb0 < j0 + cnt);
+        const int own = int(p - j0);  // (read only where diag, when it fits)
         if (diag) {
-            if (near) B::template tile<true, true>(l0, l1, l2, l3, l4, cnt, j0, p, xp, gp, up, sp, ep, isig_p, cut_p, acc);
-            else B::template tile<true, false>(l0, l1, l2, l3, l4, cnt, j0, p, xp, gp, up, sp, ep, isig_p, cut_p, acc);
+            if (near) B::template tile<true, true>(l, slice, nslice, cnt, own, xp, gp, up, sp, ep, isig_p,
+                                                           cut_p, acc);
+            else B::template tile<true, false>(l, slice, nslice, cnt, own, xp, gp, up, sp, ep, isig_p,
+                                                           cut_p, acc);
         } else {
-            if (near) B::template tile<false, true>(l0, l1, l2, l3, l4, cnt, j0, p, xp, gp, up, sp, ep, isig_p, cut_p, acc);
-            else B::template tile<false, false>(l0, l1, l2, l3, l4, cnt, j0, p, xp, gp, up, sp, ep, isig_p, cut_p, acc);
+            if (near) B::template tile<false, true>(l, slice, nslice, cnt, own, xp, gp, up, sp, ep, isig_p,
+                                                           cut_p, acc);
+            else B::template tile<false, false>(l, slice, nslice, cnt, own, xp, gp, up, sp, ep, isig_p,
+                                                           cut_p, acc);
         }
+        // FP32 sums run over at most WG terms between folds (a slice takes WG / nslice per tile),
+        // and near tiles, whose terms are large, are folded at once: the gradient's error against
+        // FP64 is then a third of what it is with the far tiles' terms added to them (hover wake,
+        // 65536 particles: 2.2e-7 and 7.5e-7; 5.0e-7 with a particle per lane and a fold per tile).
         if constexpr (kComp) {
+            if (near || ((j0 / WG + 1) & (nslice - 1)) == 0 || j0 + WG >= no) {
 #pragma unroll
-            for (int c = 0; c < kN; ++c) {
-                T s, e;
-                two_sum(hi[c], acc[c], s, e);
-                hi[c] = s;
-                lo[c] += e;
-                acc[c] = T(0);
+                for (int c = 0; c < kN; ++c) {
+                    T s, e;
+                    two_sum(hi[c], acc[c], s, e);
+                    hi[c] = s;
+                    lo[c] += e;
+                    acc[c] = T(0);
+                }
             }
         }
     }
-    if (!valid) return;  // (nothing follows in a caller's loop that this lane must reach)
     double t[16];
 #pragma unroll
     for (int c = 0; c < 16; ++c) t[c] = 0.0;
 #pragma unroll
     for (int c = 0; c < kN; ++c) t[c] = kComp ? double(hi[c]) + double(lo[c]) : double(acc[c]);
+    if (nslice > 1) {
+        // np <= 64: every wavefront holds the same particles.  The tile's LDS carries the other
+        // wavefronts' sums to wavefront 0, kPer sums at a time.
+        constexpr int kWaves = WG / 64;
+        constexpr int kFit = int(sizeof(l) / ((kWaves - 1) * 64 * sizeof(double)));
+        constexpr int kPer = kFit < kN ? kFit : kN;
+        double(*red)[kPer][64] = reinterpret_cast<double(*)[kPer][64]>(&l[0][0]);
+        for (int off = np; off < 64; off <<= 1)
+#pragma unroll
+            for (int c = 0; c < kN; ++c) t[c] += __shfl_xor(t[c], off, 64);
+        const int wave = tid >> 6, lane = tid & 63;
+#pragma unroll
+        for (int c0 = 0; c0 < kN; c0 += kPer) {
+            __syncthreads();
+            if (wave > 0) {
+#pragma unroll
+                for (int c = 0; c < kPer; ++c)
+                    if (c0 + c < kN) red[wave - 1][c][lane] = t[c0 + c];
+            }
+            __syncthreads();
+            if (wave == 0) {
+#pragma unroll
+                for (int w = 0; w < kWaves - 1; ++w)
+#pragma unroll
+                    for (int c = 0; c < kPer; ++c)
+                        if (c0 + c < kN) t[c0 + c] += red[w][c][lane];
+            }
+        }
+    }
+    // (nothing follows in a caller's loop that this lane must reach before its next barrier)
+    if (tid >= np || !valid) return;
     const double u0 = up[0], u1 = up[1], u2 = up[2];
     const double g0 = gp[0], g1 = gp[1], g2 = gp[2];
     const double s0 = sp[0], s1 = sp[1], s2 = sp[2];
@@ -475,12 +556,48 @@ __device__ __forceinline__ void backward_body(const BwdArgs& a, int64_t blk, int
 // FP32: ask for 4 wavefronts per SIMD (<= 128 VGPRs; no spills at these shapes).  FP64 keeps
 // the compiler's choice: its accumulators need twice the registers.
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_backward_f32(BwdArgs a) {
-    backward_body<T, WG, RA, RB, STR, SYM>(a, blockIdx.x, 0, a.nl, 0, a.no);
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_backward_f32(BwdArgs a, int lp) {
+    backward_body<T, WG, RA, RB, STR, SYM>(a, blockIdx.x, 0, a.nl, 0, a.no, lp);
 }
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
-__global__ __launch_bounds__(WG) void k_backward_f64(BwdArgs a) {
-    backward_body<T, WG, RA, RB, STR, SYM>(a, blockIdx.x, 0, a.nl, 0, a.no);
+__global__ __launch_bounds__(WG) void k_backward_f64(BwdArgs a, int lp) {
+    backward_body<T, WG, RA, RB, STR, SYM>(a, blockIdx.x, 0, a.nl, 0, a.no, lp);
+}
+
+// Particles per workgroup (log2; 8 = no split) of a lane set of nl particles.  A wavefront's work
+// per staged tile is P pairs per lane (about 80 VALU instructions each) and about 230
+// instructions' worth of staging, box reduction, folds and waiting.  kSlots workgroups are
+// resident on the chip (four wavefronts per SIMD); fewer than that run each wavefront faster, so
+// x = nl / P / kSlots rounds take 0.6 + 0.4 x below one and x + 0.1 from there (fitted to the
+// times of P = 4 ... 256 at 1000-200000 particles).  Without the split a set of fewer than 262144
+// particles leaves SIMDs with one wavefront or none.  A function of nl alone, so that a set gets
+// the same sums in a launch of its own and in a queue of many sets; blocks of 4 would take 1000
+// particles alone from 37 to 23 us but a queue of 300 sets of 64-600 from 150 to 490 us.
+// Measured (FP32, both roles, hover wake, us per call without and with the split): 1000
+// particles 393 / 37, 4999 1686 / 143, 16384 4970 / 659, 65536 17890 / 8170, 200000 83300 / 70200.
+constexpr int kSplitLpMin = 4, kSplitLpMax = 6, kNoSplitLp = 8;
+constexpr int64_t kSlots = 1024;
+__host__ __device__ inline int split_lp(int64_t nl) {
+    int best = kNoSplitLp;
+    int64_t least = 0;
+    for (int lp = kNoSplitLp; lp >= kSplitLpMin; --lp) {
+        if (lp > kSplitLpMax && lp != kNoSplitLp) continue;
+        const int64_t wgs = (nl + (int64_t(1) << lp) - 1) >> lp;
+        const int64_t rounds = wgs < kSlots ? (6 * kSlots + 4 * wgs) / 10 : wgs + kSlots / 10;
+        const int64_t cost = rounds * ((int64_t(80) << lp) + 230);
+        if (lp == kNoSplitLp || cost < least) {
+            best = lp;
+            least = cost;
+        }
+    }
+    return best;
+}
+
+// A value equal in every lane, moved to scalar registers.
+__device__ __forceinline__ int64_t uniform_i64(int64_t v) {
+    const uint32_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v))));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(uint64_t(v) >> 32))));
+    return int64_t((uint64_t(hi) << 32) | lo);
 }
 
 // Many independent sets in one launch: persistent workgroups pop (set, lane block) items,
@@ -488,43 +605,55 @@ __global__ __launch_bounds__(WG) void k_backward_f64(BwdArgs a) {
 // [src_off[b], src_off[b+1]) and the loop set [tgt_off[b], tgt_off[b+1]) (exchanged when
 // lane_is_tgt).  Every workgroup leaves once the counter passes the item count.
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
-__device__ __forceinline__ void backward_queue(const BwdArgs& a, const BatchQueue& q, int lane_is_tgt) {
+__device__ __forceinline__ void backward_queue(const BwdArgs& a, const BatchQueue& q, int item_lp, int lane_is_tgt) {
     __shared__ int item_s;
     for (;;) {
         if (threadIdx.x == 0) item_s = atomicAdd(q.counter, 1);
         __syncthreads();
-        const int item = item_s;
+        // (uniform, so that the set's ranges and pointers stay in scalar registers)
+        const int item = __builtin_amdgcn_readfirstlane(item_s);
         __syncthreads();
         if (item >= q.n_items) break;
-        const int2 it = q.items[item];
+        const int set = __builtin_amdgcn_readfirstlane(q.items[item].x);
+        const int64_t nth = __builtin_amdgcn_readfirstlane(q.items[item].y);
         const int64_t* lo = lane_is_tgt ? q.tgt_off : q.src_off;
         const int64_t* oo = lane_is_tgt ? q.src_off : q.tgt_off;
-        const int64_t lb = lo[it.x], ob = oo[it.x];
-        backward_body<T, WG, RA, RB, STR, SYM>(a, it.y, lb, lo[it.x + 1] - lb, ob, oo[it.x + 1] - ob);
+        const int64_t lb = uniform_i64(lo[set]), nl = uniform_i64(lo[set + 1]) - lb;
+        const int64_t ob = uniform_i64(oo[set]), no = uniform_i64(oo[set + 1]) - ob;
+        // the item's particles, in the blocks that a launch for this set alone would have
+        const int lp = split_lp(nl);
+        const int more = item_lp > lp ? item_lp - lp : 0;
+        const int64_t b0 = nth << more;
+        for (int k = 0; k < (1 << more) && ((b0 + k) << lp) < nl; ++k)
+            backward_body<T, WG, RA, RB, STR, SYM>(a, b0 + k, lb, nl, ob, no, lp);
     }
 }
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_backward_batched_f32(
-    BwdArgs a, BatchQueue q, int lane_is_tgt) {
-    backward_queue<T, WG, RA, RB, STR, SYM>(a, q, lane_is_tgt);
+    BwdArgs a, BatchQueue q, int item_lp, int lane_is_tgt) {
+    backward_queue<T, WG, RA, RB, STR, SYM>(a, q, item_lp, lane_is_tgt);
 }
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
-__global__ __launch_bounds__(WG) void k_backward_batched_f64(BwdArgs a, BatchQueue q, int lane_is_tgt) {
-    backward_queue<T, WG, RA, RB, STR, SYM>(a, q, lane_is_tgt);
+__global__ __launch_bounds__(WG) void k_backward_batched_f64(BwdArgs a, BatchQueue q, int item_lp, int lane_is_tgt) {
+    backward_queue<T, WG, RA, RB, STR, SYM>(a, q, item_lp, lane_is_tgt);
 }
 
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
-void launch_k(int grid, const BwdArgs& a, hipStream_t st) {
+void launch_k(const BwdArgs& a, hipStream_t st) {
+    static_assert(WG == 1 << kNoSplitLp, "without a split a particle per lane");
+    const int lp = split_lp(a.nl);
+    const unsigned grid = unsigned((a.nl + (int64_t(1) << lp) - 1) >> lp);
     if constexpr (std::is_same<T, float>::value)
-        hipLaunchKernelGGL((k_backward_f32<T, WG, RA, RB, STR, SYM>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_backward_f32<T, WG, RA, RB, STR, SYM>), dim3(grid), dim3(WG), 0, st, a, lp);
     else
-        hipLaunchKernelGGL((k_backward_f64<T, WG, RA, RB, STR, SYM>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_backward_f64<T, WG, RA, RB, STR, SYM>), dim3(grid), dim3(WG), 0, st, a, lp);
 }
 
 // Persistent launch over a queue (grid <= 0: only report the kernel's resident workgroups
 // per CU through *occ).
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
-hipError_t launch_kq(int grid, const BwdArgs& a, const BatchQueue& q, int lane_is_tgt, int* occ, hipStream_t st) {
+hipError_t launch_kq(int grid, const BwdArgs& a, const BatchQueue& q, int item_lp, int lane_is_tgt, int* occ,
+                     hipStream_t st) {
     if (grid <= 0) {
         if constexpr (std::is_same<T, float>::value)
             return hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -535,66 +664,67 @@ hipError_t launch_kq(int grid, const BwdArgs& a, const BatchQueue& q, int lane_i
     }
     if constexpr (std::is_same<T, float>::value)
         hipLaunchKernelGGL((k_backward_batched_f32<T, WG, RA, RB, STR, SYM>), dim3(grid), dim3(WG), 0, st, a, q,
-                           lane_is_tgt);
+                           item_lp, lane_is_tgt);
     else
         hipLaunchKernelGGL((k_backward_batched_f64<T, WG, RA, RB, STR, SYM>), dim3(grid), dim3(WG), 0, st, a, q,
-                           lane_is_tgt);
+                           item_lp, lane_is_tgt);
     return hipGetLastError();
 }
 
 template <typename T, int WG, bool RA, bool RB>
-hipError_t launch_rs(bool stretch, bool sym, const BwdArgs& a, const BatchQueue* q, int grid, int lane_is_tgt,
-                     int* occ, hipStream_t st) {
+hipError_t launch_rs(bool stretch, bool sym, const BwdArgs& a, const BatchQueue* q, int item_lp, int grid,
+                     int lane_is_tgt, int* occ, hipStream_t st) {
     if (q) {
         if (stretch) {
-            if (sym) return launch_kq<T, WG, RA, RB, true, true>(grid, a, *q, lane_is_tgt, occ, st);
-            return launch_kq<T, WG, RA, RB, true, false>(grid, a, *q, lane_is_tgt, occ, st);
+            if (sym) return launch_kq<T, WG, RA, RB, true, true>(grid, a, *q, item_lp, lane_is_tgt, occ, st);
+            return launch_kq<T, WG, RA, RB, true, false>(grid, a, *q, item_lp, lane_is_tgt, occ, st);
         }
-        if (sym) return launch_kq<T, WG, RA, RB, false, true>(grid, a, *q, lane_is_tgt, occ, st);
-        return launch_kq<T, WG, RA, RB, false, false>(grid, a, *q, lane_is_tgt, occ, st);
+        if (sym) return launch_kq<T, WG, RA, RB, false, true>(grid, a, *q, item_lp, lane_is_tgt, occ, st);
+        return launch_kq<T, WG, RA, RB, false, false>(grid, a, *q, item_lp, lane_is_tgt, occ, st);
     }
-    grid = int((a.nl + WG - 1) / WG);
     if (stretch) {
-        if (sym) launch_k<T, WG, RA, RB, true, true>(grid, a, st);
-        else launch_k<T, WG, RA, RB, true, false>(grid, a, st);
+        if (sym) launch_k<T, WG, RA, RB, true, true>(a, st);
+        else launch_k<T, WG, RA, RB, true, false>(a, st);
     } else {
-        if (sym) launch_k<T, WG, RA, RB, false, true>(grid, a, st);
-        else launch_k<T, WG, RA, RB, false, false>(grid, a, st);
+        if (sym) launch_k<T, WG, RA, RB, false, true>(a, st);
+        else launch_k<T, WG, RA, RB, false, false>(a, st);
     }
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_t(bool ra, bool rb, bool stretch, bool sym, const BwdArgs& a, const BatchQueue* q, int grid,
-                    int lane_is_tgt, int* occ, hipStream_t st) {
-    if (ra && rb) return launch_rs<T, kBwdWG, true, true>(stretch, sym, a, q, grid, lane_is_tgt, occ, st);
-    if (ra) return launch_rs<T, kBwdWG, true, false>(stretch, sym, a, q, grid, lane_is_tgt, occ, st);
-    return launch_rs<T, kBwdWG, false, true>(stretch, sym, a, q, grid, lane_is_tgt, occ, st);
+hipError_t launch_t(bool ra, bool rb, bool stretch, bool sym, const BwdArgs& a, const BatchQueue* q, int item_lp,
+                    int grid, int lane_is_tgt, int* occ, hipStream_t st) {
+    if (ra && rb) return launch_rs<T, kBwdWG, true, true>(stretch, sym, a, q, item_lp, grid, lane_is_tgt, occ, st);
+    if (ra) return launch_rs<T, kBwdWG, true, false>(stretch, sym, a, q, item_lp, grid, lane_is_tgt, occ, st);
+    return launch_rs<T, kBwdWG, false, true>(stretch, sym, a, q, item_lp, grid, lane_is_tgt, occ, st);
 }
 
 }  // namespace
+
+int backward_split_lp(int64_t nl) { return split_lp(nl); }
 
 hipError_t launch_backward(int dtype, bool role_a, bool role_b, bool stretch, bool sym,
                            const BwdArgs& a, hipStream_t st) {
     if (a.nl == 0) return hipSuccess;
     if (!role_a && !role_b) return hipErrorInvalidValue;
-    if (dtype == kDtypeF64) return launch_t<double>(role_a, role_b, stretch, sym, a, nullptr, 0, 0, nullptr, st);
-    return launch_t<float>(role_a, role_b, stretch, sym, a, nullptr, 0, 0, nullptr, st);
+    if (dtype == kDtypeF64) return launch_t<double>(role_a, role_b, stretch, sym, a, nullptr, 0, 0, 0, nullptr, st);
+    return launch_t<float>(role_a, role_b, stretch, sym, a, nullptr, 0, 0, 0, nullptr, st);
 }
 
 hipError_t launch_backward_batched(int dtype, bool role_a, bool role_b, bool stretch, bool sym, const BwdArgs& a,
-                                   const BatchQueue& q, int grid, int lane_is_tgt, hipStream_t st) {
+                                   const BatchQueue& q, int item_lp, int grid, int lane_is_tgt, hipStream_t st) {
     if (!role_a && !role_b) return hipErrorInvalidValue;
-    if (dtype == kDtypeF64) return launch_t<double>(role_a, role_b, stretch, sym, a, &q, grid, lane_is_tgt, nullptr, st);
-    return launch_t<float>(role_a, role_b, stretch, sym, a, &q, grid, lane_is_tgt, nullptr, st);
+    if (dtype == kDtypeF64) return launch_t<double>(role_a, role_b, stretch, sym, a, &q, item_lp, grid, lane_is_tgt, nullptr, st);
+    return launch_t<float>(role_a, role_b, stretch, sym, a, &q, item_lp, grid, lane_is_tgt, nullptr, st);
 }
 
 int backward_occupancy(int dtype, bool role_a, bool role_b, bool stretch, bool sym) {
     int occ = 0;
     BwdArgs a{};
     BatchQueue q{};
-    hipError_t e = dtype == kDtypeF64 ? launch_t<double>(role_a, role_b, stretch, sym, a, &q, 0, 0, &occ, nullptr)
-                                      : launch_t<float>(role_a, role_b, stretch, sym, a, &q, 0, 0, &occ, nullptr);
+    hipError_t e = dtype == kDtypeF64 ? launch_t<double>(role_a, role_b, stretch, sym, a, &q, 0, 0, 0, &occ, nullptr)
+                                      : launch_t<float>(role_a, role_b, stretch, sym, a, &q, 0, 0, 0, &occ, nullptr);
     return e == hipSuccess ? occ : 0;
 }
 

@@ -121,19 +121,41 @@ QueueLayout queue_layout(int32_t n_batch, const int64_t* tgt_off, int64_t per_bl
     return queue_layout_items(n_batch, count_blocks(n_batch, tgt_off, per_block));
 }
 
-// Adjoint of many sets: the larger of the two queues (source blocks, target blocks).
+// Adjoint of many sets.  A queue item is 2^item_lp particles of a set, or the set's own block
+// where that is larger (backward_split_lp): 256 particles, and fewer while that leaves less than
+// kBwdItems items, which is two for each of the chip's resident workgroups.  Measured (FP32, us
+// per call with one particle per lane and 256 per item / now): 300 sets of 64-600 particles
+// 335 / 150, 64 sets of 256-2000 980 / 223, 64 of
+// 512-20000 11550 / 10000.
+constexpr int64_t kBwdItems = 2048;
+constexpr int kBwdItemLpMax = 8, kBwdItemLpMin = 4;
+int64_t backward_items(int32_t n_batch, const int64_t* off, int item_lp) {
+    int64_t items = 0;
+    for (int32_t b = 0; b < n_batch; ++b) {
+        const int64_t n = off[b + 1] - off[b];
+        const int lp = std::max(item_lp, vpm::backward_split_lp(n));
+        items += (n + (int64_t(1) << lp) - 1) >> lp;
+    }
+    return items;
+}
+int backward_item_lp(int32_t n_batch, const int64_t* off) {
+    int lp = kBwdItemLpMax;
+    while (lp > kBwdItemLpMin && backward_items(n_batch, off, lp) < kBwdItems) --lp;
+    return lp;
+}
+// The larger of the two queues (source blocks, target blocks).
 QueueLayout backward_queue_layout(int32_t n_batch, const int64_t* src_off, const int64_t* tgt_off) {
-    const int64_t per = vpm::kBwdWG;
-    return queue_layout_items(n_batch, std::max(count_blocks(n_batch, src_off, per),
-                                                count_blocks(n_batch, tgt_off, per)));
+    return queue_layout_items(n_batch,
+                              std::max(backward_items(n_batch, src_off, backward_item_lp(n_batch, src_off)),
+                                       backward_items(n_batch, tgt_off, backward_item_lp(n_batch, tgt_off))));
 }
 
 hipError_t stage_and_copy(const std::vector<unsigned char>& blob, void* dst, hipStream_t st);
 
-// Stages the LPT-ordered (set, block) items of the lane sets `lane_off` (cost: lane count x
+// Stages the LPT-ordered (set, block) items of the adjoint's lane sets (cost: lane count x
 // loop-set size) with both offset tables into the workspace; returns the item count.
 hipError_t stage_queue(int32_t n_batch, const int64_t* src_off, const int64_t* tgt_off, bool lane_is_tgt,
-                       int64_t per_block, void* workspace, hipStream_t st, int64_t* n_items) {
+                       int item_lp, void* workspace, hipStream_t st, int64_t* n_items) {
     const int64_t* lane = lane_is_tgt ? tgt_off : src_off;
     const int64_t* loop = lane_is_tgt ? src_off : tgt_off;
     struct Item {
@@ -143,6 +165,7 @@ hipError_t stage_queue(int32_t n_batch, const int64_t* src_off, const int64_t* t
     std::vector<Item> items;
     for (int32_t b = 0; b < n_batch; ++b) {
         const int64_t nl = lane[b + 1] - lane[b], no = loop[b + 1] - loop[b];
+        const int64_t per_block = int64_t(1) << std::max(item_lp, vpm::backward_split_lp(nl));
         const int64_t nblk = (nl + per_block - 1) / per_block;
         for (int64_t k = 0; k < nblk; ++k)
             items.push_back({b, int(k), (no + 1) * std::min<int64_t>(per_block, nl - k * per_block)});
@@ -354,7 +377,8 @@ hipError_t backward_batched(int32_t dtype, int32_t n_batch, const int64_t* src_o
                             bool role_a, bool role_b, bool stretch, bool sym, const vpm::BwdArgs& a,
                             bool lane_is_tgt, void* workspace, hipStream_t st) {
     int64_t n_items = 0;
-    hipError_t e = stage_queue(n_batch, src_off, tgt_off, lane_is_tgt, vpm::kBwdWG, workspace, st, &n_items);
+    const int item_lp = backward_item_lp(n_batch, lane_is_tgt ? tgt_off : src_off);
+    hipError_t e = stage_queue(n_batch, src_off, tgt_off, lane_is_tgt, item_lp, workspace, st, &n_items);
     if (e != hipSuccess || n_items == 0) return e;
     DeviceInfo di;
     e = device_info(di);
@@ -370,8 +394,8 @@ hipError_t backward_batched(int32_t dtype, int32_t n_batch, const int64_t* src_o
     q.src_off = reinterpret_cast<const int64_t*>(ws + L.off_src);
     q.tgt_off = reinterpret_cast<const int64_t*>(ws + L.off_tgt);
     q.n_items = int(n_items);
-    return vpm::launch_backward_batched(dtype, role_a, role_b, stretch, sym, a, q, int(grid), lane_is_tgt ? 1 : 0,
-                                        st);
+    return vpm::launch_backward_batched(dtype, role_a, role_b, stretch, sym, a, q, item_lp, int(grid),
+                                        lane_is_tgt ? 1 : 0, st);
 }
 
 }  // namespace

@@ -116,6 +116,26 @@ def test_batched_vjp_equals_per_set_calls(kind, scheme, gpu):
             assert rel_l2(host(xw)[:, idx], rx) <= TOL[kind] and rel_l2(host(gw)[:, idx], rg) <= TOL[kind]
 
 
+@pytest.mark.parametrize("kind", KINDS)
+# one block of a workgroup's particles and its neighbours at every block size the launch picks
+# (4, 8, 16, 32, 64 particles; 256 needs more than 150000), tile ends, a lone particle
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 255, 256, 257, 2049, 5003, 9001, 16383, 20011, 50021])
+def test_vjp_at_split_sizes(kind, n, gpu):
+    rng = np.random.default_rng([23, n])
+    w = W.hover_wake(n, 1, 0.02, 10, rng) if n > 8 else {"x": rng.normal(size=(3, n)) * 0.02,
+                                                         "gamma": rng.normal(size=(3, n)), "sigma": np.full(n, 0.02)}
+    x, g, s = prepare([w["x"], w["gamma"], w["sigma"]], kind)
+    ub, sb = prepare([rng.normal(size=x.shape), rng.normal(size=x.shape) * 1e3], kind)
+    say(f"vjp split {kind} n={n}")
+    xb, gb, _, _ = vpm.vpm_backward(dev(x, kind), dev(g, kind), dev(s, kind), dev(ub, kind), dev(sb, kind))
+    if n == 1:
+        assert np.all(host(xb) == 0) and np.all(host(gb) == 0)
+        return
+    idx = np.unique(np.concatenate([[0, n // 2, n - 1], rng.integers(0, n, 5)]))
+    rx, rg = _oracle_vjp_columns(x, g, s, ub, sb, 0, idx)
+    assert rel_l2(host(xb)[:, idx], rx) <= TOL[kind] and rel_l2(host(gb)[:, idx], rg) <= TOL[kind]
+
+
 def _oracle_vjp_columns(x, g, s, ub, sb, rule, idx, scheme=0):
     """Entries of w^T J for the particles idx (all six components), each the oracle's
     dual-number tangent along a unit vector.  Only pairs that contain the particle carry a
