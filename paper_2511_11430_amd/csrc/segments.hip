@@ -413,117 +413,93 @@ __device__ __forceinline__ void fold_tile(T (&acc)[NA], T (&hi)[NA], T (&lo)[NA]
 // LPT lanes per target (neighbouring lanes of one wavefront) split each staged tile of segments
 // between them, lane q taking the segments q, q + LPT, ...; their sums are added in FP64 by a
 // butterfly before the write, so a launch with few targets still has several wavefronts per SIMD.
-template <typename T, int K, int WG, int VN, int LPT>
+template <typename T, int WG, int VN, int LPT>
 __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
-    static_assert(LPT == 1 || K == 1, "lanes per target only with one target per lane group");
     static_assert((LPT & (LPT - 1)) == 0 && LPT <= 64, "a power of two within a wavefront");
     constexpr bool kComp = std::is_same<T, float>::value;
     constexpr int NA = 12;  // u (3), J row-major (9)
-    constexpr int kSlots = WG / LPT;  // targets per workgroup and K
     __shared__ V4<T> l0[WG];
     __shared__ V4<T> l1[WG];
     __shared__ V2<T> l2[WG];  // (eps^2 for the arms, 1/|r0|^2)
     const T* __restrict__ X = static_cast<const T*>(a.xt);
-    const int tid = threadIdx.x / LPT, q = threadIdx.x % LPT;
-    const int64_t t0 = int64_t(blockIdx.x) * (kSlots * K);
+    const int part = threadIdx.x % LPT;
+    const int64_t t = int64_t(blockIdx.x) * (WG / LPT) + threadIdx.x / LPT;
+    const bool valid = t < a.n_tgt;
+    const int64_t tt = valid ? t : 0;
     const T n_f = T(a.vn);
     const T inv_n = T(1.0 / a.vn);
     const T rc2n = core_power<T>(a, VN);
 
-    T P[K][3];
-    bool valid[K];
+    const T P[3] = {X[tt], X[a.ldt + tt], X[2 * a.ldt + tt]};
+    T acc[NA], hi[NA], lo[NA];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int64_t t = t0 + tid + int64_t(k) * kSlots;
-        valid[k] = t < a.n_tgt;
-        const int64_t tt = valid[k] ? t : 0;
-        P[k][0] = X[tt];
-        P[k][1] = X[a.ldt + tt];
-        P[k][2] = X[2 * a.ldt + tt];
-    }
-    T acc[K][NA], hi[K][NA], lo[K][NA];
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-        for (int c = 0; c < NA; ++c) acc[k][c] = hi[k][c] = lo[k][c] = T(0);
+    for (int c = 0; c < NA; ++c) acc[c] = hi[c] = lo[c] = T(0);
 
     for (int64_t j0 = 0; j0 < a.n_seg; j0 += WG) {
         const int cnt = int((a.n_seg - j0) < WG ? (a.n_seg - j0) : WG);
         __syncthreads();
         stage_segments<T, WG, VN>(a, j0, cnt, l0, l1, l2);
         __syncthreads();
-        for (int jj = q; jj < cnt; jj += LPT) {
+        for (int jj = part; jj < cnt; jj += LPT) {
             const V4<T> p = l0[jj];
             const V4<T> q = l1[jj];
             const T eps2 = l2[jj].x;
             const T inv_l02 = l2[jj].y;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                T f, c[3], g[3];
-                seg_pair<T, T, VN>(P[k], p, q, eps2, inv_l02, rc2n, inv_n, n_f, f, c, g);
-                T* ac = acc[k];
-                ac[0] += f * c[0];
-                ac[1] += f * c[1];
-                ac[2] += f * c[2];
-                // f [r0]x + c g^T
-                ac[3] += c[0] * g[0];
-                ac[4] += c[0] * g[1] - f * q.z;
-                ac[5] += c[0] * g[2] + f * q.y;
-                ac[6] += c[1] * g[0] + f * q.z;
-                ac[7] += c[1] * g[1];
-                ac[8] += c[1] * g[2] - f * q.x;
-                ac[9] += c[2] * g[0] - f * q.y;
-                ac[10] += c[2] * g[1] + f * q.x;
-                ac[11] += c[2] * g[2];
-            }
+            T f, c[3], g[3];
+            seg_pair<T, T, VN>(P, p, q, eps2, inv_l02, rc2n, inv_n, n_f, f, c, g);
+            acc[0] += f * c[0];
+            acc[1] += f * c[1];
+            acc[2] += f * c[2];
+            // f [r0]x + c g^T
+            acc[3] += c[0] * g[0];
+            acc[4] += c[0] * g[1] - f * q.z;
+            acc[5] += c[0] * g[2] + f * q.y;
+            acc[6] += c[1] * g[0] + f * q.z;
+            acc[7] += c[1] * g[1];
+            acc[8] += c[1] * g[2] - f * q.x;
+            acc[9] += c[2] * g[0] - f * q.y;
+            acc[10] += c[2] * g[1] + f * q.x;
+            acc[11] += c[2] * g[2];
         }
-        if constexpr (kComp) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) fold_tile<T, NA>(acc[k], hi[k], lo[k]);
-        }
+        if constexpr (kComp) fold_tile<T, NA>(acc, hi, lo);
     }
     T* __restrict__ U = static_cast<T*>(a.u);
     T* __restrict__ Jo = static_cast<T*>(a.grad);
     T* __restrict__ Do = static_cast<T*>(a.dg);
     const T* __restrict__ Gt = static_cast<const T*>(a.gt);
+    double v[NA];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        double v[NA];
+    for (int c = 0; c < NA; ++c) v[c] = kComp ? double(hi[c]) + double(lo[c]) : double(acc[c]);
+    // every lane takes part; each ends with the same sums
 #pragma unroll
-        for (int c = 0; c < NA; ++c) v[c] = kComp ? double(hi[k][c]) + double(lo[k][c]) : double(acc[k][c]);
-        if constexpr (LPT > 1) {  // every lane takes part; each ends with the same sums
+    for (int m = 1; m < LPT; m <<= 1)
 #pragma unroll
-            for (int m = 1; m < LPT; m <<= 1)
+        for (int c = 0; c < NA; ++c) v[c] += __shfl_xor(v[c], m, 64);
+    if (!valid || part != 0) return;
+    if (U) {
 #pragma unroll
-                for (int c = 0; c < NA; ++c) v[c] += __shfl_xor(v[c], m, 64);
+        for (int c = 0; c < 3; ++c) {
+            T* dst = U + c * a.ldo + t;
+            *dst = a.accumulate ? T(double(*dst) + v[c]) : T(v[c]);
         }
-        if (!valid[k] || q != 0) continue;
-        const int64_t t = t0 + tid + int64_t(k) * kSlots;
-        if (U) {
+    }
+    if (Jo) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                T* dst = U + c * a.ldo + t;
-                *dst = a.accumulate ? T(double(*dst) + v[c]) : T(v[c]);
-            }
+        for (int c = 0; c < 9; ++c) {
+            T* dst = Jo + c * a.ldo + t;
+            *dst = a.accumulate ? T(double(*dst) + v[3 + c]) : T(v[3 + c]);
         }
-        if (Jo) {
+    }
+    if (Do) {
+        const double g[3] = {double(Gt[t]), double(Gt[a.ldt + t]), double(Gt[2 * a.ldt + t])};
 #pragma unroll
-            for (int c = 0; c < 9; ++c) {
-                T* dst = Jo + c * a.ldo + t;
-                *dst = a.accumulate ? T(double(*dst) + v[3 + c]) : T(v[3 + c]);
-            }
-        }
-        if (Do) {
-            const double g[3] = {double(Gt[t]), double(Gt[a.ldt + t]), double(Gt[2 * a.ldt + t])};
+        for (int c = 0; c < 3; ++c) {
+            // transposed: sum_b J[b][c] g_b; classical: sum_b J[c][b] g_b
+            double s = 0.0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                // transposed: sum_b J[b][c] g_b; classical: sum_b J[c][b] g_b
-                double s = 0.0;
-#pragma unroll
-                for (int b = 0; b < 3; ++b) s += (a.classical ? v[3 + 3 * c + b] : v[3 + 3 * b + c]) * g[b];
-                T* dst = Do + c * a.ldo + t;
-                *dst = a.accumulate ? T(double(*dst) + s) : T(s);
-            }
+            for (int b = 0; b < 3; ++b) s += (a.classical ? v[3 + 3 * c + b] : v[3 + 3 * b + c]) * g[b];
+            T* dst = Do + c * a.ldo + t;
+            *dst = a.accumulate ? T(double(*dst) + s) : T(s);
         }
     }
 }
@@ -536,8 +512,10 @@ __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
 // runs on dual numbers with the point's tangent w1, so the tangent of J_ab is
 // d/dw1 J_ab and term_b = sum_a w2_a (d/dw1 J)_ab = f' (w2 x r0)_b + (w2 . c') g_b +
 // (w2 . c) g'_b (primes: tangents), with J = f [r0]x + c g^T.
-template <typename T, int WG, int VN>
+// LPT lanes per target share each staged tile as in k_segments_grad.
+template <typename T, int WG, int VN, int LPT>
 __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
+    static_assert((LPT & (LPT - 1)) == 0 && LPT <= 64, "a power of two within a wavefront");
     constexpr bool kComp = std::is_same<T, float>::value;
     constexpr int NA = 12;  // J row-major (9), term (3)
     using S = Dl<T>;
@@ -548,8 +526,8 @@ __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
     const T* __restrict__ Gt = static_cast<const T*>(a.gt);
     const T* __restrict__ Ub = static_cast<const T*>(a.ub);
     const T* __restrict__ Db = static_cast<const T*>(a.db);
-    const int tid = threadIdx.x;
-    const int64_t t = int64_t(blockIdx.x) * WG + tid;
+    const int part = threadIdx.x % LPT;
+    const int64_t t = int64_t(blockIdx.x) * (WG / LPT) + threadIdx.x / LPT;
     const bool valid = t < a.n_tgt;
     const int64_t tt = valid ? t : 0;
     const T n_f = T(a.vn);
@@ -578,7 +556,7 @@ __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
         __syncthreads();
         stage_segments<T, WG, VN>(a, j0, cnt, l0, l1, l2);
         __syncthreads();
-        for (int jj = 0; jj < cnt; ++jj) {
+        for (int jj = part; jj < cnt; jj += LPT) {
             const V4<T> p = l0[jj];
             const V4<T> q = l1[jj];
             const T eps2 = l2[jj].x;
@@ -606,10 +584,15 @@ __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
         }
         if constexpr (kComp) fold_tile<T, NA>(acc, hi, lo);
     }
-    if (!valid) return;
     double v[NA];
 #pragma unroll
     for (int c = 0; c < NA; ++c) v[c] = kComp ? double(hi[c]) + double(lo[c]) : double(acc[c]);
+    // every lane takes part; each ends with the same sums
+#pragma unroll
+    for (int m = 1; m < LPT; m <<= 1)
+#pragma unroll
+        for (int c = 0; c < NA; ++c) v[c] += __shfl_xor(v[c], m, 64);
+    if (!valid || part != 0) return;
     T* __restrict__ Xb = static_cast<T*>(a.xb);
     T* __restrict__ Gb = static_cast<T*>(a.gb);
     double ub[3] = {0.0, 0.0, 0.0};
@@ -652,45 +635,77 @@ hipError_t launch_t(const SegArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <typename T, int K, int WG, int LPT>
+template <typename T, int WG, int LPT>
 hipError_t launch_grad_t(const SegArgs& a, hipStream_t st) {
-    const int64_t per = int64_t(WG / LPT) * K;
+    const int64_t per = WG / LPT;
     const int grid = int((a.n_tgt + per - 1) / per);
     if (a.rc == 0.0)
-        hipLaunchKernelGGL((k_segments_grad<T, K, WG, 0, LPT>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_grad<T, WG, 0, LPT>), dim3(grid), dim3(WG), 0, st, a);
     else if (a.vn == 1)
-        hipLaunchKernelGGL((k_segments_grad<T, K, WG, 1, LPT>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_grad<T, WG, 1, LPT>), dim3(grid), dim3(WG), 0, st, a);
     else if (a.vn == 2)
-        hipLaunchKernelGGL((k_segments_grad<T, K, WG, 2, LPT>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_grad<T, WG, 2, LPT>), dim3(grid), dim3(WG), 0, st, a);
     else
-        hipLaunchKernelGGL((k_segments_grad<T, K, WG, 3, LPT>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_grad<T, WG, 3, LPT>), dim3(grid), dim3(WG), 0, st, a);
     return hipGetLastError();
 }
 
-// Lanes per target for the gradient kernel: one above kSegGradSplit1 targets (four or more
-// wavefronts per SIMD on 256 compute units), four above kSegGradSplit4, sixteen below.
-constexpr int64_t kSegGradSplit1 = 196608;
-constexpr int64_t kSegGradSplit4 = 16384;
+// Lanes per target of the gradient and adjoint kernels: 4, 16 or 64.  A workgroup then stages a
+// tile of 256 segments (about 150 VALU instructions per wavefront with the folds) for 256 / LPT
+// targets, and each of its lanes runs 256 / LPT pairs of `per_pair` instructions; about kSegSlots
+// workgroups are resident (four wavefronts per SIMD), so a launch takes
+// ceil(LPT n / 256 / kSegSlots) rounds of that.
+// Measured (4096 segments, exponent 2, FP32, us): adjoint with one lane per target at every size /
+// with this rule: 1000 targets 1914 / 54, 16384 1921 / 314, 150000 3671 / 2531, 400000 8274 / 6727;
+// gradient with 16 lanes up to 16384 targets, 4 up to 196608, 1 above / with this rule: 1000 73 /
+// 33, 20000 329 / 245, 100003 956 / 889, 200000 2126 / 1717, 400000 3585 / 3394.
+constexpr int64_t kSegSlots = 1024;
+constexpr int kGradPairOps = 120, kVjpPairOps = 300, kSegStageOps = 150;
+int lanes_per_target(int64_t n_tgt, int per_pair) {
+    int best = 0;
+    int64_t least = 0;
+    for (int lpt = 4; lpt <= 64; lpt *= 4) {
+        const int64_t per = 256 / lpt, wgs = (n_tgt + per - 1) / per;
+        const int64_t cost = (wgs + kSegSlots - 1) / kSegSlots * (per * per_pair + kSegStageOps);
+        if (best == 0 || cost < least) {
+            best = lpt;
+            least = cost;
+        }
+    }
+    return best;
+}
 
 template <typename T>
 hipError_t launch_grad_split(const SegArgs& a, hipStream_t st) {
-    if (a.n_tgt > kSegGradSplit1) return launch_grad_t<T, 1, 256, 1>(a, st);
-    if (a.n_tgt > kSegGradSplit4) return launch_grad_t<T, 1, 256, 4>(a, st);
-    return launch_grad_t<T, 1, 256, 16>(a, st);
+    switch (lanes_per_target(a.n_tgt, kGradPairOps)) {
+        case 4: return launch_grad_t<T, 256, 4>(a, st);
+        case 16: return launch_grad_t<T, 256, 16>(a, st);
+        default: return launch_grad_t<T, 256, 64>(a, st);
+    }
 }
 
-template <typename T, int WG>
+template <typename T, int WG, int LPT>
 hipError_t launch_vjp_t(const SegArgs& a, hipStream_t st) {
-    const int grid = int((a.n_tgt + WG - 1) / WG);
+    const int64_t per = WG / LPT;
+    const int grid = int((a.n_tgt + per - 1) / per);
     if (a.rc == 0.0)
-        hipLaunchKernelGGL((k_segments_vjp<T, WG, 0>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_vjp<T, WG, 0, LPT>), dim3(grid), dim3(WG), 0, st, a);
     else if (a.vn == 1)
-        hipLaunchKernelGGL((k_segments_vjp<T, WG, 1>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_vjp<T, WG, 1, LPT>), dim3(grid), dim3(WG), 0, st, a);
     else if (a.vn == 2)
-        hipLaunchKernelGGL((k_segments_vjp<T, WG, 2>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_vjp<T, WG, 2, LPT>), dim3(grid), dim3(WG), 0, st, a);
     else
-        hipLaunchKernelGGL((k_segments_vjp<T, WG, 3>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_vjp<T, WG, 3, LPT>), dim3(grid), dim3(WG), 0, st, a);
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_vjp_split(const SegArgs& a, hipStream_t st) {
+    switch (lanes_per_target(a.n_tgt, kVjpPairOps)) {
+        case 4: return launch_vjp_t<T, 256, 4>(a, st);
+        case 16: return launch_vjp_t<T, 256, 16>(a, st);
+        default: return launch_vjp_t<T, 256, 64>(a, st);
+    }
 }
 
 }  // namespace
@@ -703,8 +718,8 @@ hipError_t launch_segments_gradient(int dtype, const SegArgs& a, hipStream_t st)
 
 hipError_t launch_segments_vjp(int dtype, const SegArgs& a, hipStream_t st) {
     if (a.n_tgt == 0) return hipSuccess;
-    if (dtype == kDtypeF64) return launch_vjp_t<double, 256>(a, st);
-    return launch_vjp_t<float, 256>(a, st);
+    if (dtype == kDtypeF64) return launch_vjp_split<double>(a, st);
+    return launch_vjp_split<float>(a, st);
 }
 
 template <typename T>

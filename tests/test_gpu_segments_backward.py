@@ -151,3 +151,18 @@ def test_rk3_program_with_lattice_gradient_vs_oracle_tangents(kind, gpu):
     X2, G2 = dev(x, "f64").requires_grad_(True), dev(g, "f64").requires_grad_(True)
     AG.rk3_program_loss(X2, G2, dev(s, ek), steps, dt, dev(y, ek)).backward()
     assert rel_l2(host(X2.grad), gx) > 1e-3  # 0.46 % here
+
+
+@pytest.mark.parametrize("kind", KINDS)
+# the edges of a workgroup's 4, 16 or 64 targets and of the 256-segment tile
+@pytest.mark.parametrize("n,n_seg", [(1, 257), (5, 255), (4097, 300), (16385, 256), (66001, 65)])
+def test_segments_gradient_and_vjp_at_split_sizes(kind, n, n_seg, gpu):
+    a, b, gs, x, g, ub, db = _case(kind, n=max(n, 16), seed=7)
+    a, b, gs, x, g, ub, db = a[:, :n_seg], b[:, :n_seg], gs[:n_seg], x[:, :n], g[:, :n], ub[:, :n], db[:, :n]
+    D = [dev(v, kind) for v in (a, b, gs, x)]
+    say(f"segments split {kind} n={n} n_seg={n_seg}")
+    _, J, _ = vpm.vpm_eval_segments_gradient(*D, 0.02, 2)
+    assert rel_l2(host(J), oracle.segments_gradient(a, b, gs, x, 0.02, 2).reshape(9, -1)) <= TOL[kind]
+    xb, gb = vpm.vpm_segments_backward(*D, 0.02, 2, dev(ub, kind), dev(db, kind), gamma_tgt=dev(g, kind))
+    xo, go = oracle.segments_vjp(a, b, gs, x, 0.02, 2, ub, db, g)
+    assert rel_l2(host(xb), xo) <= TOL[kind] and rel_l2(host(gb), go) <= TOL[kind]
