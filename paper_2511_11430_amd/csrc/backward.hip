@@ -280,41 +280,6 @@ struct Bwd {
     }
 };
 
-// A value moved between lanes by a DPP control; lanes the move does not reach keep their own.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_move(float v) {
-    const int i = __float_as_int(v);
-    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xf, false));
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_move(double v) {
-    const int64_t b = __double_as_longlong(v);
-    const int lo = int(uint32_t(b)), hi = int(uint32_t(uint64_t(b) >> 32));
-    const uint32_t l2 = uint32_t(__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false));
-    const uint32_t h2 = uint32_t(__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false));
-    return __longlong_as_double(int64_t((uint64_t(h2) << 32) | l2));
-}
-// Minimum of v[0..2] and maximum of v[3..6] over a wavefront, valid in lane 63: row shifts by 1,
-// 2, 4 and 8, then the two row broadcasts (lane 15 of rows 0 and 2 into the next row, lane 31
-// into rows 2 and 3).  One register move per step where a shuffle goes through the LDS unit.
-template <int CTRL, int ROWS, typename T>
-__device__ __forceinline__ void minmax_step(T (&v)[7]) {
-#pragma unroll
-    for (int c = 0; c < 7; ++c) {
-        const T o = dpp_move<CTRL, ROWS>(v[c]);
-        v[c] = c < 3 ? fmin(v[c], o) : fmax(v[c], o);
-    }
-}
-template <typename T>
-__device__ __forceinline__ void wave_minmax_last(T (&v)[7]) {
-    minmax_step<0x111, 0xf>(v);  // row_shr:1
-    minmax_step<0x112, 0xf>(v);  // row_shr:2
-    minmax_step<0x114, 0xf>(v);  // row_shr:4
-    minmax_step<0x118, 0xf>(v);  // row_shr:8
-    minmax_step<0x142, 0xa>(v);  // row_bcast:15
-    minmax_step<0x143, 0xc>(v);  // row_bcast:31
-}
-
 // Workgroup bounding box (v[0..2] min, v[3..5] max) and largest cut (v[6]): a shuffle
 // reduction per wavefront, then LDS.  Ends with a barrier; every thread gets the result.
 template <typename T>

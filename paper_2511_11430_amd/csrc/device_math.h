@@ -190,6 +190,41 @@ __device__ __forceinline__ void wave_box(const T (&lo)[3], const T (&hi)[3], T c
     ocut = v[6];
 }
 
+// A value moved between lanes by a DPP control; lanes the move does not reach keep their own.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_move(float v) {
+    const int i = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double v) {
+    const int64_t b = __double_as_longlong(v);
+    const int lo = int(uint32_t(b)), hi = int(uint32_t(uint64_t(b) >> 32));
+    const uint32_t l2 = uint32_t(__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false));
+    const uint32_t h2 = uint32_t(__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false));
+    return __longlong_as_double(int64_t((uint64_t(h2) << 32) | l2));
+}
+// Minimum of v[0..2] and maximum of v[3..6] over a wavefront, valid in lane 63: row shifts by 1,
+// 2, 4 and 8, then the two row broadcasts (lane 15 of rows 0 and 2 into the next row, lane 31
+// into rows 2 and 3).  One register move per step where a shuffle goes through the LDS unit.
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ void minmax_step(T (&v)[7]) {
+#pragma unroll
+    for (int c = 0; c < 7; ++c) {
+        const T o = dpp_move<CTRL, ROWS>(v[c]);
+        v[c] = c < 3 ? fmin(v[c], o) : fmax(v[c], o);
+    }
+}
+template <typename T>
+__device__ __forceinline__ void wave_minmax_last(T (&v)[7]) {
+    minmax_step<0x111, 0xf>(v);  // row_shr:1
+    minmax_step<0x112, 0xf>(v);  // row_shr:2
+    minmax_step<0x114, 0xf>(v);  // row_shr:4
+    minmax_step<0x118, 0xf>(v);  // row_shr:8
+    minmax_step<0x142, 0xa>(v);  // row_bcast:15
+    minmax_step<0x143, 0xc>(v);  // row_bcast:31
+}
+
 // A value known to be equal in every lane, moved to a scalar register.
 __device__ __forceinline__ float uniform(float v) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
@@ -201,25 +236,18 @@ __device__ __forceinline__ double uniform(double v) {
     return __longlong_as_double((static_cast<unsigned long long>(unsigned(hi)) << 32) | unsigned(lo));
 }
 
-// Workgroup-wide bounding box (lo, hi per component) and maximum cut: a shuffle reduction in
-// each wavefront, then the wavefront results through LDS (scratch: 7 values per wavefront).
+// Workgroup-wide bounding box (lo, hi per component) and maximum cut: a reduction by register
+// moves in each wavefront, then the wavefront results through LDS (scratch: 7 values per wavefront).
 // Ends with a barrier; every thread receives the result.
 template <typename T>
 __device__ __forceinline__ void block_box(const T (&lo)[3], const T (&hi)[3], T cut, T (&olo)[3], T (&ohi)[3],
                                           T& ocut, T* scratch) {
     T v[7] = {lo[0], lo[1], lo[2], hi[0], hi[1], hi[2], cut};
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-        for (int c = 0; c < 7; ++c) {
-            const T o = __shfl_xor(v[c], off, 64);
-            v[c] = c < 3 ? fmin(v[c], o) : fmax(v[c], o);
-        }
-    }
+    wave_minmax_last(v);
     const int wave = threadIdx.x >> 6;
     const int nwave = (blockDim.x + 63) >> 6;
     __syncthreads();  // previous readers of scratch are done
-    if ((threadIdx.x & 63) == 0) {
+    if ((threadIdx.x & 63) == 63) {
 #pragma unroll
         for (int c = 0; c < 7; ++c) scratch[wave * 7 + c] = v[c];
     }

@@ -523,18 +523,53 @@ __global__ __launch_bounds__(WG) void k_pair_fwd(FwdArgs a) {
     B::run(a, s0, s1, t0, t1, a.src_begin - a.tgt_begin, lp, lq, ls, box, chunk_id);
 }
 
-// Adds the per-chunk FP64 partials of every target in chunk order and stores the result.
-template <typename T, int MODE>
-__global__ __launch_bounds__(256) void k_pair_fwd_finish(FwdArgs a) {
+// Do the n sources from b on overlap the m sources from j on?
+__device__ __forceinline__ bool ex_overlap(int64_t b, int n, int64_t j, int m) { return b < j + m && j < b + n; }
+
+// One slice of a staged tile for the sliced form: the sources first, first + step, ...
+template <typename T, int MODE, bool SYM, bool CHECK, bool NEAR>
+__device__ __forceinline__ void slice_tile(const typename SrcTile<T>::V4 (*lsrc)[256], const T* ls, int first, int step,
+                                           int cnt, int64_t j0, const T (&xi)[3], const T (&gi)[3], T ngi1, T ngi2,
+                                           T cut_i, int64_t ex, T* acc) {
+#pragma unroll 2
+    for (int jj = first; jj < cnt; jj += step) {
+        const typename SrcTile<T>::V4 p = lsrc[0][jj], q = lsrc[1][jj];
+        pair_fwd<T, MODE, SYM, CHECK, NEAR>(p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w, ls + jj, xi[0], xi[1], xi[2],
+                                            gi[0], gi[1], gi[2], ngi1, ngi2, cut_i, j0 + jj, ex, acc, acc);
+    }
+}
+
+// Adds the per-chunk FP64 partials of every target and stores the result.  L targets per
+// workgroup, G groups of lanes: group g adds the chunks g, g + G, ... in order, then the groups'
+// sums are added in group order.  Bound by the latency of a lane's loads: with one lane per
+// target, 128 targets of 1024 chunks took 266 us (328 us with the pair kernel, now 41).
+template <typename T, int MODE, int L, int G>
+__global__ __launch_bounds__(L * G) void k_pair_fwd_finish(FwdArgs a) {
     constexpr int kNacc = nacc_of(MODE);
-    const int64_t t = a.tgt_begin + int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (t >= a.tgt_end) return;
+    __shared__ double sum[G][L];
+    const int l = threadIdx.x % L, g = threadIdx.x / L;
+    const int64_t t = a.tgt_begin + int64_t(blockIdx.x) * L + l;
+    const bool valid = t < a.tgt_end;
+    const int64_t tt = valid ? t : a.tgt_begin;
     double tot[kNacc];
 #pragma unroll
     for (int c = 0; c < kNacc; ++c) tot[c] = 0.0;
-    for (int ch = 0; ch < a.nchunk; ++ch)
+#pragma unroll 4
+    for (int ch = g; ch < a.nchunk; ch += G)
 #pragma unroll
-        for (int c = 0; c < kNacc; ++c) tot[c] += a.part[(int64_t(ch) * kNacc + c) * a.tgt_end + t];
+        for (int c = 0; c < kNacc; ++c) tot[c] += a.part[(int64_t(ch) * kNacc + c) * a.tgt_end + tt];
+#pragma unroll
+    for (int c = 0; c < kNacc; ++c) {
+        sum[g][l] = tot[c];
+        __syncthreads();
+        if (g == 0) {
+            double v = sum[0][l];
+            for (int k = 1; k < G; ++k) v += sum[k][l];
+            tot[c] = v;
+        }
+        __syncthreads();
+    }
+    if (g != 0 || !valid) return;
     double g0 = 0.0, g1 = 0.0, g2 = 0.0;
     if (MODE != kModeVelocity) {
         const T* gt = static_cast<const T*>(a.gt);
@@ -543,6 +578,167 @@ __global__ __launch_bounds__(256) void k_pair_fwd_finish(FwdArgs a) {
         g2 = double(gt[2 * a.ldt + t]);
     }
     store_target<T, MODE>(a, t, g0, g1, g2, tot);
+}
+
+// Sliced form for target sets too small to fill the chip with a target per lane: a workgroup of
+// 256 lanes owns P = 2^lp <= 64 targets and its lanes form 256 / P slices that share each staged
+// tile of 256 sources (lane tid: target tid mod P, slice tid / P, which takes the tile's sources
+// slice, slice + 256 / P, ...).  The slices' sums are added in FP64, by shuffles within a
+// wavefront and through LDS across wavefronts, in a fixed order; with nchunk > 1 the workgroup
+// sees one chunk of the sources and leaves partial sums for k_pair_fwd_finish.
+// FP32 sums run over at most 256 sources between folds; near tiles, whose terms are large, are
+// folded at once (at most 64 terms of a near tile per sum, so they need no second set of sums).
+// The work per source tile of a wavefront is P pairs per lane, plus staging and two reductions.
+// Bound by VALU issue from about 5000 targets on, below by the latency of a tile (three barriers
+// and a load, 2 us).  Small target boxes also leave fewer tiles near: 65536 hover particles take
+// 3040 us in blocks of 64 and 3130 in blocks of 256, both with 16 chunks (FP64 7260 and 8970).
+// Measured (us per call, a target per lane with 256-source chunks / this form): 300 particles
+// 66 / 17, 1021 80 / 17, 2500 109 / 25, 4999 108 / 47; 4096 in a cube in FP64 282 / 159.
+template <typename T, int MODE, bool SYM>
+__global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
+    constexpr int WG = 256, kWaves = WG / 64;
+    constexpr bool kComp = std::is_same<T, float>::value;
+    constexpr int kNacc = nacc_of(MODE);
+    using V4 = typename SrcTile<T>::V4;
+    __shared__ V4 lsrc[2][WG];  // p and q of FwdBlock; later the other wavefronts' sums
+    __shared__ T ls[WG];
+    __shared__ T box[7 * kWaves];
+    const T* __restrict__ xs = static_cast<const T*>(a.xs);
+    const T* __restrict__ gs = static_cast<const T*>(a.gs);
+    const T* __restrict__ ss = static_cast<const T*>(a.ss);
+    const T* __restrict__ xt = static_cast<const T*>(a.xt);
+    const T* __restrict__ gt = static_cast<const T*>(a.gt);
+    const T* __restrict__ st = static_cast<const T*>(a.st);
+    const T far2 = T(Prec<T>::kFarRho2);
+    const int tid = threadIdx.x;
+    const int np = 1 << lp, slice = tid >> lp, nslice = WG >> lp;
+    const int64_t t0 = a.tgt_begin + (int64_t(blockIdx.x) << lp);
+    const int64_t t = t0 + (tid & (np - 1));
+    const bool valid = t < a.tgt_end;
+    const int64_t tt = valid ? t : t0;
+    int64_t s0 = a.src_begin, s1 = a.src_end;
+    if (a.nchunk > 1) {
+        s0 += int64_t(blockIdx.y) * a.chunk;
+        s1 = s0 + a.chunk < s1 ? s0 + a.chunk : s1;
+    }
+    const T xi[3] = {xt[tt], xt[a.ldt + tt], xt[2 * a.ldt + tt]};
+    T gi[3] = {T(0), T(0), T(0)};
+    if (MODE != kModeVelocity) {
+        gi[0] = gt[tt];
+        gi[1] = gt[a.ldt + tt];
+        gi[2] = gt[2 * a.ldt + tt];
+    }
+    // (kept opaque so that the products stay plain multiplies by a register)
+    const T ngi1 = opaque(-gi[1]), ngi2 = opaque(-gi[2]);
+    T cut_i = T(0);
+    if (SYM) {
+        const T sg = st[tt];
+        cut_i = T(0.5) * far2 * sg * sg;
+    }
+    int64_t ex = -2;
+    if (valid) {
+        if (a.self) ex = t + (a.src_begin - a.tgt_begin);
+        else if (a.excl) ex = int64_t(a.excl[t]);
+    }
+    T blo[3], bhi[3], bcut;
+    block_box(xi, xi, cut_i, blo, bhi, bcut, box);
+
+    T acc[kNacc], hi[kNacc], lo[kNacc];
+#pragma unroll
+    for (int c = 0; c < kNacc; ++c) acc[c] = hi[c] = lo[c] = T(0);
+    int since = 0;  // sources in the FP32 sums since the last fold
+    for (int64_t j0 = s0; j0 < s1; j0 += WG) {
+        const int cnt = int((s1 - j0) < WG ? (s1 - j0) : WG);
+        __syncthreads();
+        {
+            // lanes past the end repeat the tile's first source, which is in the box already
+            const int64_t j = j0 + (tid < cnt ? tid : 0);
+            const T sg = ss[j];
+            V4 p, q;
+            p.x = xs[j];
+            p.y = xs[a.lds + j];
+            p.z = xs[2 * a.lds + j];
+            q.x = gs[j];
+            q.y = gs[a.lds + j];
+            q.z = gs[2 * a.lds + j];
+            q.w = SYM ? T(0.5) * far2 * sg * sg : far2 * sg * sg;
+            p.w = -q.z;
+            lsrc[0][tid] = p;
+            lsrc[1][tid] = q;
+            ls[tid] = T(1) / sg;
+            const T pl[3] = {p.x, p.y, p.z};
+            T tlo[3], thi[3], tcut;
+            block_box(pl, pl, q.w, tlo, thi, tcut, box);
+            bool check;
+            if (a.self) check = ex_overlap(t0 + (a.src_begin - a.tgt_begin), np, j0, cnt);
+            else check = a.excl && __syncthreads_or(ex >= j0 && ex < j0 + cnt);
+            T d2 = T(0);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const T gap = fmax(fmax(tlo[c] - bhi[c], blo[c] - thi[c]), T(0));
+                d2 += gap * gap;
+            }
+            const bool near = d2 < (SYM ? tcut + bcut : tcut);
+            if (check) {
+                if (near) slice_tile<T, MODE, SYM, true, true>(lsrc, ls, slice, nslice, cnt, j0, xi, gi, ngi1, ngi2, cut_i, ex, acc);
+                else slice_tile<T, MODE, SYM, true, false>(lsrc, ls, slice, nslice, cnt, j0, xi, gi, ngi1, ngi2, cut_i, ex, acc);
+            } else {
+                if (near) slice_tile<T, MODE, SYM, false, true>(lsrc, ls, slice, nslice, cnt, j0, xi, gi, ngi1, ngi2, cut_i, ex, acc);
+                else slice_tile<T, MODE, SYM, false, false>(lsrc, ls, slice, nslice, cnt, j0, xi, gi, ngi1, ngi2, cut_i, ex, acc);
+            }
+            since += np;  // WG / nslice
+            if constexpr (kComp) {
+                if (near || since >= WG || j0 + WG >= s1) {
+                    since = 0;
+#pragma unroll
+                    for (int c = 0; c < kNacc; ++c) {  // as FwdBlock::fold
+                        const T y = acc[c] + lo[c];
+                        const T h = hi[c] + y;
+                        lo[c] = y - (h - hi[c]);
+                        hi[c] = h;
+                        acc[c] = T(0);
+                    }
+                }
+            }
+        }
+    }
+    double tot[kNacc];
+#pragma unroll
+    for (int c = 0; c < kNacc; ++c)
+        tot[c] = held_sign(MODE, c) * (kComp ? double(hi[c]) + double(lo[c]) : double(acc[c]));
+    for (int off = np; off < 64; off <<= 1)
+#pragma unroll
+        for (int c = 0; c < kNacc; ++c) tot[c] += __shfl_xor(tot[c], off, 64);
+    // every wavefront holds the same targets: the tile's LDS carries the sums of wavefronts 1 ...
+    // to wavefront 0, kPer sums at a time
+    constexpr int kFit = int(sizeof(lsrc) / ((kWaves - 1) * 64 * sizeof(double)));
+    constexpr int kPer = kFit < kNacc ? kFit : kNacc;
+    double(*red)[kPer][64] = reinterpret_cast<double(*)[kPer][64]>(&lsrc[0][0]);
+    const int wave = tid >> 6, lane = tid & 63;
+#pragma unroll
+    for (int c0 = 0; c0 < kNacc; c0 += kPer) {
+        __syncthreads();
+        if (wave > 0) {
+#pragma unroll
+            for (int c = 0; c < kPer; ++c)
+                if (c0 + c < kNacc) red[wave - 1][c][lane] = tot[c0 + c];
+        }
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int w = 0; w < kWaves - 1; ++w)
+#pragma unroll
+                for (int c = 0; c < kPer; ++c)
+                    if (c0 + c < kNacc) tot[c0 + c] += red[w][c][lane];
+        }
+    }
+    if (tid >= np || !valid) return;
+    if (a.nchunk > 1) {
+#pragma unroll
+        for (int c = 0; c < kNacc; ++c) a.part[(int64_t(blockIdx.y) * kNacc + c) * a.tgt_end + t] = tot[c];
+    } else {
+        store_target<T, MODE>(a, t, gi[0], gi[1], gi[2], tot);
+    }
 }
 
 // Persistent workgroups over a queue of (set, target block) items in decreasing cost order.
@@ -575,6 +771,18 @@ __global__ __launch_bounds__(WG) void k_pair_fwd_batched(FwdArgs a, BatchQueue b
 // ------------------------------------------------------------------ host-side launchers
 namespace {
 
+// Few targets have many chunks each and take 64 groups of lanes; many fill the chip with four.
+constexpr int64_t kFinishFew = 8192;
+template <typename T, int MODE>
+hipError_t launch_finish(const FwdArgs& a, hipStream_t st) {
+    const int64_t nt = a.tgt_end - a.tgt_begin;
+    if (nt <= kFinishFew)
+        hipLaunchKernelGGL((k_pair_fwd_finish<T, MODE, 16, 64>), dim3(unsigned((nt + 15) / 16)), dim3(1024), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_pair_fwd_finish<T, MODE, 64, 4>), dim3(unsigned((nt + 63) / 64)), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
 template <typename T, int K, int WG, int MODE, bool SYM, int U>
 hipError_t launch_one(const FwdArgs& a, const BatchQueue* bq, int grid, hipStream_t st) {
     if (bq) {
@@ -585,9 +793,36 @@ hipError_t launch_one(const FwdArgs& a, const BatchQueue* bq, int grid, hipStrea
     hipLaunchKernelGGL((k_pair_fwd<T, K, WG, MODE, SYM, U>), dim3(grid, ny), dim3(WG), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || ny == 1) return e;
+    return launch_finish<T, MODE>(a, st);
+}
+
+template <typename T, int MODE, bool SYM>
+hipError_t launch_slice(const FwdArgs& a, int lp, hipStream_t st) {
     const int64_t nt = a.tgt_end - a.tgt_begin;
-    hipLaunchKernelGGL((k_pair_fwd_finish<T, MODE>), dim3(int((nt + 255) / 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
+    const unsigned grid = unsigned((nt + (int64_t(1) << lp) - 1) >> lp);
+    const unsigned ny = a.nchunk > 1 ? unsigned(a.nchunk) : 1u;
+    hipLaunchKernelGGL((k_pair_fwd_slice<T, MODE, SYM>), dim3(grid, ny), dim3(256), 0, st, a, lp);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || ny == 1) return e;
+    return launch_finish<T, MODE>(a, st);
+}
+
+template <typename T>
+hipError_t launch_slice_mode(int mode, bool sym, const FwdArgs& a, int lp, hipStream_t st) {
+    switch (mode) {
+        case kModeTransposed:
+            return sym ? launch_slice<T, kModeTransposed, true>(a, lp, st)
+                       : launch_slice<T, kModeTransposed, false>(a, lp, st);
+        case kModeClassical:
+            return sym ? launch_slice<T, kModeClassical, true>(a, lp, st)
+                       : launch_slice<T, kModeClassical, false>(a, lp, st);
+        case kModeVelocity:
+            return sym ? launch_slice<T, kModeVelocity, true>(a, lp, st)
+                       : launch_slice<T, kModeVelocity, false>(a, lp, st);
+        default:
+            return sym ? launch_slice<T, kModeGradient, true>(a, lp, st)
+                       : launch_slice<T, kModeGradient, false>(a, lp, st);
+    }
 }
 
 template <typename T, int K, int WG, int MODE, bool SYM, int U>
@@ -653,6 +888,12 @@ hipError_t launch_pair_fwd(int dtype, int variant, int mode, bool sym, const Fwd
 #undef X
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_pair_fwd_slice(int dtype, int mode, bool sym, const FwdArgs& a, int lp, hipStream_t st) {
+    if (lp < 0 || lp > 6) return hipErrorInvalidValue;
+    return dtype == kDtypeF64 ? launch_slice_mode<double>(mode, sym, a, lp, st)
+                              : launch_slice_mode<float>(mode, sym, a, lp, st);
 }
 
 int pair_fwd_occupancy(int dtype, int variant, int mode, bool sym, bool batched) {

@@ -267,18 +267,22 @@ int64_t targets_per_block(int32_t dtype, int variant) {
     return int64_t(vpm::kF32Variants[variant].k) * vpm::kF32Variants[variant].wg;
 }
 
-// Source split for one small target set: when there are fewer target blocks than
-// kSplitBelow, the sources are cut into chunks (multiples of 256, at least kMinChunk) so that
-// about kSplitGoal workgroups run; partial sums go to the workspace.  Depends only on sizes.
-constexpr int64_t kSplitBelow = 1024;
-constexpr int64_t kSplitGoal = 2048;
-constexpr int64_t kMinChunk = 256;
-
+// How one set of targets is spread over the chip: blocks of 2^lp targets in the sliced form
+// (lp <= 6) or of one or two targets per lane (lp = kPlainLp), and the sources in nchunk chunks
+// (multiples of 256) whose partial sums go to the workspace.  Depends only on sizes.
+constexpr int kPlainLp = 8;
 struct SplitPlan {
+    int lp = kPlainLp;
     int64_t nchunk = 1, chunk = 0;
     size_t bytes = 0;
 };
-SplitPlan split_plan(int32_t dtype, int variant, int nacc, int64_t n_src, int64_t n_tgt) {
+
+// A caller's own kernel shape: fewer target blocks than kSplitBelow are split into chunks of at
+// least kMinChunk sources so that about kSplitGoal workgroups run.
+constexpr int64_t kSplitBelow = 1024;
+constexpr int64_t kSplitGoal = 2048;
+constexpr int64_t kMinChunk = 256;
+SplitPlan shape_split(int32_t dtype, int variant, int nacc, int64_t n_src, int64_t n_tgt) {
     SplitPlan p;
     p.chunk = n_src;
     const int64_t per_block = targets_per_block(dtype, variant);
@@ -299,6 +303,54 @@ SplitPlan split_plan(int32_t dtype, int variant, int nacc, int64_t n_src, int64_
     }
     p.bytes = align_up(size_t(p.nchunk) * size_t(nacc) * size_t(n_tgt) * sizeof(double));
     return p;
+}
+
+// The library's own choice for one set: the cheapest by this count of a wavefront's VALU
+// instructions (3.5 ns each with four wavefronts per SIMD).  A 256-source tile costs P pairs per
+// lane (about 30 instructions in FP32, twice that in FP64) and kTile for staging and reductions,
+// and no less than kLatency, a workgroup kGroup more; about 1024 workgroups are resident, fewer
+// run each wavefront faster, and the last ones leave a tail, so x rounds take 0.6 + 0.4 x or
+// x + 0.3, whichever is more; chunks add the finishing launch and its traffic.  In FP64, where a
+// pair in a core is a call, the 256-target blocks pay a fifth for the tiles that are near them and
+// not near 64-target blocks.  Partial sums are held to kMaxPartials, and to `room` bytes.
+// Measured (us, shape_split / this rule): 10000 hover particles 132 / 115, 65536 3500 / 3190
+// (flight 3320 / 2860), 20000 in FP64 1297 / 923, 128 points of 262144 particles 331 / 41, 4096
+// points of 100000 281 / 232, 8000 points of a million 5050 / 3830.
+constexpr size_t kMaxPartials = size_t(96) << 20;
+SplitPlan auto_split(int32_t dtype, int nacc, int64_t n_src, int64_t n_tgt, size_t room) {
+    constexpr int64_t kSlots = 1024, kTile = 170, kLatency = 400, kGroup = 300, kFinish = 1500;
+    const int64_t pair = dtype == kDtypeF64 ? 60 : 30;
+    if (room > kMaxPartials) room = kMaxPartials;
+    SplitPlan best;
+    best.chunk = n_src;
+    if (n_src < 1 || n_tgt < 1) return best;
+    double least = -1.0;
+    for (int lp : {2, 3, 4, 5, 6, kPlainLp}) {
+        const int64_t blocks = (n_tgt + (int64_t(1) << lp) - 1) >> lp;
+        const int64_t tile = (pair << lp) * (lp == kPlainLp && dtype == kDtypeF64 ? 6 : 5) / 5 + kTile;
+        // 1, 2, 3, 4, 6, 8, 12, ... chunks
+        for (int64_t want = 1; want == 1 || n_src / want >= kMinChunk;
+             want += want == 1 || (want & (want - 1)) ? (want + 2) / 3 : want / 2) {
+            const int64_t chunk = want == 1 ? n_src : ((n_src + want - 1) / want + 255) / 256 * 256;
+            const int64_t nchunk = (n_src + chunk - 1) / chunk;
+            const size_t bytes =
+                nchunk > 1 ? align_up(size_t(nchunk) * size_t(nacc) * size_t(n_tgt) * sizeof(double)) : 0;
+            if (bytes > room) break;
+            const double x = double(blocks) * double(nchunk) / kSlots;
+            const double rounds = std::max(0.6 + 0.4 * x, x + 0.3);
+            const double tiles = double((chunk + 255) / 256);
+            const double cost = std::max(rounds * (tiles * double(tile) + kGroup),
+                                         tiles * double(std::max(tile, kLatency)) + kGroup) +
+                                (nchunk > 1 ? kFinish + double(bytes) / 7000.0 : 0.0);
+            if (least >= 0.0 && cost >= least) continue;
+            least = cost;
+            best.lp = lp;
+            best.chunk = chunk;
+            best.nchunk = nchunk;
+            best.bytes = bytes;
+        }
+    }
+    return best;
 }
 
 // The same split with as many chunks as `bytes` of partial sums hold (none below two).
@@ -364,8 +416,10 @@ vpm_status classical_backward(int32_t dtype, bool sym, bool self, int64_t n_src,
     f.part = nullptr; f.chunk = n_src; f.nchunk = 1;
     vpm_options fo = default_options();
     fo.self = self ? 1 : 0;
-    const int variant = choose_variant(fo, false, n_tgt);
     const int mode = fwd_mode(fo, true);
+    const int lp = auto_split(dtype, vpm::nacc_of(mode), n_src, n_tgt, 0).lp;  // (no workspace here)
+    if (lp != kPlainLp) return hip_status(vpm::launch_pair_fwd_slice(dtype, mode, sym, f, lp, st));
+    const int variant = choose_variant(fo, false, n_tgt);
     const int64_t per_block = targets_per_block(dtype, variant);
     const int64_t grid = (n_tgt + per_block - 1) / per_block;
     return hip_status(vpm::launch_pair_fwd(dtype, variant, mode, sym, f, nullptr, int(grid), st));
@@ -456,9 +510,10 @@ size_t vpm_workspace_size(int32_t dtype, int32_t n_batch, const int64_t* src_off
     if (check_offsets(n_batch, src_off) != VPM_OK || check_offsets(n_batch, tgt_off) != VPM_OK) return 0;
     if (check_options(o) != VPM_OK) return 0;
     if (n_batch == 1) {
-        const int variant = choose_variant(o, false, tgt_off[1]);
         const int nacc = o.gradient ? vpm::nacc_of(vpm::kModeGradient) : vpm::nacc_of(vpm::kModeTransposed);
-        return split_plan(dtype, variant, nacc, src_off[1], tgt_off[1]).bytes;
+        if (o.variant > 0 && !o.gradient)
+            return shape_split(dtype, o.variant - 1, nacc, src_off[1], tgt_off[1]).bytes;
+        return auto_split(dtype, nacc, src_off[1], tgt_off[1], kMaxPartials).bytes;
     }
     return queue_layout(n_batch, tgt_off, kMinTargetsPerBlock).total;
 }
@@ -575,14 +630,26 @@ vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, con
     const int64_t per_block = targets_per_block(dtype, variant);
 
     if (n_batch == 1) {
-        SplitPlan sp = split_plan(dtype, variant, vpm::nacc_of(mode), n_src, n_tgt);
-        if (noalloc && sp.nchunk > 1 && sp.bytes > ws_bytes)
-            sp = fit_plan(sp, vpm::nacc_of(mode), n_src, n_tgt, ws_bytes);
-        if (sp.nchunk > 1 && workspace && ws_bytes >= sp.bytes) {
+        const size_t room = workspace ? ws_bytes : 0;
+        SplitPlan sp;
+        if (o.variant > 0) {
+            sp = shape_split(dtype, variant, vpm::nacc_of(mode), n_src, n_tgt);
+            if (noalloc && sp.bytes > room) sp = fit_plan(sp, vpm::nacc_of(mode), n_src, n_tgt, room);
+            if (sp.bytes > room) {
+                sp.nchunk = 1;
+                sp.chunk = n_src;
+            }
+        } else {
+            // velocity only counts the nine sums of the stretching modes, as vpm_workspace_size does
+            sp = auto_split(dtype, vpm::nacc_of(o.gradient ? vpm::kModeGradient : vpm::kModeTransposed), n_src, n_tgt,
+                            room);
+        }
+        if (sp.nchunk > 1) {
             a.part = static_cast<double*>(workspace);
             a.chunk = sp.chunk;
             a.nchunk = int32_t(sp.nchunk);
         }
+        if (sp.lp != kPlainLp) return hip_status(vpm::launch_pair_fwd_slice(dtype, mode, sym, a, sp.lp, st));
         const int64_t grid = (n_tgt + per_block - 1) / per_block;
         return hip_status(vpm::launch_pair_fwd(dtype, variant, mode, sym, a, nullptr, int(grid), st));
     }

@@ -263,6 +263,37 @@ def test_source_split_for_small_target_sets(kind, gpu):
 
 
 @pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("mode", ["velocity", "transposed", "classical", "gradient"])
+# (sources, targets): a lone pair, block edges (4 to 64 targets), tile edges, few targets with many
+# chunks, more targets than sources, and sets whose sources are both sliced and chunked
+@pytest.mark.parametrize("ns,nt", [(1, 1), (3, 5), (255, 257), (257, 4), (2500, 63), (30011, 129), (300, 8193),
+                                   (9001, 9001)])
+def test_sliced_and_chunked_targets(kind, mode, ns, nt, gpu):
+    import torch
+    rng = np.random.default_rng([29, ns, nt])
+    x, g, s = prepare(_random_set(ns, 31, spread=0.5), kind)
+    y, gy, sy = prepare(_random_set(nt, 37, spread=0.5), kind)
+    ex = rng.integers(0, ns, nt)
+    y[:, ::3] = x[:, ex[::3]]  # every third target is its excluded source
+    sc = 1 if mode == "classical" else 0
+    A = [dev_(v, kind) for v in (x, g, s, y, gy, sy)]
+    E = torch.tensor(ex.astype(np.int32), device="cuda")
+    say(f"sliced {kind} {mode} {ns} -> {nt}")
+    uo, do = oracle.eval_pairs(x, g, s, x_tgt=y, gam_tgt=gy, sig_tgt=sy, excl=ex, scheme=sc, sigma_rule=1)
+    if mode == "velocity":
+        u, d = vpm.vpm_eval_velocity_stretching(*A, tgt_exclude=E, velocity_only=True, sigma_rule=1)
+    elif mode == "gradient":
+        u, d, _ = vpm.vpm_eval_velocity_gradient(*A, tgt_exclude=E, sigma_rule=1)
+    else:
+        u, d = vpm.vpm_eval_velocity_stretching(*A, tgt_exclude=E, scheme=sc, sigma_rule=1)
+    if ns == 1 and nt == 1:
+        assert np.all(host(u) == 0)
+        return
+    assert rel_l2(host(u), uo) <= TOL[kind]
+    assert d is None or rel_l2(host(d), do) <= TOL[kind]
+
+
+@pytest.mark.parametrize("kind", KINDS)
 def test_permutation_invariance(kind, gpu):
     """Shuffling the particles changes every tile and the summation order; results agree to
     rounding (also a guard against LDS races: a missing barrier would not reproduce)."""
