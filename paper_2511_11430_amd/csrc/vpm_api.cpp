@@ -312,13 +312,19 @@ SplitPlan shape_split(int32_t dtype, int variant, int nacc, int64_t n_src, int64
 // run each wavefront faster, and the last ones leave a tail, so x rounds take 0.6 + 0.4 x or
 // x + 0.3, whichever is more; chunks add the finishing launch and its traffic.  In FP64, where a
 // pair in a core is a call, the 256-target blocks pay a fifth for the tiles that are near them and
-// not near 64-target blocks.  Partial sums are held to kMaxPartials, and to `room` bytes.
-// Measured (us, shape_split / this rule): 10000 hover particles 132 / 115, 65536 3500 / 3190
-// (flight 3320 / 2860), 20000 in FP64 1297 / 923, 128 points of 262144 particles 331 / 41, 4096
+// not near 64-target blocks.  In FP32 a target per lane is left to more than kPlainFrom targets:
+// below, slices are within 5 % either way (65536 hover particles 3040 us, 3130 with a target per
+// lane; flight 2990 and 2825) and their shorter FP32 sums hold the error down (7e-8 against 1.3e-7
+// with folds every 256 sources and 8.8e-8 every 128).  The gradient mode's 21 sums leave a slice
+// three wavefronts per SIMD, an eighth slower per pair than a target per lane.  Partial sums are held to kMaxPartials, and to `room` bytes.
+// Measured (us, shape_split / this rule): 10000 hover particles 132 / 115, 65536 3400 / 3040
+// (flight 3250 / 2990), 20000 in FP64 1297 / 923, 128 points of 262144 particles 331 / 41, 4096
 // points of 100000 281 / 232, 8000 points of a million 5050 / 3830.
-constexpr size_t kMaxPartials = size_t(96) << 20;
+constexpr size_t kMaxPartials = size_t(128) << 20;
 SplitPlan auto_split(int32_t dtype, int nacc, int64_t n_src, int64_t n_tgt, size_t room) {
     constexpr int64_t kSlots = 1024, kTile = 170, kLatency = 400, kGroup = 300, kFinish = 1500;
+    constexpr int64_t kPlainFrom = 131072;
+    const bool grad = nacc == vpm::nacc_of(vpm::kModeGradient);
     const int64_t pair = dtype == kDtypeF64 ? 60 : 30;
     if (room > kMaxPartials) room = kMaxPartials;
     SplitPlan best;
@@ -326,8 +332,11 @@ SplitPlan auto_split(int32_t dtype, int nacc, int64_t n_src, int64_t n_tgt, size
     if (n_src < 1 || n_tgt < 1) return best;
     double least = -1.0;
     for (int lp : {2, 3, 4, 5, 6, kPlainLp}) {
+        if (lp == kPlainLp && dtype != kDtypeF64 && !grad && n_tgt <= kPlainFrom) continue;
         const int64_t blocks = (n_tgt + (int64_t(1) << lp) - 1) >> lp;
-        const int64_t tile = (pair << lp) * (lp == kPlainLp && dtype == kDtypeF64 ? 6 : 5) / 5 + kTile;
+        const int64_t per_pair = lp == kPlainLp ? (dtype == kDtypeF64 ? pair * 6 / 5 : pair)
+                                                : (dtype != kDtypeF64 && grad ? pair * 9 / 8 : pair);
+        const int64_t tile = (per_pair << lp) + kTile;
         // 1, 2, 3, 4, 6, 8, 12, ... chunks
         for (int64_t want = 1; want == 1 || n_src / want >= kMinChunk;
              want += want == 1 || (want & (want - 1)) ? (want + 2) / 3 : want / 2) {
