@@ -36,6 +36,9 @@
 // (FP32 with per-tile two-sum folding, or FP64), summed in FP64 at the end.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "device_math.h"
 
 // The FP64 kernels call their in-core weights (a convergent call), and clang then reports the
@@ -54,7 +57,9 @@ constexpr int kSlots = (kMaxTerms + 255) / 256;  // 7
 constexpr int kMaxLevel = 10;
 // how far the M2L's batches of eight scalar loads can read past a cell's last moment
 constexpr int kM2lOverrun = 8;
-constexpr int kNearTile = 256;
+constexpr int kL2pItem = 256;
+constexpr int kUnit = 64;
+constexpr int kFoldUnits = 4;
 constexpr int kOffsets = 343;  // [-3, 3]^3
 constexpr double kInv4Pi = 0.0795774715459476678844418816862571810;
 // 1/k for the monomial recurrences a^k/k! = (a^(k-1)/(k-1)!) a (1/k) (a multiply, not an FP64
@@ -225,21 +230,27 @@ __global__ __launch_bounds__(256) void k_fmm_keys(const T* __restrict__ x, int64
     keys[p] = (uint64_t(cell_code(ic[0], ic[1], ic[2])) << 32) | uint64_t(p);
 }
 
-template <typename T>
+template <typename T, typename V4, typename V2>
 __global__ __launch_bounds__(256) void k_fmm_gather(const T* __restrict__ x, const T* __restrict__ g,
                                                     const T* __restrict__ sg, int64_t ld, int64_t n,
                                                     const uint64_t* __restrict__ keys, T* __restrict__ xs,
-                                                    T* __restrict__ gs, T* __restrict__ ss, int32_t* __restrict__ perm,
+                                                    T* __restrict__ gs, V4* __restrict__ sp, V4* __restrict__ sq,
+                                                    V2* __restrict__ sw, int32_t* __restrict__ perm,
                                                     uint32_t* __restrict__ lcode, int level) {
     const int64_t q = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (q >= n) return;
     const uint64_t k = keys[q];
     const int64_t i = int64_t(k & 0xffffffffull);
+    const T xv[3] = {x[i], x[ld + i], x[2 * ld + i]}, gv[3] = {g[i], g[ld + i], g[2 * ld + i]};
     for (int d = 0; d < 3; ++d) {
-        xs[d * n + q] = x[d * ld + i];
-        gs[d * n + q] = g[d * ld + i];
+        xs[d * n + q] = xv[d];
+        gs[d * n + q] = gv[d];
     }
-    ss[q] = sg[i];
+    // the near field's packed records
+    const T sj = sg[i], is = T(1) / sj;
+    sp[q] = V4{xv[0], xv[1], xv[2], -gv[2]};
+    sq[q] = V4{gv[0], gv[1], gv[2], Prec<T>::kFarRho2 * sj * sj};
+    sw[q] = V2{is, is * is};
     perm[q] = int32_t(i);
     lcode[q] = uint32_t(k >> 32) >> (3 * (kMaxLevel - level));
 }
@@ -438,53 +449,54 @@ __global__ __launch_bounds__(256) void k_fmm_p2m(const T* __restrict__ xs, const
                                                  FmmLevel lv, const int32_t* __restrict__ count,
                                                  const double* __restrict__ box, int level, int p,
                                                  const uint32_t* __restrict__ terms) {
-    const int cell = blockIdx.x;
-    if (cell >= *count) return;
-    const int nt = nterms(p);
-    __shared__ double pw[64][3][kMaxOrder + 1];
-    __shared__ double gg[64][3];
-    int ic[3];
-    cell_coords(lv.code[cell], ic);
-    double c[3];
-    for (int d = 0; d < 3; ++d) c[d] = cell_centre(box, d, ic[d], level);
-    double acc[kSlots][3];
-    for (int j = 0; j < kSlots; ++j)
-        for (int d = 0; d < 3; ++d) acc[j][d] = 0.0;
-    const int b0 = lv.pstart[cell], b1 = lv.pstart[cell + 1];
-    for (int base = b0; base < b1; base += 64) {
-        const int m = b1 - base < 64 ? b1 - base : 64;
-        __syncthreads();
-        if (int(threadIdx.x) < 3 * m) {
-            const int q = threadIdx.x / 3, d = threadIdx.x % 3;
-            const double a = double(xs[d * n + base + q]) - c[d];
-            double v = 1.0;
-            pw[q][d][0] = 1.0;
-            for (int i = 1; i <= p; ++i) {
-                v = v * a / double(i);
-                pw[q][d][i] = v;
+    const int ncell = *count;
+    for (int cell = blockIdx.x; cell < ncell; cell += gridDim.x) {
+        const int nt = nterms(p);
+        __shared__ double pw[64][3][kMaxOrder + 1];
+        __shared__ double gg[64][3];
+        int ic[3];
+        cell_coords(lv.code[cell], ic);
+        double c[3];
+        for (int d = 0; d < 3; ++d) c[d] = cell_centre(box, d, ic[d], level);
+        double acc[kSlots][3];
+        for (int j = 0; j < kSlots; ++j)
+            for (int d = 0; d < 3; ++d) acc[j][d] = 0.0;
+        const int b0 = lv.pstart[cell], b1 = lv.pstart[cell + 1];
+        for (int base = b0; base < b1; base += 64) {
+            const int m = b1 - base < 64 ? b1 - base : 64;
+            __syncthreads();
+            if (int(threadIdx.x) < 3 * m) {
+                const int q = threadIdx.x / 3, d = threadIdx.x % 3;
+                const double a = double(xs[d * n + base + q]) - c[d];
+                double v = 1.0;
+                pw[q][d][0] = 1.0;
+                for (int i = 1; i <= p; ++i) {
+                    v = v * a / double(i);
+                    pw[q][d][i] = v;
+                }
+                gg[q][d] = double(gs[d * n + base + q]);
             }
-            gg[q][d] = double(gs[d * n + base + q]);
+            __syncthreads();
+            for (int j = 0; j < kSlots; ++j) {
+                const int t = threadIdx.x + 256 * j;
+                if (t >= nt) break;
+                const uint32_t k = terms[t];
+                const int k0 = int(k & 0xff), k1 = int((k >> 8) & 0xff), k2 = int(k >> 16);
+                for (int q = 0; q < m; ++q) {
+                    const double mono = pw[q][0][k0] * pw[q][1][k1] * pw[q][2][k2];
+                    for (int d = 0; d < 3; ++d) acc[j][d] += gg[q][d] * mono;
+                }
+            }
         }
-        __syncthreads();
         for (int j = 0; j < kSlots; ++j) {
             const int t = threadIdx.x + 256 * j;
             if (t >= nt) break;
-            const uint32_t k = terms[t];
-            const int k0 = int(k & 0xff), k1 = int((k >> 8) & 0xff), k2 = int(k >> 16);
-            for (int q = 0; q < m; ++q) {
-                const double mono = pw[q][0][k0] * pw[q][1][k1] * pw[q][2][k2];
-                for (int d = 0; d < 3; ++d) acc[j][d] += gg[q][d] * mono;
-            }
+            for (int d = 0; d < 3; ++d) lv.M[(int64_t(cell) * 3 + d) * nt + t] = acc[j][d];
         }
+        // the M2L's batched reads run up to kM2lOverrun terms past a cell's last moment: after the
+        // level's last cell they find zeros, not memory that no cell writes
+        if (cell == ncell - 1 && int(threadIdx.x) < kM2lOverrun) lv.M[int64_t(cell + 1) * 3 * nt + threadIdx.x] = 0.0;
     }
-    for (int j = 0; j < kSlots; ++j) {
-        const int t = threadIdx.x + 256 * j;
-        if (t >= nt) break;
-        for (int d = 0; d < 3; ++d) lv.M[(int64_t(cell) * 3 + d) * nt + t] = acc[j][d];
-    }
-    // the M2L's batched reads run up to kM2lOverrun terms past a cell's last moment: after the
-    // level's last cell they find zeros, not memory that no cell writes
-    if (cell == *count - 1 && int(threadIdx.x) < kM2lOverrun) lv.M[int64_t(cell + 1) * 3 * nt + threadIdx.x] = 0.0;
 }
 
 // One axis of a separable Taylor shift of 3 x nt coefficients (mpos order, [3][nt]) held in
@@ -528,69 +540,76 @@ __device__ __forceinline__ void shift_axis(const double* in, double* out, const 
 __global__ __launch_bounds__(256) void k_fmm_m2m(FmmLevel par, FmmLevel chi, const int32_t* __restrict__ count, int l,
                                                  const double* __restrict__ box, int p,
                                                  const uint32_t* __restrict__ terms) {
-    const int cell = blockIdx.x;
-    if (cell >= *count) return;
-    const int nt = nterms(p);
-    extern __shared__ double sShift[];
-    double* bufA = sShift;
-    double* bufB = sShift + 3 * nt;
-    __shared__ double pw[3][kMaxOrder + 1];
-    const int c0 = par.first[cell], c1 = par.first[cell + 1];
-    int ip[3];
-    cell_coords(par.code[cell], ip);
-    double acc[kSlots][3];
-    for (int j = 0; j < kSlots; ++j)
-        for (int d = 0; d < 3; ++d) acc[j][d] = 0.0;
-    for (int q = c0; q < c1; ++q) {
-        __syncthreads();
-        if (threadIdx.x < 3) {
-            const int d = threadIdx.x;
-            int ic[3];
-            cell_coords(chi.code[q], ic);
-            const double dl = cell_centre(box, d, ic[d], l + 1) - cell_centre(box, d, ip[d], l);
-            double v = 1.0;
-            pw[d][0] = 1.0;
-            for (int i = 1; i <= p; ++i) {
-                v = v * dl / double(i);
-                pw[d][i] = v;
+    const int ncell = *count;
+    for (int cell = blockIdx.x; cell < ncell; cell += gridDim.x) {
+        const int nt = nterms(p);
+        extern __shared__ double sShift[];
+        double* bufA = sShift;
+        double* bufB = sShift + 3 * nt;
+        __shared__ double pw[3][kMaxOrder + 1];
+        const int c0 = par.first[cell], c1 = par.first[cell + 1];
+        int ip[3];
+        cell_coords(par.code[cell], ip);
+        double acc[kSlots][3];
+        for (int j = 0; j < kSlots; ++j)
+            for (int d = 0; d < 3; ++d) acc[j][d] = 0.0;
+        for (int q = c0; q < c1; ++q) {
+            __syncthreads();
+            if (threadIdx.x < 3) {
+                const int d = threadIdx.x;
+                int ic[3];
+                cell_coords(chi.code[q], ic);
+                const double dl = cell_centre(box, d, ic[d], l + 1) - cell_centre(box, d, ip[d], l);
+                double v = 1.0;
+                pw[d][0] = 1.0;
+                for (int i = 1; i <= p; ++i) {
+                    v = v * dl / double(i);
+                    pw[d][i] = v;
+                }
+            }
+            const double* Mc = chi.M + int64_t(q) * 3 * nt;
+            for (int i = threadIdx.x; i < 3 * nt; i += 256) bufA[i] = Mc[i];
+            __syncthreads();
+            shift_axis<false>(bufA, bufB, pw[0], 0, p, nt, terms);
+            __syncthreads();
+            shift_axis<false>(bufB, bufA, pw[1], 1, p, nt, terms);
+            __syncthreads();
+            for (int j = 0; j < kSlots; ++j) {
+                const int t = threadIdx.x + 256 * j;
+                if (t >= nt) break;
+                double o[3];
+                shift_axis_term<false>(bufA, pw[2], 2, p, nt, terms[t], o);
+                for (int d = 0; d < 3; ++d) acc[j][d] += o[d];
             }
         }
-        const double* Mc = chi.M + int64_t(q) * 3 * nt;
-        for (int i = threadIdx.x; i < 3 * nt; i += 256) bufA[i] = Mc[i];
-        __syncthreads();
-        shift_axis<false>(bufA, bufB, pw[0], 0, p, nt, terms);
-        __syncthreads();
-        shift_axis<false>(bufB, bufA, pw[1], 1, p, nt, terms);
-        __syncthreads();
         for (int j = 0; j < kSlots; ++j) {
             const int t = threadIdx.x + 256 * j;
             if (t >= nt) break;
-            double o[3];
-            shift_axis_term<false>(bufA, pw[2], 2, p, nt, terms[t], o);
-            for (int d = 0; d < 3; ++d) acc[j][d] += o[d];
+            for (int d = 0; d < 3; ++d) par.M[(int64_t(cell) * 3 + d) * nt + t] = acc[j][d];
         }
+        // zeros after the level's last cell for the M2L's batched reads (as in k_fmm_p2m)
+        if (cell == ncell - 1 && int(threadIdx.x) < kM2lOverrun) par.M[int64_t(cell + 1) * 3 * nt + threadIdx.x] = 0.0;
     }
-    for (int j = 0; j < kSlots; ++j) {
-        const int t = threadIdx.x + 256 * j;
-        if (t >= nt) break;
-        for (int d = 0; d < 3; ++d) par.M[(int64_t(cell) * 3 + d) * nt + t] = acc[j][d];
-    }
-    // zeros after the level's last cell for the M2L's batched reads (as in k_fmm_p2m)
-    if (cell == *count - 1 && int(threadIdx.x) < kM2lOverrun) par.M[int64_t(cell + 1) * 3 * nt + threadIdx.x] = 0.0;
 }
 
 // ---------------------------------------------------------------- M2L and L2L
-// LDS of one M2L group in doubles: the (p + 1)^3 grid and its zero; with MLDS also the source
-// cell's moments (3 nt, and kM2lOverrun zeros after them) and the grid index of every term (nt,
-// and kM2lOverrun more, as ints).  At least 3 nt for the group's sums at the end.
-__host__ __device__ inline int m2l_group_doubles(int p, bool mlds) {
+// Low-order M2L: LDS of one wavefront in doubles, the (p + 1)^3 grid and its zero, or the 3 nt
+// sums at the end; kM2lWaves wavefronts per workgroup, up to order kM2lWaveOrder.
+constexpr int kM2lWaves = 4;
+constexpr int kM2lWaveOrder = 12;
+__host__ __device__ inline int m2l_grid_doubles(int p) {
     const int nt = nterms(p);
-    int g = (p + 1) * (p + 1) * (p + 1) + 1;
-    if (mlds) g += 3 * nt + kM2lOverrun + (nt + kM2lOverrun + 1) / 2;
+    const int g = (p + 1) * (p + 1) * (p + 1) + 1;
     return g > 3 * nt ? g : 3 * nt;
 }
+// High-order M2L: the grid and its zero, the source cell's moments (3 nt, and kM2lOverrun zeros
+// after them) and the grid index of every term (nt, and kM2lOverrun more, as ints).
+inline int m2l_unit_doubles(int p) {
+    const int nt = nterms(p);
+    return (p + 1) * (p + 1) * (p + 1) + 1 + 3 * nt + kM2lOverrun + (nt + kM2lOverrun + 1) / 2;
+}
 
-// Work units of the high-order M2L (orders whose grid fills the LDS, one group per cell).
+// Work units of the high-order M2L (one workgroup per cell).
 // The terms n are cut into blocks of 64 (one wavefront's lanes, in degree order); block b's
 // lanes walk the same k, up to the prefix length of its lowest-degree term.  Those walks are
 // very uneven (at order 18 from 1330 steps for the first block down to 1), so each block's walk
@@ -720,89 +739,199 @@ inline bool m2l_units(int p, M2lUnits& u) {
 typedef __attribute__((address_space(4))) const double* CDouble;
 typedef __attribute__((address_space(4))) const uint32_t* CUint;
 
+// The interaction list of a target cell (its parent's neighbours' children that are not its own
+// neighbours): the sources' indices and offset numbers in list_src, list_off, in candidate order,
+// and (-1/w)^k in sc.  Run by a workgroup of at least 256 lanes; returns the number of entries.
+// cand: 4 ints.  Ends with a barrier.
+__device__ __forceinline__ int m2l_list(const FmmLevel& lv, int ncell, int cell, int l, double w, int p,
+                                        int32_t* list_src, int32_t* list_off, double* sc, int32_t* cand) {
+    int ic[3];
+    cell_coords(lv.code[cell], ic);
+    const int side = 1 << l;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    int idx = -1, off = 0;
+    if (tid < 216) {
+        const int pn = tid / 8, ch = tid % 8;
+        const int pc[3] = {(ic[0] >> 1) + pn / 9 - 1, (ic[1] >> 1) + (pn / 3) % 3 - 1, (ic[2] >> 1) + pn % 3 - 1};
+        const int s[3] = {2 * pc[0] + (ch >> 2), 2 * pc[1] + ((ch >> 1) & 1), 2 * pc[2] + (ch & 1)};
+        const bool inside = pc[0] >= 0 && pc[1] >= 0 && pc[2] >= 0 && 2 * pc[0] < side && 2 * pc[1] < side &&
+                            2 * pc[2] < side;
+        const bool adjacent = abs(s[0] - ic[0]) <= 1 && abs(s[1] - ic[1]) <= 1 && abs(s[2] - ic[2]) <= 1;
+        if (inside && !adjacent) idx = find_code(lv.code, ncell, cell_code(s[0], s[1], s[2]));
+        off = (ic[0] - s[0] + 3) * 49 + (ic[1] - s[1] + 3) * 7 + (ic[2] - s[2] + 3);
+    }
+    const unsigned long long hit = __ballot(idx >= 0);
+    __syncthreads();  // the previous cell's list is read
+    if (lane == 0 && wave < 4) cand[wave] = __popcll(hit);
+    if (tid <= p) {
+        // (-1/w)^k
+        double v = 1.0;
+        for (int k = 0; k < tid; ++k) v *= -1.0 / w;
+        sc[tid] = v;
+    }
+    __syncthreads();
+    if (idx >= 0) {
+        int at = __popcll(hit & ((1ull << lane) - 1));
+        for (int q = 0; q < wave; ++q) at += cand[q];
+        list_src[at] = idx;
+        list_off[at] = off;
+    }
+    __syncthreads();
+    return cand[0] + cand[1] + cand[2] + cand[3];
+}
+
 // One workgroup per target cell of level l: L = M2L over the interaction list (written, not
 // added: the parent's shifted expansion is added afterwards by k_fmm_l2l).  With the
 // unit-spacing table D of the offset and the cell width w,
 //   L_n = w^(-1-|n|)/(4 pi) sum_k D_{n+k} (-1/w)^|k| M_k = (-1)^|n|/(4 pi w) sum_k D'_{n+k} M_k,
 //   D'_m = (-1/w)^|m| D_m.
-// The workgroup is G groups of glanes lanes (a multiple of 64); group g takes interactions
-// g, g + G, ...  Each interaction's D' is staged in the group's LDS grid of (p + 1)^3 entries
-// (plus one zero), where the index of n + k is the sum of the indices of n and k.  Lanes own
-// terms n (t = lane + glanes j, j < SLOTS); the terms k with |k| <= p - |n| are a prefix of the
-// degree order, so the lanes of a wavefront walk the same k, whose M_k and grid index are
-// uniform (scalar loads), and a lane past its prefix reads the zero.  Per lane and k: one LDS
-// read and three FMAs.  The groups' sums are added in group order at the end (deterministic).
-// Low orders take several 256-lane groups (interactions in parallel).  High orders, whose grids
-// fill the LDS, take one group of kUnitWaves wavefronts (MLDS), which also stages the source
-// cell's moments and the terms' grid indices in LDS, so that the walk over k reads LDS (in
-// order, pipelined) instead of waiting on a batch of scalar loads every eight steps; there the
-// walks of the blocks of 64 terms are cut into pieces dealt evenly to the wavefronts
-// (M2lUnits), and each term adds its pieces' partial sums in k order at the end.
-template <int SLOTS, bool MLDS>
-__global__ __launch_bounds__(1024) void k_fmm_m2l(FmmLevel lv, const int32_t* __restrict__ count, int l,
-                                                  const double* __restrict__ box, int p,
-                                                  const uint32_t* __restrict__ terms, const double* __restrict__ dtab,
-                                                  int glanes, const M2lUnits units) {
-    const int cell = blockIdx.x;
+// An interaction's D' is staged in an LDS grid of (p + 1)^3 entries (plus one zero), where the
+// index of n + k is the sum of the indices of n and k.  Lanes own terms n; the terms k with
+// |k| <= p - |n| are a prefix of the degree order, so the lanes of a wavefront walk the same k,
+// whose M_k and grid index are uniform, and a lane past its prefix reads the zero.  Per lane and k:
+// one LDS read and three FMAs.
+//
+// Low orders (kM2lWaves grids fit the LDS): every wavefront takes interactions of its own, with its
+// own grid and no workgroup barrier, and all the terms (t = lane + 64 j, j < SLOTS), so the waits
+// of one wavefront's scalar loads are filled by the others; M_k and the grid index of a batch of
+// eight k are read once for all its blocks of terms.  The wavefronts' sums are added in order at
+// the end.  Bound by the latency of the scalar loads at two to six wavefronts per SIMD.
+// Measured (all levels, us; 256-lane groups that shared one interaction, of which the wavefront of
+// the lowest degrees walked most steps / now): order 8 on 5000 hover particles at depth 4
+// 1229 / 547, order 10 on 200000 2185 / 1017, order 12 on the million-particle wake 1507 / 1060.
+template <int SLOTS>
+__global__ __launch_bounds__(64 * kM2lWaves) void k_fmm_m2l_wave(FmmLevel lv, const int32_t* __restrict__ count, int l,
+                                                                 const double* __restrict__ box, int p,
+                                                                 const uint32_t* __restrict__ terms,
+                                                                 const double* __restrict__ dtab) {
     const int ncell = *count;
-    if (cell >= ncell) return;
     const int nt = nterms(p);
-    const int ngroup = int(blockDim.x) / glanes;
-    // the group is uniform over each wavefront (groups of whole wavefronts)
-    const int grp = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / glanes), gt = int(threadIdx.x) % glanes;
     const int gsize = (p + 1) * (p + 1) * (p + 1) + 1;  // grid + the zero
-    const int gstride = m2l_group_doubles(p, MLDS);
-    extern __shared__ double sDyn[];                    // ngroup grids; reused for the final sum
-    double* sDg = sDyn + grp * gstride;
-    double* sM = sDg + gsize;                                   // MLDS: [3][nt] + zeros
-    int32_t* sG = reinterpret_cast<int32_t*>(sM + 3 * nt + kM2lOverrun);  // MLDS: [nt] + zeros
-    __shared__ int32_t cand[216];
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), lane = int(threadIdx.x) & 63;
+    extern __shared__ double sDyn[];  // kM2lWaves grids; reused for the final sums
     __shared__ int32_t list_src[216];
     __shared__ int32_t list_off[216];
-    __shared__ int32_t nlist;
+    __shared__ int32_t cand[4];
     __shared__ double sc[kMaxOrder + 1];
-    int ic[3];
-    cell_coords(lv.code[cell], ic);
-    const int side = 1 << l;
     const double w = ldexp(2.0 * box[3], -l);
-    if (threadIdx.x < 216) {
-        const int pn = threadIdx.x / 8, ch = threadIdx.x % 8;
-        const int pc[3] = {(ic[0] >> 1) + pn / 9 - 1, (ic[1] >> 1) + (pn / 3) % 3 - 1, (ic[2] >> 1) + pn % 3 - 1};
-        const int s[3] = {2 * pc[0] + (ch >> 2), 2 * pc[1] + ((ch >> 1) & 1), 2 * pc[2] + (ch & 1)};
-        int idx = -1;
-        const bool inside = pc[0] >= 0 && pc[1] >= 0 && pc[2] >= 0 && 2 * pc[0] < side && 2 * pc[1] < side &&
-                            2 * pc[2] < side;
-        const bool adjacent = abs(s[0] - ic[0]) <= 1 && abs(s[1] - ic[1]) <= 1 && abs(s[2] - ic[2]) <= 1;
-        if (inside && !adjacent) idx = find_code(lv.code, ncell, cell_code(s[0], s[1], s[2]));
-        cand[threadIdx.x] = idx;
-        if (idx >= 0)
-            list_off[threadIdx.x] = (ic[0] - s[0] + 3) * 49 + (ic[1] - s[1] + 3) * 7 + (ic[2] - s[2] + 3);
-    }
-    if (threadIdx.x <= p) {
-        // (-1/w)^k
-        double v = 1.0;
-        for (int k = 0; k < int(threadIdx.x); ++k) v *= -1.0 / w;
-        sc[threadIdx.x] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int m = 0;
-        for (int t = 0; t < 216; ++t)
-            if (cand[t] >= 0) {
-                list_src[m] = cand[t];
-                list_off[m] = list_off[t];
-                ++m;
-            }
-        nlist = m;
-    }
     const CUint gidx = (CUint)(terms + kMaxTerms);
     const int zero_at = gsize - 1;  // the staging never writes there
-    if (gt == 0) sDg[zero_at] = 0.0;
-    if constexpr (MLDS) {
+    double* sDg = sDyn + wave * m2l_grid_doubles(p);
+    int nb[SLOTS], cnt[SLOTS], smax[SLOTS], deg[SLOTS];
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+        const int t = lane + 64 * j;
+        nb[j] = 0;
+        cnt[j] = 0;
+        deg[j] = 0;
+        if (t < nt) {
+            const uint32_t k = terms[t];
+            deg[j] = int(k & 0xff) + int((k >> 8) & 0xff) + int(k >> 16);
+            nb[j] = int(terms[kMaxTerms + t]);
+            cnt[j] = nterms(p - deg[j]);
+        }
+        // lane 0 owns the block's lowest degree, hence its longest prefix
+        smax[j] = __builtin_amdgcn_readfirstlane(cnt[j]);
+    }
+    for (int cell = blockIdx.x; cell < ncell; cell += gridDim.x) {
+        const int nlist = __builtin_amdgcn_readfirstlane(
+            m2l_list(lv, ncell, cell, l, w, p, list_src, list_off, sc, cand));
+        if (lane == 0) sDg[zero_at] = 0.0;
+        double acc[SLOTS][3];
+#pragma unroll
+        for (int j = 0; j < SLOTS; ++j)
+            for (int d = 0; d < 3; ++d) acc[j][d] = 0.0;
+        for (int e = wave; e < nlist; e += kM2lWaves) {
+            const double* D = dtab + int64_t(__builtin_amdgcn_readfirstlane(list_off[e])) * nt;
+            __builtin_amdgcn_wave_barrier();  // every lane is done with the previous interaction's grid
+#pragma unroll
+            for (int j = 0; j < SLOTS; ++j)
+                if (lane + 64 * j < nt) sDg[nb[j]] = D[lane + 64 * j] * sc[deg[j]];
+            __builtin_amdgcn_wave_barrier();
+            const int src = __builtin_amdgcn_readfirstlane(list_src[e]);
+            const CDouble M0 = (CDouble)(lv.M + int64_t(src) * 3 * nt);
+            // 8 steps per batch of scalar loads, which may read up to 7 terms past a lane's
+            // prefix; those lanes multiply by the zero.  Past a cell's first two components the
+            // reads find the next component's moments, past the third the next cell's, or the
+            // zeros that the moments' writers leave after the level's last cell: always finite.
+            for (int s0 = 0; s0 < smax[0]; s0 += 8) {
+                int ks[8];
+                double m[3][8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    ks[i] = int(gidx[s0 + i]);
+                    m[0][i] = M0[s0 + i];
+                    m[1][i] = M0[nt + s0 + i];
+                    m[2][i] = M0[2 * nt + s0 + i];
+                }
+#pragma unroll
+                for (int j = 0; j < SLOTS; ++j) {
+                    if (s0 >= smax[j]) break;  // the later blocks' prefixes are shorter still
+                    // lanes past their prefix read the zero after the grid (no branch, so that
+                    // the eight reads are in flight together)
+                    double Dv[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) Dv[i] = sDg[s0 + i < cnt[j] ? nb[j] + ks[i] : zero_at];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        acc[j][0] += Dv[i] * m[0][i];
+                        acc[j][1] += Dv[i] * m[1][i];
+                        acc[j][2] += Dv[i] * m[2][i];
+                    }
+                }
+            }
+        }
+        // add the wavefronts' sums in order through LDS (3 nt doubles per wavefront)
+        __syncthreads();
+        double* sum = sDyn + wave * m2l_grid_doubles(p);
+#pragma unroll
+        for (int j = 0; j < SLOTS; ++j) {
+            const int t = lane + 64 * j;
+            if (t < nt)
+                for (int d = 0; d < 3; ++d) sum[d * nt + t] = acc[j][d];
+        }
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < 3 * nt; idx += 64 * kM2lWaves) {
+            const int d = idx / nt, t = idx - d * nt;
+            double v = 0.0;
+            for (int g = 0; g < kM2lWaves; ++g) v += sDyn[g * m2l_grid_doubles(p) + d * nt + t];
+            const uint32_t k = terms[t];
+            const int dg = int(k & 0xff) + int((k >> 8) & 0xff) + int(k >> 16);
+            const double f = ((dg & 1) ? -kInv4Pi : kInv4Pi) / w;
+            lv.L[(int64_t(cell) * 3 + d) * nt + t] = v * f;
+        }
+    }
+}
+
+// High orders: one interaction at a time in a workgroup of kUnitWaves wavefronts, which also
+// stages the source cell's moments and the terms' grid indices in LDS, so that the walk over k
+// reads LDS (in order, pipelined) instead of waiting on a batch of scalar loads every eight steps;
+// the walks of the blocks of 64 terms are cut into pieces dealt evenly to the wavefronts
+// (M2lUnits), and each term adds its pieces' partial sums in k order at the end.
+__global__ __launch_bounds__(64 * kUnitWaves) void k_fmm_m2l(FmmLevel lv, const int32_t* __restrict__ count, int l,
+                                                             const double* __restrict__ box, int p,
+                                                             const uint32_t* __restrict__ terms,
+                                                             const double* __restrict__ dtab, const M2lUnits units) {
+    const int ncell = *count;
+    const int nt = nterms(p);
+    const int gsize = (p + 1) * (p + 1) * (p + 1) + 1;  // grid + the zero
+    extern __shared__ double sDyn[];                    // the grid; reused for the final sum
+    double* sDg = sDyn;
+    double* sM = sDg + gsize;                                              // [3][nt] + zeros
+    int32_t* sG = reinterpret_cast<int32_t*>(sM + 3 * nt + kM2lOverrun);  // [nt] + zeros
+    __shared__ int32_t list_src[216];
+    __shared__ int32_t list_off[216];
+    __shared__ int32_t cand[4];
+    __shared__ double sc[kMaxOrder + 1];
+    const double w = ldexp(2.0 * box[3], -l);
+    const int zero_at = gsize - 1;  // the staging never writes there
+    const int gt = threadIdx.x;
+    constexpr int glanes = 64 * kUnitWaves;
+    for (int cell = blockIdx.x; cell < ncell; cell += gridDim.x) {
+        const int nlist = m2l_list(lv, ncell, cell, l, w, p, list_src, list_off, sc, cand);
+        if (gt == 0) sDg[zero_at] = 0.0;
         for (int t = gt; t < nt + kM2lOverrun; t += glanes) sG[t] = t < nt ? int(terms[kMaxTerms + t]) : 0;
         if (gt < kM2lOverrun) sM[3 * nt + gt] = 0.0;
-    }
-    if constexpr (MLDS) {
         // one group of kUnitWaves wavefronts; wavefront w walks the pieces units.wave_unit[w][.]
         const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), lane = int(threadIdx.x) & 63;
         int uid[kUnitSlots], nb[kUnitSlots], lim[kUnitSlots], k0[kUnitSlots], k1[kUnitSlots];
@@ -886,90 +1015,6 @@ __global__ __launch_bounds__(1024) void k_fmm_m2l(FmmLevel lv, const int32_t* __
             const double f = ((dg & 1) ? -kInv4Pi : kInv4Pi) / w;
             lv.L[(int64_t(cell) * 3 + d) * nt + t] = v * f;
         }
-        return;
-    } else {
-        int nb[SLOTS], cnt[SLOTS], smax[SLOTS], deg[SLOTS];
-        double acc[SLOTS][3];
-#pragma unroll
-        for (int j = 0; j < SLOTS; ++j) {
-            const int t = gt + glanes * j;
-            nb[j] = 0;
-            cnt[j] = 0;
-            deg[j] = 0;
-            if (t < nt) {
-                const uint32_t k = terms[t];
-                deg[j] = int(k & 0xff) + int((k >> 8) & 0xff) + int(k >> 16);
-                nb[j] = int(terms[kMaxTerms + t]);
-                cnt[j] = nterms(p - deg[j]);
-            }
-            // lane 0 of the wavefront owns its lowest degree, hence the longest prefix
-            smax[j] = __builtin_amdgcn_readfirstlane(cnt[j]);
-            for (int d = 0; d < 3; ++d) acc[j][d] = 0.0;
-        }
-        __syncthreads();
-        const int rounds = (nlist + ngroup - 1) / ngroup;
-        for (int r = 0; r < rounds; ++r) {
-            const int e = r * ngroup + grp;
-            const bool has = e < nlist;
-            __syncthreads();
-            if (has) {
-                const double* D = dtab + int64_t(list_off[e]) * nt;
-                for (int t = gt; t < nt; t += glanes) {
-                    const uint32_t k = terms[t];
-                    sDg[terms[kMaxTerms + t]] = D[t] * sc[int(k & 0xff) + int((k >> 8) & 0xff) + int(k >> 16)];
-                }
-            }
-            __syncthreads();
-            if (!has) continue;
-            const int src = __builtin_amdgcn_readfirstlane(list_src[e]);
-            const CDouble M0 = (CDouble)(lv.M + int64_t(src) * 3 * nt);
-#pragma unroll
-            for (int j = 0; j < SLOTS; ++j) {
-                // 8 steps per batch of scalar loads, which may read up to 7 terms past a lane's
-                // prefix; those lanes multiply by the zero.  Past a cell's first two components the
-                // reads find the next component's moments, past the third the next cell's, or the
-                // zeros that the moments' writers leave after the level's last cell: always finite.
-                for (int s0 = 0; s0 < smax[j]; s0 += 8) {
-                    int ks[8];
-                    double m[3][8];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        ks[i] = int(gidx[s0 + i]);
-                        m[0][i] = M0[s0 + i];
-                        m[1][i] = M0[nt + s0 + i];
-                        m[2][i] = M0[2 * nt + s0 + i];
-                    }
-                    // lanes past their prefix read the zero after the grid (no branch, so that the
-                    // eight reads are in flight together)
-                    double Dv[8];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) Dv[i] = sDg[s0 + i < cnt[j] ? nb[j] + ks[i] : zero_at];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        acc[j][0] += Dv[i] * m[0][i];
-                        acc[j][1] += Dv[i] * m[1][i];
-                        acc[j][2] += Dv[i] * m[2][i];
-                    }
-                }
-            }
-        }
-        // add the groups' sums in group order through LDS (3 nt doubles per group)
-        __syncthreads();
-        for (int j = 0; j < SLOTS; ++j) {
-            const int t = gt + glanes * j;
-            if (t >= nt) break;
-            for (int d = 0; d < 3; ++d) sDyn[(grp * 3 + d) * nt + t] = acc[j][d];
-        }
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < 3 * nt; idx += blockDim.x) {
-            const int d = idx / nt, t = idx - d * nt;
-            double v = 0.0;
-            for (int g2 = 0; g2 < ngroup; ++g2) v += sDyn[(g2 * 3 + d) * nt + t];
-            const uint32_t k = terms[t];
-            const int dg = int(k & 0xff) + int((k >> 8) & 0xff) + int(k >> 16);
-            const double f = ((dg & 1) ? -kInv4Pi : kInv4Pi) / w;
-            lv.L[(int64_t(cell) * 3 + d) * nt + t] = v * f;
-        }
     }
 }
 
@@ -978,76 +1023,124 @@ __global__ __launch_bounds__(1024) void k_fmm_m2l(FmmLevel lv, const int32_t* __
 __global__ __launch_bounds__(256) void k_fmm_l2l(FmmLevel chi, FmmLevel par, const int32_t* __restrict__ count, int l,
                                                  const double* __restrict__ box, int p,
                                                  const uint32_t* __restrict__ terms) {
-    const int cell = blockIdx.x;
-    if (cell >= *count) return;
-    const int nt = nterms(p);
-    extern __shared__ double sShift[];
-    double* bufA = sShift;
-    double* bufB = sShift + 3 * nt;
-    __shared__ double pw[3][kMaxOrder + 1];
-    const int pa = chi.parent[cell];
-    if (threadIdx.x < 3) {
-        const int d = threadIdx.x;
-        int ic[3], ip[3];
-        cell_coords(chi.code[cell], ic);
-        cell_coords(par.code[pa], ip);
-        const double dl = cell_centre(box, d, ic[d], l) - cell_centre(box, d, ip[d], l - 1);
-        double v = 1.0;
-        pw[d][0] = 1.0;
-        for (int i = 1; i <= p; ++i) {
-            v = v * dl / double(i);
-            pw[d][i] = v;
+    const int ncell = *count;
+    for (int cell = blockIdx.x; cell < ncell; cell += gridDim.x) {
+        __syncthreads();  // the previous cell's buffers are read
+        const int nt = nterms(p);
+        extern __shared__ double sShift[];
+        double* bufA = sShift;
+        double* bufB = sShift + 3 * nt;
+        __shared__ double pw[3][kMaxOrder + 1];
+        const int pa = chi.parent[cell];
+        if (threadIdx.x < 3) {
+            const int d = threadIdx.x;
+            int ic[3], ip[3];
+            cell_coords(chi.code[cell], ic);
+            cell_coords(par.code[pa], ip);
+            const double dl = cell_centre(box, d, ic[d], l) - cell_centre(box, d, ip[d], l - 1);
+            double v = 1.0;
+            pw[d][0] = 1.0;
+            for (int i = 1; i <= p; ++i) {
+                v = v * dl / double(i);
+                pw[d][i] = v;
+            }
         }
-    }
-    const double* Lp = par.L + int64_t(pa) * 3 * nt;
-    for (int i = threadIdx.x; i < 3 * nt; i += 256) bufA[i] = Lp[i];
-    __syncthreads();
-    shift_axis<true>(bufA, bufB, pw[0], 0, p, nt, terms);
-    __syncthreads();
-    shift_axis<true>(bufB, bufA, pw[1], 1, p, nt, terms);
-    __syncthreads();
-    for (int t = threadIdx.x; t < nt; t += 256) {
-        double o[3];
-        shift_axis_term<true>(bufA, pw[2], 2, p, nt, terms[t], o);
-        for (int d = 0; d < 3; ++d) chi.L[(int64_t(cell) * 3 + d) * nt + t] += o[d];
+        const double* Lp = par.L + int64_t(pa) * 3 * nt;
+        for (int i = threadIdx.x; i < 3 * nt; i += 256) bufA[i] = Lp[i];
+        __syncthreads();
+        shift_axis<true>(bufA, bufB, pw[0], 0, p, nt, terms);
+        __syncthreads();
+        shift_axis<true>(bufB, bufA, pw[1], 1, p, nt, terms);
+        __syncthreads();
+        for (int t = threadIdx.x; t < nt; t += 256) {
+            double o[3];
+            shift_axis_term<true>(bufA, pw[2], 2, p, nt, terms[t], o);
+            for (int d = 0; d < 3; ++d) chi.L[(int64_t(cell) * 3 + d) * nt + t] += o[d];
+        }
     }
 }
 
 // ---------------------------------------------------------------- near field + evaluation
-// Work items: chunks of kNearTile consecutive targets of one leaf (one workgroup).
+// Chunks of consecutive particles of one leaf: items of kL2pItem targets (a workgroup of the
+// L2P), listed by leaf and first particle, and units of kUnit particles (a wavefront's targets or
+// one staged subtile of sources of the near field), listed the same way with every leaf's first
+// unit (unit0[leaf count] = unit count).  counts: [0] items, [1] units.
 __global__ __launch_bounds__(1024) void k_fmm_items(const int32_t* __restrict__ count, const int32_t* __restrict__ pstart,
                                                     int32_t* __restrict__ item_leaf, int32_t* __restrict__ item_t0,
-                                                    int32_t* __restrict__ nitems) {
-    __shared__ int32_t part[1024];
+                                                    int32_t* __restrict__ unit_leaf, int32_t* __restrict__ unit_t0,
+                                                    int32_t* __restrict__ unit0, int32_t* __restrict__ counts) {
+    __shared__ int32_t part[2][1024];
     const int64_t nl = *count;
     const int tid = threadIdx.x;
     const int64_t chunk = (nl + 1023) / 1024;
     const int64_t b = int64_t(tid) * chunk;
     const int64_t e = b + chunk < nl ? b + chunk : nl;
-    int32_t cnt = 0;
-    for (int64_t i = b; i < e; ++i) cnt += (pstart[i + 1] - pstart[i] + kNearTile - 1) / kNearTile;
-    part[tid] = cnt;
+    int32_t ni = 0, nu = 0;
+    for (int64_t i = b; i < e; ++i) {
+        const int32_t m = pstart[i + 1] - pstart[i];
+        ni += (m + kL2pItem - 1) / kL2pItem;
+        nu += (m + kUnit - 1) / kUnit;
+    }
+    part[0][tid] = ni;
+    part[1][tid] = nu;
     __syncthreads();
     for (int off = 1; off < 1024; off <<= 1) {
-        const int32_t v = tid >= off ? part[tid - off] : 0;
+        const int32_t v = tid >= off ? part[0][tid - off] : 0, w = tid >= off ? part[1][tid - off] : 0;
         __syncthreads();
-        part[tid] += v;
+        part[0][tid] += v;
+        part[1][tid] += w;
         __syncthreads();
     }
-    int32_t pos = part[tid] - cnt;
-    for (int64_t i = b; i < e; ++i)
-        for (int32_t t0 = pstart[i]; t0 < pstart[i + 1]; t0 += kNearTile) {
-            item_leaf[pos] = int32_t(i);
-            item_t0[pos] = t0;
-            ++pos;
+    int32_t pi = part[0][tid] - ni, pu = part[1][tid] - nu;
+    for (int64_t i = b; i < e; ++i) {
+        unit0[i] = pu;
+        for (int32_t t0 = pstart[i]; t0 < pstart[i + 1]; t0 += kL2pItem) {
+            item_leaf[pi] = int32_t(i);
+            item_t0[pi] = t0;
+            ++pi;
         }
-    if (tid == 1023) *nitems = part[1023];
+        for (int32_t t0 = pstart[i]; t0 < pstart[i + 1]; t0 += kUnit) {
+            unit_leaf[pu] = int32_t(i);
+            unit_t0[pu] = t0;
+            ++pu;
+        }
+    }
+    if (tid == 1023) {
+        counts[0] = part[0][1023];
+        counts[1] = part[1][1023];
+        unit0[nl] = part[1][1023];
+    }
+}
+
+// Bounding box and largest core cut of every unit's particles, a wavefront per unit.
+template <typename T, typename V4>
+__global__ __launch_bounds__(256) void k_fmm_unit_box(const int32_t* __restrict__ nunits,
+                                                      const int32_t* __restrict__ unit_leaf,
+                                                      const int32_t* __restrict__ unit_t0,
+                                                      const int32_t* __restrict__ pstart, const V4* __restrict__ sp,
+                                                      const V4* __restrict__ sq, T* __restrict__ box) {
+    const int nu = *nunits, lane = threadIdx.x & 63;
+    for (int u = int(blockIdx.x) * 4 + int(threadIdx.x >> 6); u < nu; u += int(gridDim.x) * 4) {
+        const int j0 = unit_t0[u], je = pstart[unit_leaf[u] + 1];
+        const int j = j0 + lane < je ? j0 + lane : j0;  // past the end: the unit's first particle again
+        const V4 p = sp[j];
+        T v[7] = {p.x, p.y, p.z, p.x, p.y, p.z, sq[j].w};
+        wave_minmax_last(v);
+        if (lane == 63) {
+            T* b = box + 8 * int64_t(u);
+            for (int c = 0; c < 7; ++c) b[c] = v[c];
+            b[7] = T(0);
+        }
+    }
 }
 
 struct NearArgs {
     const void* xs;
     const void* gs;
-    const void* ss;
+    const void* sp;  // packed sorted particles: (x, -Gamma_z)
+    const void* sq;  // (Gamma, cut = rho_far^2 sigma^2)
+    const void* sw;  // (1/sigma, 1/sigma^2)
+    const void* ubox;          // [units][8]
     const int32_t* perm;
     int64_t n;
     FmmLevel leaf;
@@ -1055,6 +1148,10 @@ struct NearArgs {
     const int32_t* item_leaf;
     const int32_t* item_t0;
     const int32_t* nitems;
+    const int32_t* unit_leaf;
+    const int32_t* unit_t0;
+    const int32_t* unit0;
+    const int32_t* nunits;
     const double* box;
     int level;
     int p;
@@ -1074,20 +1171,20 @@ struct NearArgs {
 constexpr int kL2pLanes = 128;
 template <typename T, bool CLASSICAL>
 __global__ __launch_bounds__(kL2pLanes) void k_fmm_l2p(NearArgs a, double* __restrict__ far) {
-    const int item = blockIdx.x;
-    if (item >= *a.nitems) return;
     const T* __restrict__ xs = static_cast<const T*>(a.xs);
     const T* __restrict__ gs = static_cast<const T*>(a.gs);
     const int64_t n = a.n;
+    for (int item = blockIdx.x; item < *a.nitems; item += gridDim.x) {
     const int leaf = a.item_leaf[item];
     const int q0 = a.item_t0[item] + int(threadIdx.x);
     const int qend = a.leaf.pstart[leaf + 1];
     const int nt = nterms(a.p);
     extern __shared__ double sLx[];  // the leaf's expansion, [3][nt] (dynamic: 3 nt doubles)
+    __syncthreads();                 // the previous item's expansion is read
     for (int t = threadIdx.x; t < nt; t += kL2pLanes)
         for (int d = 0; d < 3; ++d) sLx[d * nt + t] = a.leaf.L[(int64_t(leaf) * 3 + d) * nt + t];
     __syncthreads();
-    if (q0 >= qend) return;
+    if (q0 >= qend) continue;
     int ic[3];
     cell_coords(a.leaf.code[leaf], ic);
     // the second target repeats the first where the item ends (computed, not written)
@@ -1161,6 +1258,7 @@ __global__ __launch_bounds__(kL2pLanes) void k_fmm_l2p(NearArgs a, double* __res
         if (a.grad)
             for (int c = 0; c < 3; ++c)
                 for (int e = 0; e < 3; ++e) far[(6 + 3 * c + e) * n + q] = J[c][e];
+    }
     }
 }
 
@@ -1278,49 +1376,67 @@ __device__ constexpr double near_held_sign(bool classical, bool grad, int c) {
          : (c == 7 ? -1.0 : 1.0);
 }
 
-// Near field of one work item: the exact Gaussian pair sum over the 27 neighbouring leaves.
-// Sources stream through LDS in tiles of 256; each wavefront tests every 64-source subtile
-// against its own 64 targets and runs the loop without the core test where the boxes are
-// farther apart than the subtile's largest core cut (rho_far sigma).  The epilogue adds the
-// far field (if any) and writes in the caller's order.
-template <typename T, bool CLASSICAL, bool GRAD>
-__global__ __launch_bounds__(256, GRAD ? 4 : 1) void k_fmm_near(NearArgs a) {
+// Near field: the exact Gaussian pair sum over the 27 neighbouring leaves, one workgroup per unit
+// of 64 targets (a target per lane of every wavefront).  The neighbours' units are dealt to the NW
+// wavefronts in turn; a wavefront stages a unit's packed records in its own LDS slot (no
+// workgroup barrier in the loop), tests the unit's box against its targets' box and runs the loop
+// without the core test where they are farther apart than the unit's largest core cut
+// (rho_far sigma).  The wavefronts' sums are added in FP64 in a fixed order, and wavefront 0 adds
+// the far field (if any) and writes in the caller's order.
+// Bound by VALU issue (41 instructions per pair with the core test and its branch).
+// Measured (kernel, us; 256 targets per workgroup that shared 256-source tiles / now): the
+// million-particle flight wake at depth 6 20030 / 17300 (1234 G near pairs per second), with the
+// gradient 100003 particles at depth 5 1463 / 900.
+template <typename T, bool CLASSICAL, bool GRAD, int NW>
+__global__ __launch_bounds__(64 * NW, (GRAD && std::is_same<T, float>::value) ? 4 : 1) void k_fmm_near(NearArgs a) {
     constexpr bool kComp = std::is_same<T, float>::value;
     constexpr int NA = GRAD ? 21 : 9;
-    const int item = blockIdx.x;
-    if (item >= *a.nitems) return;
-    const T* __restrict__ xs = static_cast<const T*>(a.xs);
-    const T* __restrict__ gs = static_cast<const T*>(a.gs);
-    const T* __restrict__ ss = static_cast<const T*>(a.ss);
-    const int64_t n = a.n;
-    const int leaf = a.item_leaf[item];
-    const int t0 = a.item_t0[item];
-    const int tend = a.leaf.pstart[leaf + 1];
-    const int q = t0 + int(threadIdx.x);
-    const bool valid = q < tend;
-    const int qq = valid ? q : t0;
-    const int nleaf = *a.count;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int wq0 = t0 + 64 * wv;  // first target of this wavefront
-
     using V4 = typename std::conditional<kComp, float4, double4>::type;
     using V2 = typename std::conditional<kComp, float2, double2>::type;
-    // per source: (x, -Gamma_z), (Gamma, cut) and (1/sigma, 1/sigma^2)
-    __shared__ V4 sp[kNearTile], sq[kNearTile];
-    __shared__ V2 sw[kNearTile];
-    __shared__ T sbox[4][7];
-    __shared__ int32_t nb_lo[27], nb_hi[27];
+    using CT = __attribute__((address_space(4))) const T*;
+    struct Slot {
+        V4 p[kUnit], q[kUnit];
+        V2 w[kUnit];
+    };
+    __shared__ Slot slots[NW];
+    __shared__ int32_t nb_u0[27], nb_hi[27], nb_pre[28];
+    const T* __restrict__ xs = static_cast<const T*>(a.xs);
+    const T* __restrict__ gs = static_cast<const T*>(a.gs);
+    const V4* __restrict__ gsp = static_cast<const V4*>(a.sp);
+    const V4* __restrict__ gsq = static_cast<const V4*>(a.sq);
+    const V2* __restrict__ gsw = static_cast<const V2*>(a.sw);
+    const CT ubox = (CT)(static_cast<const T*>(a.ubox));
+    const int64_t n = a.n;
+    const int nleaf = *a.count, nunits = *a.nunits;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int side = 1 << a.level;
+    Slot& sl = slots[wv];
+    for (int item = blockIdx.x; item < nunits; item += gridDim.x) {
+    const int leaf = a.unit_leaf[item];
+    const int t0 = a.unit_t0[item];
+    const int tend = a.leaf.pstart[leaf + 1];
+    const int q = t0 + lane;
+    const bool valid = q < tend;
+    const int qq = valid ? q : t0;
     int ic[3];
     cell_coords(a.leaf.code[leaf], ic);
-    const int side = 1 << a.level;
+    __syncthreads();  // the previous unit's sums and lists are read
     if (threadIdx.x < 27) {
         const int t = threadIdx.x;
         const int s[3] = {ic[0] + t / 9 - 1, ic[1] + (t / 3) % 3 - 1, ic[2] + t % 3 - 1};
         int idx = -1;
         if (s[0] >= 0 && s[1] >= 0 && s[2] >= 0 && s[0] < side && s[1] < side && s[2] < side)
             idx = find_code(a.leaf.code, nleaf, cell_code(s[0], s[1], s[2]));
-        nb_lo[t] = idx >= 0 ? a.leaf.pstart[idx] : 0;
+        const int u0 = idx >= 0 ? a.unit0[idx] : 0;
+        nb_u0[t] = u0;
         nb_hi[t] = idx >= 0 ? a.leaf.pstart[idx + 1] : 0;
+        nb_pre[t + 1] = idx >= 0 ? a.unit0[idx + 1] - u0 : 0;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        nb_pre[0] = 0;
+        for (int t = 0; t < 27; ++t) nb_pre[t + 1] += nb_pre[t];
     }
     __syncthreads();
 
@@ -1328,76 +1444,58 @@ __global__ __launch_bounds__(256, GRAD ? 4 : 1) void k_fmm_near(NearArgs a) {
     const T gxi = gs[qq], gyi = gs[n + qq], gzi = gs[2 * n + qq];
     // (kept opaque so that their products stay plain multiplies by a register)
     const T ngyi = opaque_reg(-gyi), ngzi = opaque_reg(-gzi);
-    // box of this wavefront's targets (lanes past the end repeat the item's first target)
-    T tlo[3], thi[3], tcut;
-    {
-        const T pl[3] = {xi, yi, zi};
-        wave_box(pl, pl, T(0), tlo, thi, tcut);
+    // this unit's box: its lower and upper corner in scalar registers
+    T tlo[3], thi[3];
+    for (int d = 0; d < 3; ++d) {
+        tlo[d] = ubox[8 * int64_t(item) + d];
+        thi[d] = ubox[8 * int64_t(item) + 3 + d];
     }
     T acc[NA], hi[NA], lo[NA];
 #pragma unroll
     for (int c = 0; c < NA; ++c) acc[c] = hi[c] = lo[c] = T(0);
-    for (int nb = 0; nb < 27; ++nb) {
-        const int lo_j = nb_lo[nb], hi_j = nb_hi[nb];
-        for (int j0 = lo_j; j0 < hi_j; j0 += kNearTile) {
-            const int cnt = hi_j - j0 < kNearTile ? hi_j - j0 : kNearTile;
-            __syncthreads();
-            {
-                const bool has = int(threadIdx.x) < cnt;
-                const int j = has ? j0 + threadIdx.x : j0;
-                T pl[3];
-                for (int d = 0; d < 3; ++d) pl[d] = xs[d * n + j];
-                const T sj = ss[j];
-                const T is = T(1) / sj;
-                const T cut = Prec<T>::kFarRho2 * sj * sj;
-                const T g0 = gs[j], g1 = gs[n + j], g2 = gs[2 * n + j];
-                sp[threadIdx.x] = V4{pl[0], pl[1], pl[2], -g2};
-                sq[threadIdx.x] = V4{g0, g1, g2, cut};
-                sw[threadIdx.x] = V2{is, is * is};
-                // subtile box of this wavefront's 64 staged sources (past the end: the tile's
-                // first source again, which only makes the box larger)
-                T blo[3], bhi[3], bcut;
-                wave_box(pl, pl, cut, blo, bhi, bcut);
-                if (lane == 0) {
-                    for (int d = 0; d < 3; ++d) {
-                        sbox[wv][d] = blo[d];
-                        sbox[wv][3 + d] = bhi[d];
-                    }
-                    sbox[wv][6] = bcut;
-                }
-            }
-            __syncthreads();
-            for (int sub = 0; sub * 64 < cnt; ++sub) {
-                const int jb = sub * 64;
-                const int je = cnt - jb < 64 ? cnt : jb + 64;
-                T d2 = T(0);
-                for (int d = 0; d < 3; ++d) {
-                    const T g1 = sbox[sub][d] - thi[d], g2 = tlo[d] - sbox[sub][3 + d];
-                    const T gap = g1 > g2 ? g1 : g2;
-                    d2 += gap > T(0) ? gap * gap : T(0);
-                }
-                // the self pairs of this wavefront's targets can only lie in a subtile whose
-                // sources overlap their index range
-                const bool self_sub = j0 + jb < wq0 + 64 && j0 + je > wq0;
-                if (d2 >= sbox[sub][6]) {
-                    // every pair of this wavefront and subtile is outside the cores
+    const int total = __builtin_amdgcn_readfirstlane(nb_pre[27]);
+    int nb = 0, folded = 0;
+    for (int k = wv; k < total; k += NW) {
+        while (k >= __builtin_amdgcn_readfirstlane(nb_pre[nb + 1])) ++nb;
+        const int u = __builtin_amdgcn_readfirstlane(nb_u0[nb] + (k - nb_pre[nb]));
+        const int j0 = __builtin_amdgcn_readfirstlane(a.unit_t0[u]);
+        const int left = __builtin_amdgcn_readfirstlane(nb_hi[nb]) - j0;
+        const int cnt = left < kUnit ? left : kUnit;
+        if (lane < cnt) {
+            sl.p[lane] = gsp[j0 + lane];
+            sl.q[lane] = gsq[j0 + lane];
+            sl.w[lane] = gsw[j0 + lane];
+        }
+        __builtin_amdgcn_wave_barrier();
+        const CT ub = ubox + 8 * int64_t(u);
+        T d2 = T(0);
+        for (int d = 0; d < 3; ++d) {
+            const T g1 = ub[d] - thi[d], g2 = tlo[d] - ub[3 + d];
+            const T gap = g1 > g2 ? g1 : g2;
+            d2 += gap > T(0) ? gap * gap : T(0);
+        }
+        if (d2 >= ub[6]) {
+            // every pair of this wavefront and unit is outside the cores
 #pragma unroll 2
-                    for (int jj = jb; jj < je; ++jj)
-                        near_pair<T, CLASSICAL, GRAD, false>(xi, yi, zi, gxi, gyi, gzi, ngyi, ngzi, sp[jj], sq[jj],
-                                                             sw + jj, acc);
-                } else if (self_sub) {
-                    for (int jj = jb; jj < je; ++jj) {
-                        if (j0 + jj == qq) continue;  // self pair
-                        near_pair<T, CLASSICAL, GRAD, true>(xi, yi, zi, gxi, gyi, gzi, ngyi, ngzi, sp[jj], sq[jj],
-                                                            sw + jj, acc);
-                    }
-                } else {
-                    for (int jj = jb; jj < je; ++jj)
-                        near_pair<T, CLASSICAL, GRAD, true>(xi, yi, zi, gxi, gyi, gzi, ngyi, ngzi, sp[jj], sq[jj],
-                                                            sw + jj, acc);
-                }
+            for (int jj = 0; jj < cnt; ++jj)
+                near_pair<T, CLASSICAL, GRAD, false>(xi, yi, zi, gxi, gyi, gzi, ngyi, ngzi, sl.p[jj], sl.q[jj],
+                                                     sl.w + jj, acc);
+        } else if (u == item) {
+            for (int jj = 0; jj < cnt; ++jj) {
+                if (j0 + jj == qq) continue;  // self pair
+                near_pair<T, CLASSICAL, GRAD, true>(xi, yi, zi, gxi, gyi, gzi, ngyi, ngzi, sl.p[jj], sl.q[jj],
+                                                    sl.w + jj, acc);
             }
-            if constexpr (kComp) {
+        } else {
+            for (int jj = 0; jj < cnt; ++jj)
+                near_pair<T, CLASSICAL, GRAD, true>(xi, yi, zi, gxi, gyi, gzi, ngyi, ngzi, sl.p[jj], sl.q[jj],
+                                                    sl.w + jj, acc);
+        }
+        __builtin_amdgcn_wave_barrier();  // every lane is done with the slot before it is refilled
+        // FP32 sums run over at most kFoldUnits units
+        if constexpr (kComp) {
+            if (++folded == kFoldUnits || k + NW >= total) {
+                folded = 0;
 #pragma unroll
                 for (int c = 0; c < NA; ++c) {
                     T s, e;
@@ -1409,11 +1507,31 @@ __global__ __launch_bounds__(256, GRAD ? 4 : 1) void k_fmm_near(NearArgs a) {
             }
         }
     }
-    if (!valid) return;
     double S[NA];
 #pragma unroll
     for (int c = 0; c < NA; ++c)
         S[c] = near_held_sign(CLASSICAL, GRAD, c) * (kComp ? double(hi[c]) + double(lo[c]) : double(acc[c]));
+    // the staging slots carry the sums of wavefronts 1 ... to wavefront 0, kPer sums at a time
+    constexpr int kFit = int(sizeof(slots) / ((NW - 1) * 64 * sizeof(double)));
+    constexpr int kPer = kFit < NA ? kFit : NA;
+    double(*red)[kPer][64] = reinterpret_cast<double(*)[kPer][64]>(&slots[0]);
+#pragma unroll
+    for (int c0 = 0; c0 < NA; c0 += kPer) {
+        __syncthreads();
+        if (wv > 0) {
+#pragma unroll
+            for (int c = 0; c < kPer; ++c)
+                if (c0 + c < NA) red[wv - 1][c][lane] = S[c0 + c];
+        }
+        __syncthreads();
+        if (wv == 0) {
+            for (int w = 0; w < NW - 1; ++w)
+#pragma unroll
+                for (int c = 0; c < kPer; ++c)
+                    if (c0 + c < NA) S[c0 + c] += red[w][c][lane];
+        }
+    }
+    if (wv != 0 || !valid) continue;
     const double Gi[3] = {double(gxi), double(gyi), double(gzi)};
     double u[3] = {S[0] * kInv4Pi, S[1] * kInv4Pi, S[2] * kInv4Pi};
     double dgv[3];
@@ -1463,17 +1581,19 @@ __global__ __launch_bounds__(256, GRAD ? 4 : 1) void k_fmm_near(NearArgs a) {
         T* __restrict__ JO = static_cast<T*>(a.grad);
         for (int c = 0; c < 9; ++c) JO[c * a.ldo + o] = T(Jn[c]);
     }
+    }
 }
 
 // ---------------------------------------------------------------- workspace
 size_t al256(size_t v) { return (v + 255) / 256 * 256; }
 
 struct Layout {
-    size_t keys, box, scan, xs, gs, ss, perm, lcode, terms, dtab, item_leaf, item_t0, counts, far;
+    size_t keys, box, scan, xs, gs, sp, sq, sw, perm, lcode, terms, dtab, item_leaf, item_t0, unit_leaf, unit_t0, unit0,
+        ubox, counts, far;
     size_t code[kMaxLevel + 1], first[kMaxLevel + 1], pstart[kMaxLevel + 1], parent[kMaxLevel + 1];
     size_t M[kMaxLevel + 1], L[kMaxLevel + 1];
     int64_t cap[kMaxLevel + 1];
-    int64_t items_cap;
+    int64_t items_cap, units_cap;
     size_t total;
 };
 
@@ -1492,15 +1612,23 @@ Layout layout(int64_t n, int level, int order, size_t es) {
     y.scan = take(nb * 4 > 6 * kBoxParts * sizeof(double) ? nb * 4 : 6 * kBoxParts * sizeof(double));
     y.xs = take(3 * size_t(n) * es);
     y.gs = take(3 * size_t(n) * es);
-    y.ss = take(size_t(n) * es);
+    y.sp = take(4 * size_t(n) * es);
+    y.sq = take(4 * size_t(n) * es);
+    y.sw = take(2 * size_t(n) * es);
     y.perm = take(size_t(n) * 4);
     y.lcode = take(size_t(n) * 4);
     y.terms = take(size_t(2 * kMaxTerms + 8) * 4);  // + 8: M2L's batched reads past a prefix
     y.dtab = take(size_t(kOffsets) * nt * sizeof(double));
-    y.items_cap = n / kNearTile + n + 1;
+    const int64_t leaves = level < 10 && (int64_t(1) << (3 * level)) < n ? int64_t(1) << (3 * level) : n;
+    y.items_cap = n / kL2pItem + leaves + 1;
+    y.units_cap = n / kUnit + leaves + 1;
     y.item_leaf = take(size_t(y.items_cap) * 4);
     y.item_t0 = take(size_t(y.items_cap) * 4);
-    y.counts = take(size_t(kMaxLevel + 2) * 4);
+    y.unit_leaf = take(size_t(y.units_cap) * 4);
+    y.unit_t0 = take(size_t(y.units_cap) * 4);
+    y.unit0 = take(size_t(leaves + 1) * 4);
+    y.ubox = take(size_t(y.units_cap) * 8 * es);
+    y.counts = take(size_t(kMaxLevel + 3) * 4);
     y.far = take(15 * size_t(n) * sizeof(double));
     for (int l = 0; l <= level; ++l) {
         const int64_t full = int64_t(1) << (3 * l);
@@ -1517,6 +1645,33 @@ Layout layout(int64_t n, int level, int order, size_t es) {
     return y;
 }
 
+// Blocks of 64 terms: 1 up to order 5, 2 up to 7, 3 at 8, 5 up to 10, 8 up to 12.
+void launch_m2l_wave(unsigned cells, size_t lds, hipStream_t st, const FmmLevel& lv, const int32_t* count, int l,
+                     const double* box, int p, const uint32_t* terms, const double* dtab) {
+    const dim3 g(cells), b(64 * kM2lWaves);
+    const int blocks = (nterms(p) + 63) / 64;
+    if (blocks <= 1) hipLaunchKernelGGL(k_fmm_m2l_wave<1>, g, b, lds, st, lv, count, l, box, p, terms, dtab);
+    else if (blocks <= 2) hipLaunchKernelGGL(k_fmm_m2l_wave<2>, g, b, lds, st, lv, count, l, box, p, terms, dtab);
+    else if (blocks <= 3) hipLaunchKernelGGL(k_fmm_m2l_wave<3>, g, b, lds, st, lv, count, l, box, p, terms, dtab);
+    else if (blocks <= 5) hipLaunchKernelGGL(k_fmm_m2l_wave<5>, g, b, lds, st, lv, count, l, box, p, terms, dtab);
+    else hipLaunchKernelGGL(k_fmm_m2l_wave<8>, g, b, lds, st, lv, count, l, box, p, terms, dtab);
+}
+
+template <typename T, bool GRAD, int NW>
+void launch_near(int classical, unsigned grid, const NearArgs& na, hipStream_t st) {
+    if (classical)
+        hipLaunchKernelGGL((k_fmm_near<T, true, GRAD, NW>), dim3(grid), dim3(64 * NW), 0, st, na);
+    else
+        hipLaunchKernelGGL((k_fmm_near<T, false, GRAD, NW>), dim3(grid), dim3(64 * NW), 0, st, na);
+}
+
+// Workgroups launched for a level's cells (or the leaves' items and units) beyond the particles'
+// share; the kernels take further cells in strides of the grid.  The occupied cells are known only
+// on the device, and a workgroup per possible cell would be mostly empty (262144 at depth 6, of
+// which the million-particle wake occupies 616).
+constexpr int64_t kCellBlocks = 4096;
+constexpr int64_t kNearFewUnits = 512;
+
 template <typename T>
 hipError_t run_fmm(int64_t n, const T* x, const T* g, const T* sg, int64_t ld, int level, int p, int classical,
                    T* u, T* dg, T* grad, int64_t ldo, unsigned char* ws, hipStream_t st) {
@@ -1525,14 +1680,22 @@ hipError_t run_fmm(int64_t n, const T* x, const T* g, const T* sg, int64_t ld, i
     double* box = reinterpret_cast<double*>(ws + y.box);
     T* xs = reinterpret_cast<T*>(ws + y.xs);
     T* gs = reinterpret_cast<T*>(ws + y.gs);
-    T* ss = reinterpret_cast<T*>(ws + y.ss);
+    using V4 = typename std::conditional<std::is_same<T, float>::value, float4, double4>::type;
+    using V2 = typename std::conditional<std::is_same<T, float>::value, float2, double2>::type;
+    V4* sp = reinterpret_cast<V4*>(ws + y.sp);
+    V4* sq = reinterpret_cast<V4*>(ws + y.sq);
+    V2* sw = reinterpret_cast<V2*>(ws + y.sw);
+    int32_t* unit_leaf = reinterpret_cast<int32_t*>(ws + y.unit_leaf);
+    int32_t* unit_t0 = reinterpret_cast<int32_t*>(ws + y.unit_t0);
+    int32_t* unit0 = reinterpret_cast<int32_t*>(ws + y.unit0);
+    T* ubox = reinterpret_cast<T*>(ws + y.ubox);
     int32_t* perm = reinterpret_cast<int32_t*>(ws + y.perm);
     uint32_t* lcode = reinterpret_cast<uint32_t*>(ws + y.lcode);
     uint32_t* terms = reinterpret_cast<uint32_t*>(ws + y.terms);
     double* dtab = reinterpret_cast<double*>(ws + y.dtab);
     int32_t* item_leaf = reinterpret_cast<int32_t*>(ws + y.item_leaf);
     int32_t* item_t0 = reinterpret_cast<int32_t*>(ws + y.item_t0);
-    int32_t* counts = reinterpret_cast<int32_t*>(ws + y.counts);  // [level + 1] cells, then items
+    int32_t* counts = reinterpret_cast<int32_t*>(ws + y.counts);  // [level + 1] cells, then items and units
     FmmLevel lv[kMaxLevel + 1];
     for (int l = 0; l <= level; ++l) {
         lv[l].code = reinterpret_cast<uint32_t*>(ws + y.code[l]);
@@ -1557,8 +1720,8 @@ hipError_t run_fmm(int64_t n, const T* x, const T* g, const T* sg, int64_t ld, i
     hipLaunchKernelGGL(k_fmm_keys<T>, dim3(unsigned(P / 256)), dim3(256), 0, st, x, ld, n, level, box, keys, P);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = sort_keys(keys, P, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_fmm_gather<T>, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, x, g, sg, ld, n, keys, xs,
-                       gs, ss, perm, lcode, level);
+    hipLaunchKernelGGL((k_fmm_gather<T, V4, V2>), dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, x, g, sg, ld, n,
+                       keys, xs, gs, sp, sq, sw, perm, lcode, level);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // leaves: distinct leaf codes of the sorted particles
     {
@@ -1582,69 +1745,70 @@ hipError_t run_fmm(int64_t n, const T* x, const T* g, const T* sg, int64_t ld, i
     }
     hipLaunchKernelGGL(k_fmm_terms, dim3(1), dim3(64), 0, st, p, terms);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    // M2L: as many groups of 256 lanes as 60 KiB of LDS allow (at most 4), each holding its grid
-    // (or its 3 nt sums at the end if those are larger); where fewer than two fit, one group of
-    // kUnitWaves wavefronts that share the terms' walks in balanced pieces (m2l_units)
-    const size_t m2l_grid = size_t(m2l_group_doubles(p, false)) * sizeof(double);
-    int m2l_groups = int((60 * 1024) / m2l_grid);
-    m2l_groups = m2l_groups > 4 ? 4 : m2l_groups;
-    int m2l_gsize = 256;
     M2lUnits units{};
-    size_t m2l_lds = size_t(m2l_groups) * m2l_grid;
-    if (m2l_groups < 2) {
-        m2l_groups = 1;
-        m2l_gsize = 64 * kUnitWaves;
+    size_t m2l_lds = size_t(kM2lWaves) * m2l_grid_doubles(p) * sizeof(double);
+    if (p > kM2lWaveOrder) {
         if (!m2l_units(p, units)) return hipErrorInvalidValue;
-        // the group's grid, moments and indices, or the pieces' partial sums at the end
-        const size_t grid = size_t(m2l_group_doubles(p, true));
+        // the grid, moments and indices, or the pieces' partial sums at the end
+        const size_t grid = size_t(m2l_unit_doubles(p));
         const size_t sums = size_t(units.n) * 64 * 3;
         m2l_lds = (grid > sums ? grid : sums) * sizeof(double);
-    } else if (nterms(p) > 5 * m2l_gsize) {
-        // every term has a lane: 5 per lane in 256-lane groups (two or more groups fit only
-        // while 3 nt doubles take at most 30 KiB, nt <= 1280)
-        return hipErrorInvalidValue;
     }
+    auto cells_of = [&](int l) { return unsigned(std::min<int64_t>(y.cap[l], kCellBlocks)); };
     const size_t shift_lds = size_t(6 * nterms(p)) * sizeof(double);  // M2M and L2L: two 3 nt buffers
     if (level >= 2) {
         hipLaunchKernelGGL(k_fmm_dtab, dim3(kOffsets), dim3(256), 0, st, p, terms, dtab);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_fmm_p2m<T>, dim3(unsigned(y.cap[level])), dim3(256), 0, st, xs, gs, n, lv[level],
+        hipLaunchKernelGGL(k_fmm_p2m<T>, dim3(cells_of(level)), dim3(256), 0, st, xs, gs, n, lv[level],
                            counts + level, box, level, p, terms);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         for (int l = level - 1; l >= 2; --l) {
-            hipLaunchKernelGGL(k_fmm_m2m, dim3(unsigned(y.cap[l])), dim3(256), shift_lds, st, lv[l], lv[l + 1],
+            hipLaunchKernelGGL(k_fmm_m2m, dim3(cells_of(l)), dim3(256), shift_lds, st, lv[l], lv[l + 1],
                                counts + l, l, box, p, terms);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
         for (int l = 2; l <= level; ++l) {
-            if (m2l_gsize == 256)
-                hipLaunchKernelGGL((k_fmm_m2l<5, false>), dim3(unsigned(y.cap[l])), dim3(256 * m2l_groups), m2l_lds, st, lv[l],
-                               counts + l, l, box, p, terms, dtab, m2l_gsize, units);
+            const unsigned cells = cells_of(l);
+            if (p > kM2lWaveOrder)
+                hipLaunchKernelGGL(k_fmm_m2l, dim3(cells), dim3(64 * kUnitWaves), m2l_lds, st, lv[l], counts + l, l, box,
+                                   p, terms, dtab, units);
             else
-                hipLaunchKernelGGL((k_fmm_m2l<2, true>), dim3(unsigned(y.cap[l])), dim3(m2l_gsize), m2l_lds, st, lv[l],
-                               counts + l, l, box, p, terms, dtab, m2l_gsize, units);
+                launch_m2l_wave(cells, m2l_lds, st, lv[l], counts + l, l, box, p, terms, dtab);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             if (l >= 3) {
-                hipLaunchKernelGGL(k_fmm_l2l, dim3(unsigned(y.cap[l])), dim3(256), shift_lds, st, lv[l], lv[l - 1],
+                hipLaunchKernelGGL(k_fmm_l2l, dim3(cells_of(l)), dim3(256), shift_lds, st, lv[l], lv[l - 1],
                                    counts + l, l, box, p, terms);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
         }
     }
+    int32_t* item_counts = counts + level + 1;
     hipLaunchKernelGGL(k_fmm_items, dim3(1), dim3(1024), 0, st, counts + level, lv[level].pstart, item_leaf, item_t0,
-                       counts + level + 1);
+                       unit_leaf, unit_t0, unit0, item_counts);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // one workgroup per unit of a moderately occupied tree; further units are taken in strides
+    const int64_t near_grid = std::min<int64_t>(y.units_cap, n / kUnit + kCellBlocks);
+    hipLaunchKernelGGL((k_fmm_unit_box<T, V4>), dim3(unsigned(std::min<int64_t>((y.units_cap + 3) / 4, 4096))), dim3(256),
+                       0, st, item_counts + 1, unit_leaf, unit_t0, lv[level].pstart, sp, sq, ubox);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     NearArgs na;
     na.xs = xs;
     na.gs = gs;
-    na.ss = ss;
+    na.sp = sp;
+    na.sq = sq;
+    na.sw = sw;
+    na.ubox = ubox;
     na.perm = perm;
     na.n = n;
     na.leaf = lv[level];
     na.count = counts + level;
     na.item_leaf = item_leaf;
     na.item_t0 = item_t0;
-    na.nitems = counts + level + 1;
+    na.nitems = item_counts;
+    na.unit_leaf = unit_leaf;
+    na.unit_t0 = unit_t0;
+    na.unit0 = unit0;
+    na.nunits = item_counts + 1;
     na.box = box;
     na.level = level;
     na.p = p;
@@ -1653,7 +1817,7 @@ hipError_t run_fmm(int64_t n, const T* x, const T* g, const T* sg, int64_t ld, i
     na.dg = dg;
     na.grad = grad;
     na.ldo = ldo;
-    const unsigned grid = unsigned((n + kNearTile - 1) / kNearTile + y.cap[level]);
+    const unsigned grid = unsigned(std::min<int64_t>(y.items_cap, n / kL2pItem + kCellBlocks));
     if (level >= 2) {
         double* far = reinterpret_cast<double*>(ws + y.far);
         const size_t l2p_lds = size_t(3 * nterms(p)) * sizeof(double);
@@ -1664,16 +1828,15 @@ hipError_t run_fmm(int64_t n, const T* x, const T* g, const T* sg, int64_t ld, i
         if ((e = hipGetLastError()) != hipSuccess) return e;
         na.far = far;
     }
-    if (grad) {
-        if (classical)
-            hipLaunchKernelGGL((k_fmm_near<T, true, true>), dim3(grid), dim3(256), 0, st, na);
-        else
-            hipLaunchKernelGGL((k_fmm_near<T, false, true>), dim3(grid), dim3(256), 0, st, na);
+    const unsigned ng = unsigned(near_grid);
+    // four wavefronts per unit; more while the units are too few to fill the chip with four
+    constexpr int kFewWaves = std::is_same<T, float>::value ? 16 : 8;
+    if (n / kUnit < kNearFewUnits) {
+        if (grad) launch_near<T, true, kFewWaves>(classical, ng, na, st);
+        else launch_near<T, false, kFewWaves>(classical, ng, na, st);
     } else {
-        if (classical)
-            hipLaunchKernelGGL((k_fmm_near<T, true, false>), dim3(grid), dim3(256), 0, st, na);
-        else
-            hipLaunchKernelGGL((k_fmm_near<T, false, false>), dim3(grid), dim3(256), 0, st, na);
+        if (grad) launch_near<T, true, 4>(classical, ng, na, st);
+        else launch_near<T, false, 4>(classical, ng, na, st);
     }
     return hipGetLastError();
 }

@@ -83,6 +83,20 @@ def test_fmm_edge_cases(kind, gpu):
     assert rel_l2(host(u), uo) <= TOL[kind] and rel_l2(host(d), do) <= TOL[kind]
 
 
+@pytest.mark.parametrize("kind", KINDS)
+# more particles than the near field gives sixteen wavefronts per 64 targets; leaves from one
+# particle to many units; every width of the M2L's term blocks
+@pytest.mark.parametrize("level,order", [(4, 4), (4, 8), (5, 10), (4, 12), (4, 14)])
+def test_fmm_many_units_matches_oracle_fmm(kind, level, order, gpu):
+    x, g, s = _wake(33001, kind)
+    say(f"fmm units {kind} level={level} order={order}")
+    u, d, J = vpm.vpm_fmm_eval(dev(x, kind), dev(g, kind), dev(s, kind), level, order, want_grad=True)
+    u2, d2 = vpm.vpm_fmm_eval(dev(x, kind), dev(g, kind), dev(s, kind), level, order)
+    uo, do, Jo = oracle.fmm(x, g, s, level, order, want_grad=True)
+    for got, ref in ((u, uo), (d, do), (J, Jo.reshape(9, -1)), (u2, uo), (d2, do)):
+        assert rel_l2(host(got), ref) <= TOL[kind]
+
+
 def test_fmm_full_size_against_direct(gpu):
     """The 1,048,576-particle forward-flight wake at depth 6 (leaf width 6.5 sigma_max) and
     orders 12 and 18: the FP32C FMM against the FP64 oracle's direct sums at 512 sampled
