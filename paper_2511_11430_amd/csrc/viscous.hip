@@ -24,13 +24,17 @@
 //   4. k_pack: one 12-value record per particle in sorted order
 //      (x, y, z, sigma^2/2 | omega = Gamma/V, V | (nu + nu_t)/2, 0, 0, 0);
 //   5. k_sub_box: bounding box and largest sigma^2/2 of every 64 records (and of every 256);
-//   6. k_pse: one wavefront per 64 sorted targets, independent of the other wavefronts (no
-//      workgroup barrier).  It skips 256-record tiles and then 64-record subtiles that are out of
+//   6. k_pse: a workgroup per 64 sorted targets, whose wavefronts take the 256-record tiles in turn,
+//      independently of each other (no workgroup barrier in the loop).  A wavefront skips 256-record tiles and then 64-record subtiles that are out of
 //      reach of its own box (boxes read with scalar loads, the next tile's ahead of its test),
 //      stages each remaining subtile into its own LDS slot with one coalesced load, and reads the
 //      records from there by broadcast.  Pairs outside the cut take no transcendental.  FP32
-//      sums are folded into two-sum pairs after every subtile; the epilogue runs in FP64 and
-//      writes each result to the particle's original index.
+//      sums are folded into two-sum pairs after every subtile; the wavefronts' sums are added in
+//      FP64 in a fixed order, and the epilogue writes each result to the particle's original index.
+//      Bound by VALU issue and, for few particles, by a wavefront's scan over the tiles' boxes: one
+//      wavefront per 64 targets left 100003 particles 1.5 wavefronts per SIMD.
+//      Measured (FP32, whole call, us, one wavefront / now): 5000 hover particles 357 / 105, 20000
+//      1051 / 210, 100003 4066 / 1158 (flight 1313 / 471), a million in flight 13894 / 9000.
 //  - k_vreman: one lane per particle, FP64 arithmetic.
 #include <hip/hip_runtime.h>
 
@@ -42,7 +46,6 @@ namespace vpm {
 namespace {
 
 constexpr int kTile = 256;
-constexpr int kFold = 128;
 
 template <typename T>
 using V4 = typename std::conditional<std::is_same<T, float>::value, float4, double4>::type;
@@ -243,6 +246,8 @@ __global__ __launch_bounds__(256) void k_sub_box(const PseRec<T>* __restrict__ r
     }
 }
 
+constexpr int64_t kPseFewGroups = 1024;
+
 struct PseArgs {
     const void* rec;
     const void* sub;
@@ -265,17 +270,16 @@ __device__ __forceinline__ bool box_near(const T* b, const T (&lo)[3], const T (
     return d2 < far2 * (b[6] + h);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_pse(PseArgs a) {
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void k_pse(PseArgs a) {
     using CT = __attribute__((address_space(4))) const T*;
     constexpr bool kComp = std::is_same<T, float>::value;
     using V4 = typename std::conditional<kComp, float4, double4>::type;
     // each wavefront stages the 64 records of one near subtile at a time in its own slot
-    __shared__ V4 lrec[4][64][3];
+    __shared__ V4 lrec[NW][64][3];
     const T far2 = T(Prec<T>::kFarRho2);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-    const int64_t p0 = (int64_t(blockIdx.x) * 4 + wave) * 64;
-    if (p0 >= a.n) return;  // the whole wavefront
+    const int64_t p0 = int64_t(blockIdx.x) * 64;
     const int lane = threadIdx.x & 63;
     const int64_t p = p0 + lane;
     const bool valid = p < a.n;
@@ -303,11 +307,14 @@ __global__ __launch_bounds__(256) void k_pse(PseArgs a) {
     const int64_t ntiles = (a.n + 255) / 256;
     const int64_t nsub = (a.n + 63) / 64;
     T tb[7];
+    {
+        const int64_t t0 = wave < ntiles ? wave : 0;
 #pragma unroll
-    for (int c = 0; c < 7; ++c) tb[c] = ctile[c];
-    for (int64_t tt = 0; tt < ntiles; ++tt) {
-        // the next tile's box is read before this one is tested
-        const int64_t tn = tt + 1 < ntiles ? tt + 1 : tt;
+        for (int c = 0; c < 7; ++c) tb[c] = ctile[8 * t0 + c];
+    }
+    for (int64_t tt = wave; tt < ntiles; tt += NW) {
+        // this wavefront's next tile's box is read before this one is tested
+        const int64_t tn = tt + NW < ntiles ? tt + NW : tt;
         T nb[7];
 #pragma unroll
         for (int c = 0; c < 7; ++c) nb[c] = ctile[8 * tn + c];
@@ -360,16 +367,28 @@ __global__ __launch_bounds__(256) void k_pse(PseArgs a) {
 #pragma unroll
         for (int c = 0; c < 7; ++c) tb[c] = nb[c];
     }
-    if (!valid) return;
+    double tot[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) tot[c] = kComp ? double(shi[c]) + double(slo[c]) : double(acc[c]);
+    // the staging slots carry the sums of wavefronts 1 ... to wavefront 0
+    double(*red)[3][64] = reinterpret_cast<double(*)[3][64]>(&lrec[0][0][0]);
+    static_assert(sizeof(lrec) >= (NW - 1) * 3 * 64 * sizeof(double), "three sums per wavefront fit its slot");
+    __syncthreads();
+    if (wave > 0) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) red[wave - 1][c][lane] = tot[c];
+    }
+    __syncthreads();
+    if (wave != 0 || !valid) return;
+    for (int w = 0; w < NW - 1; ++w)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) tot[c] += red[w][c][lane];
     {
         // With inv = 1 / sigma_ij^2 the pair weight (2 nu_ij / sigma_ij^2) zeta_{sigma_ij} equals
         // nu_ij inv^(5/2) exp(-s^2 inv / 2) 2 (2 pi)^(-3/2); the sums above hold everything but
         // the constant and V_i.
 #pragma clang fp contract(off)
         constexpr double kPseScale = 0.1269872718684819395715266098692720;  // 2 (2 pi)^(-3/2)
-        double tot[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) tot[c] = kComp ? double(shi[c]) + double(slo[c]) : double(acc[c]);
         uint64_t li = a.keys[p] & 0xffffffffull;
         if (li >= uint64_t(a.n)) return;  // never taken after a correct sort
         const int64_t i = a.begin + int64_t(li);
@@ -466,7 +485,12 @@ hipError_t pse_set(int64_t begin, int64_t end, const T* x, const T* g, const T* 
     a.dg = dg;
     a.ldo = ldo;
     a.accumulate = accumulate;
-    hipLaunchKernelGGL(k_pse<T>, dim3(unsigned(ntiles)), dim3(256), 0, st, a);
+    // four wavefronts per 64 targets; sixteen while that leaves the chip short of wavefronts
+    const int64_t groups = (n + 63) / 64;
+    if (groups < kPseFewGroups)
+        hipLaunchKernelGGL((k_pse<T, 16>), dim3(unsigned(groups)), dim3(1024), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_pse<T, 4>), dim3(unsigned(groups)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 }  // namespace

@@ -243,3 +243,22 @@ def test_viscous_chain_small(kind, gpu):
     do = do + oracle.pse(x, g, s, vol, W.NU_AIR, nuto)
     assert rel_l2(host(nut), nuto) <= TOL[kind]
     assert rel_l2(host(d), do) <= TOL[kind]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+# a group of 64 targets and its neighbours, one tile of 256 records per wavefront and one more, and
+# both widths of the workgroup
+@pytest.mark.parametrize("n", [63, 65, 257, 1025, 4097, 65601])
+def test_diffusion_at_group_sizes(kind, n, gpu):
+    rng = np.random.default_rng([41, n])
+    if n < 10000:
+        x, g, s = _random_set(n, 43)
+    else:
+        w = W.hover_wake(n, 1, 0.02, 10, rng)
+        x, g, s = w["x"], w["gamma"], w["sigma"]
+    x, g, s, vol, nut = prepare([x, g, s, W.particle_volume(s), rng.uniform(0.0, 1e-4, n)], kind)
+    say(f"diffusion {kind} n={n}")
+    d = vpm.vpm_eval_diffusion(dev(x, kind), dev(g, kind), dev(s, kind), dev(vol, kind), W.NU_AIR, dev(nut, kind))
+    idx = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 300)]))
+    ref = oracle.pse(x, g, s, vol, W.NU_AIR, nut, targets=idx)
+    assert rel_l2(host(d)[:, idx], ref) <= TOL[kind]
