@@ -17,6 +17,8 @@
 // multiply-adds, and the sums hold u_y and u_z negated until the epilogue.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_math.h"
 #include "vpm_internal.h"
 
@@ -281,6 +283,13 @@ template <typename T> __device__ __forceinline__ Dl<T> operator*(T a, Dl<T> b) {
 __device__ __forceinline__ float val(float x) { return x; }
 __device__ __forceinline__ double val(double x) { return x; }
 template <typename T> __device__ __forceinline__ T val(Dl<T> x) { return x.v; }
+// 0 where the pair is dropped (a select per number: selecting a whole dual number goes through
+// scratch memory)
+__device__ __forceinline__ float zero_if(bool off, float x) { return off ? 0.0f : x; }
+__device__ __forceinline__ double zero_if(bool off, double x) { return off ? 0.0 : x; }
+template <typename T> __device__ __forceinline__ Dl<T> zero_if(bool off, Dl<T> x) {
+    return {off ? T(0) : x.v, off ? T(0) : x.d};
+}
 __device__ __forceinline__ float recip(float x) { return 1.0f / x; }
 __device__ __forceinline__ double recip(double x) { return 1.0 / x; }
 template <typename T> __device__ __forceinline__ Dl<T> recip(Dl<T> x) {
@@ -318,16 +327,9 @@ __device__ __forceinline__ void seg_pair(const S (&P)[3], const V4<T>& p, const 
     const S D = d1 * i1 - d2 * i2;
     const S e1 = d1 * i1 * i1 * i1, e2 = d2 * i2 * i2 * i2;
     const S di = i1 - i2;
-    const S gDx = q.x * di - r1x * e1 + r2x * e2;
-    const S gDy = q.y * di - r1y * e1 + r2y * e2;
-    const S gDz = q.z * di - r1z * e1 + r2z * e2;
-    // c x r0
-    const S wx = c[1] * q.z - c[2] * q.y;
-    const S wy = c[2] * q.x - c[0] * q.z;
-    const S wz = c[0] * q.y - c[1] * q.x;
     S ga, gb;  // grad f = ga grad D + gb (c x r0)
     if constexpr (VN == 0) {
-        const S ic2 = val(c2) > T(0) ? recip(c2) : S(T(0));
+        const S ic2 = zero_if(!(val(c2) > T(0)), recip(c2));
         f = p.w * D * ic2;
         ga = p.w * ic2;
         gb = T(-2) * f * ic2;
@@ -349,13 +351,27 @@ __device__ __forceinline__ void seg_pair(const S (&P)[3], const V4<T>& p, const 
         ga = p.w * Kc;
         gb = (T(2) * p.w) * D * Kp * inv_l02;
     }
-    // selected after the products: an arm of zero length makes grad D non-finite
+    // (an arm of zero length makes the factors non-finite)
     const bool off = val(l1s) < eps2 || val(l2s) < eps2;
-    const S zero(T(0));
-    f = off ? zero : f;
-    g[0] = off ? zero : ga * gDx + gb * wx;
-    g[1] = off ? zero : ga * gDy + gb * wy;
-    g[2] = off ? zero : ga * gDz + gb * wz;
+    f = zero_if(off, f);
+    if constexpr (std::is_same<S, T>::value) {
+        // with r2 = r1 - r0 and c x r0 = |r0|^2 r1 - (r0.r1) r0 the gradient is a sum of r0 and r1
+        const S al = zero_if(off, ga * (di - e2) - gb * d1);
+        const S be = zero_if(off, ga * (e2 - e1) + gb * q.w);
+        g[0] = al * q.x + be * r1x;
+        g[1] = al * q.y + be * r1y;
+        g[2] = al * q.z + be * r1z;
+    } else {
+        // (its derivative loses digits in that form: FP32 error of x_bar 1.15e-6, 7.4e-7 in this one)
+        const S wx = c[1] * q.z - c[2] * q.y;  // c x r0
+        const S wy = c[2] * q.x - c[0] * q.z;
+        const S wz = c[0] * q.y - c[1] * q.x;
+        gb = zero_if(off, gb);
+        const S k0 = zero_if(off, ga * di), k1 = zero_if(off, ga * e1), k2 = zero_if(off, ga * e2);
+        g[0] = q.x * k0 - r1x * k1 + r2x * k2 + gb * wx;
+        g[1] = q.y * k0 - r1y * k1 + r2y * k2 + gb * wy;
+        g[2] = q.z * k0 - r1z * k1 + r2z * k2 + gb * wz;
+    }
 }
 
 // Stages one tile of segments in LDS (shared by the gradient and adjoint kernels).
@@ -410,14 +426,39 @@ __device__ __forceinline__ void fold_tile(T (&acc)[NA], T (&hi)[NA], T (&lo)[NA]
     }
 }
 
+// J += [w]x (row-major; [w]x y = w x y).
+__device__ __forceinline__ void add_cross(double* J, const double* w) {
+    J[1] -= w[2];
+    J[2] += w[1];
+    J[3] += w[2];
+    J[5] -= w[0];
+    J[6] -= w[1];
+    J[7] += w[0];
+}
+
+// A lane's share of a tile: 256 / LPT consecutive segments, started at a rotated place so that the
+// lanes' LDS reads fall into different banks.  Consecutive segments are mostly the edges of one
+// ring, whose contributions largely cancel: dealt out one by one, every lane sums edges that do
+// not, with several times the rounding error.
+template <int LPT>
+__device__ __forceinline__ int share_index(int part, int i) {
+    constexpr int C = 256 / LPT;
+    return part * C + ((i + part * C / 16) & (C - 1));
+}
+// FP32 sums run over at most 64 segments between folds.
+template <int LPT>
+constexpr int kFoldTiles = LPT > 4 ? LPT / 4 : 1;
+
 // LPT lanes per target (neighbouring lanes of one wavefront) split each staged tile of segments
-// between them, lane q taking the segments q, q + LPT, ...; their sums are added in FP64 by a
-// butterfly before the write, so a launch with few targets still has several wavefronts per SIMD.
+// between them (share_index); their sums are added in FP64 by a butterfly before the write, so a
+// launch with few targets still has several wavefronts per SIMD.  Bound by VALU issue: 83
+// instructions per pair (FP32, exponent 2; 100 with grad D and c x r0 formed apart and the nine
+// products of [r0]x summed).  J = [sum f r0]x + sum c g^T.
 template <typename T, int WG, int VN, int LPT>
 __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
-    static_assert((LPT & (LPT - 1)) == 0 && LPT <= 64, "a power of two within a wavefront");
+    static_assert((LPT & (LPT - 1)) == 0 && LPT <= 64 && WG == 256, "a power of two within a wavefront");
     constexpr bool kComp = std::is_same<T, float>::value;
-    constexpr int NA = 12;  // u (3), J row-major (9)
+    constexpr int NA = 15;  // u (3), sum c g^T row-major (9), sum f r0 (3)
     __shared__ V4<T> l0[WG];
     __shared__ V4<T> l1[WG];
     __shared__ V2<T> l2[WG];  // (eps^2 for the arms, 1/|r0|^2)
@@ -440,7 +481,9 @@ __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
         __syncthreads();
         stage_segments<T, WG, VN>(a, j0, cnt, l0, l1, l2);
         __syncthreads();
-        for (int jj = part; jj < cnt; jj += LPT) {
+        for (int i = 0; i < WG / LPT; ++i) {
+            const int jj = share_index<LPT>(part, i);
+            if (jj >= cnt) continue;
             const V4<T> p = l0[jj];
             const V4<T> q = l1[jj];
             const T eps2 = l2[jj].x;
@@ -450,18 +493,17 @@ __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
             acc[0] += f * c[0];
             acc[1] += f * c[1];
             acc[2] += f * c[2];
-            // f [r0]x + c g^T
-            acc[3] += c[0] * g[0];
-            acc[4] += c[0] * g[1] - f * q.z;
-            acc[5] += c[0] * g[2] + f * q.y;
-            acc[6] += c[1] * g[0] + f * q.z;
-            acc[7] += c[1] * g[1];
-            acc[8] += c[1] * g[2] - f * q.x;
-            acc[9] += c[2] * g[0] - f * q.y;
-            acc[10] += c[2] * g[1] + f * q.x;
-            acc[11] += c[2] * g[2];
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) acc[3 + 3 * r + b] += c[r] * g[b];
+            acc[12] += f * q.x;
+            acc[13] += f * q.y;
+            acc[14] += f * q.z;
         }
-        if constexpr (kComp) fold_tile<T, NA>(acc, hi, lo);
+        if constexpr (kComp) {
+            if ((j0 / WG) % kFoldTiles<LPT> == kFoldTiles<LPT> - 1 || j0 + WG >= a.n_seg) fold_tile<T, NA>(acc, hi, lo);
+        }
     }
     T* __restrict__ U = static_cast<T*>(a.u);
     T* __restrict__ Jo = static_cast<T*>(a.grad);
@@ -475,6 +517,7 @@ __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
     for (int m = 1; m < LPT; m <<= 1)
 #pragma unroll
         for (int c = 0; c < NA; ++c) v[c] += __shfl_xor(v[c], m, 64);
+    add_cross(v + 3, v + 12);
     if (!valid || part != 0) return;
     if (U) {
 #pragma unroll
@@ -515,9 +558,9 @@ __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
 // LPT lanes per target share each staged tile as in k_segments_grad.
 template <typename T, int WG, int VN, int LPT>
 __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
-    static_assert((LPT & (LPT - 1)) == 0 && LPT <= 64, "a power of two within a wavefront");
+    static_assert((LPT & (LPT - 1)) == 0 && LPT <= 64 && WG == 256, "a power of two within a wavefront");
     constexpr bool kComp = std::is_same<T, float>::value;
-    constexpr int NA = 12;  // J row-major (9), term (3)
+    constexpr int NA = 15;  // sum c g^T row-major (9), term (3), sum f r0 (3)
     using S = Dl<T>;
     __shared__ V4<T> l0[WG];
     __shared__ V4<T> l1[WG];
@@ -542,8 +585,12 @@ __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
             db[c] = Db[c * a.ldb + tt];
         }
     }
-    const T* w1 = a.classical ? gam : db;
-    const T* w2 = a.classical ? db : gam;
+    T w1[3], w2[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        w1[c] = a.classical ? gam[c] : db[c];
+        w2[c] = a.classical ? db[c] : gam[c];
+    }
     S P[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) P[c] = S(X[c * a.ldt + tt], w1[c]);
@@ -556,22 +603,22 @@ __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
         __syncthreads();
         stage_segments<T, WG, VN>(a, j0, cnt, l0, l1, l2);
         __syncthreads();
-        for (int jj = part; jj < cnt; jj += LPT) {
+        for (int i = 0; i < WG / LPT; ++i) {
+            const int jj = share_index<LPT>(part, i);
+            if (jj >= cnt) continue;
             const V4<T> p = l0[jj];
             const V4<T> q = l1[jj];
             const T eps2 = l2[jj].x;
             const T inv_l02 = l2[jj].y;
             S f, c[3], g[3];
             seg_pair<S, T, VN>(P, p, q, eps2, inv_l02, rc2n, inv_n, n_f, f, c, g);
-            acc[0] += c[0].v * g[0].v;
-            acc[1] += c[0].v * g[1].v - f.v * q.z;
-            acc[2] += c[0].v * g[2].v + f.v * q.y;
-            acc[3] += c[1].v * g[0].v + f.v * q.z;
-            acc[4] += c[1].v * g[1].v;
-            acc[5] += c[1].v * g[2].v - f.v * q.x;
-            acc[6] += c[2].v * g[0].v - f.v * q.y;
-            acc[7] += c[2].v * g[1].v + f.v * q.x;
-            acc[8] += c[2].v * g[2].v;
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) acc[3 * r + b] += c[r].v * g[b].v;
+            acc[12] += f.v * q.x;
+            acc[13] += f.v * q.y;
+            acc[14] += f.v * q.z;
             const T wc = w2[0] * c[0].v + w2[1] * c[1].v + w2[2] * c[2].v;
             const T wcd = w2[0] * c[0].d + w2[1] * c[1].d + w2[2] * c[2].d;
             // w2 x r0
@@ -582,7 +629,9 @@ __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
             acc[10] += f.d * xr1 + wcd * g[1].v + wc * g[1].d;
             acc[11] += f.d * xr2 + wcd * g[2].v + wc * g[2].d;
         }
-        if constexpr (kComp) fold_tile<T, NA>(acc, hi, lo);
+        if constexpr (kComp) {
+            if ((j0 / WG) % kFoldTiles<LPT> == kFoldTiles<LPT> - 1 || j0 + WG >= a.n_seg) fold_tile<T, NA>(acc, hi, lo);
+        }
     }
     double v[NA];
 #pragma unroll
@@ -592,6 +641,7 @@ __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
     for (int m = 1; m < LPT; m <<= 1)
 #pragma unroll
         for (int c = 0; c < NA; ++c) v[c] += __shfl_xor(v[c], m, 64);
+    add_cross(v, v + 12);
     if (!valid || part != 0) return;
     T* __restrict__ Xb = static_cast<T*>(a.xb);
     T* __restrict__ Gb = static_cast<T*>(a.gb);
@@ -656,9 +706,9 @@ hipError_t launch_grad_t(const SegArgs& a, hipStream_t st) {
 // workgroups are resident (four wavefronts per SIMD), so a launch takes
 // ceil(LPT n / 256 / kSegSlots) rounds of that.
 // Measured (4096 segments, exponent 2, FP32, us): adjoint with one lane per target at every size /
-// with this rule: 1000 targets 1914 / 54, 16384 1921 / 314, 150000 3671 / 2531, 400000 8274 / 6727;
-// gradient with 16 lanes up to 16384 targets, 4 up to 196608, 1 above / with this rule: 1000 73 /
-// 33, 20000 329 / 245, 100003 956 / 889, 200000 2126 / 1717, 400000 3585 / 3394.
+// now: 1000 targets 1914 / 46, 16384 1921 / 335, 100003 2425 /
+// 1943, 400000 7984 / 6932; gradient with 16 lanes up to 16384 targets, 4 up to 196608, 1 above /
+// now: 1000 73 / 29, 16384 168 / 138, 100003 960 / 710, 400000 3585 / 2718.
 constexpr int64_t kSegSlots = 1024;
 constexpr int kGradPairOps = 120, kVjpPairOps = 300, kSegStageOps = 150;
 int lanes_per_target(int64_t n_tgt, int per_pair) {
