@@ -6,9 +6,9 @@
 //    closed path c00 -> c01 -> c11 -> c10 with unit circulation; each edge is the finite
 //    straight segment law (r1 x r2) r0 . (r1/|r1| - r2/|r2|) / (4 pi |r0|^2 (d^2n + rc^2n)^(1/n))
 //    with the Vatistas core, d^2 = |r1 x r2|^2 / |r0|^2.  Entry = n_i . u_ring_j(c_i).
-//  - k_lu_panel / k_lu_swap_trsm / k_lu_gemm: dense LU with partial pivoting, blocked
-//    in panels of 16 columns for n <= 1024 (a panel in one workgroup with a row per lane, the
-//    rest on many workgroups); k_lu_factor: the same column by column in one workgroup for
+//  - k_lu_panel / k_lu_step: dense LU with partial pivoting, blocked in panels of 16 columns for
+//    n <= 1024 (a panel in one workgroup with a row per lane, the update of the other columns in
+//    strips on many workgroups beside the next panel); k_lu_factor: the same column by column in one workgroup for
 //    larger n; k_lu_solve_blocked / k_lu_solve: the two triangular solves in one workgroup (in
 //    blocks of 64 rows for n <= 1024).  Pivot = largest |entry|
 //    of the column, the first such row on ties.
@@ -174,16 +174,14 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_factor(int64_t n, double* A, 
 }
 
 // ---- blocked LU for n <= kLuThreads: panels of kPanel columns.  Each panel is factored in one
-// workgroup with its rows in registers (one row per lane); the row exchanges are then applied
-// to the other columns, the panel's block row of U is solved, and the trailing matrix takes the
-// panel's rank-kPanel update on many workgroups.  Every entry receives the same operations in
-// the same order as in the unblocked factorisation above (a_rc -= l_rk u_kc for k = 0, 1, ...,
-// a_rk /= u_kk), and the pivots are chosen the same way, so the factors agree with the
-// unblocked ones up to how each update is contracted into an FMA.
+// workgroup with its rows in registers (one row per lane); the other columns take its row
+// exchanges, and those right of it their part of its block row of U and its rank-kPanel update.
+// Every entry receives the same operations in the same order as in the unblocked factorisation
+// above (a_rc -= l_rk u_kc for k = 0, 1, ..., a_rk /= u_kk), and the pivots are chosen the same
+// way, so the factors agree with the unblocked ones up to how each update is contracted into an
+// FMA.
 constexpr int kPanel = 16;
 
-// Panel [j0, j0 + nb): rows [j0, n), row j0 + t in lane t (the workgroup has as many
-// wavefronts as the rows need).
 // Unsigned maximum over lanes 0 .. 16 * kRows - 1 of a full wavefront, returned in every lane:
 // row shifts by 1, 2, 4 and 8 leave each 16-lane row's maximum in its last lane; for a whole
 // wavefront the two row broadcasts then carry row 0 into row 1, row 2 into row 3 and lane 31
@@ -204,165 +202,214 @@ __device__ __forceinline__ uint32_t lanes_umax(uint32_t k) {
 }
 
 // The first lane (lowest lane index) holding the largest 64-bit key among lanes 0 .. 16 * kRows
-// - 1 (lanes beyond hold 0): maximum of the high words, then of the low words among the lanes
-// that hold the high maximum, then a ballot.  Returns the lane and the maximum.
+// - 1 (lanes beyond hold 0): maximum of the high words, and where several lanes hold it, of the
+// low words among those, then a ballot.  Returns the lane and the maximum.
 template <int kRows>
 __device__ __forceinline__ int first_umax(uint64_t key, uint64_t& kmax) {
     const uint32_t hi = uint32_t(key >> 32), lo = uint32_t(key);
     const uint32_t hmax = lanes_umax<kRows>(hi);
-    const uint32_t lmax = lanes_umax<kRows>(hi == hmax ? lo : 0u);
-    kmax = (uint64_t(hmax) << 32) | lmax;
-    return __ffsll((unsigned long long)__ballot(hi == hmax && lo == lmax)) - 1;
+    unsigned long long at = __ballot(hi == hmax);
+    if (at & (at - 1)) {  // uniform
+        const uint32_t lmax = lanes_umax<kRows>(hi == hmax ? lo : 0u);
+        at = __ballot(hi == hmax && lo == lmax);
+    }
+    const int lead = __ffsll(at) - 1;
+    kmax = (uint64_t(hmax) << 32) | uint32_t(__builtin_amdgcn_readlane(int(lo), lead));
+    return lead;
 }
 
-// One panel of kPanel columns in one workgroup, a row per lane held in registers (rows j0 ..
-// n-1; the launch has whole wavefronts).  Pivot search on the key bits(|a|) + 1 (0 for rows
-// above the diagonal or past n): for non-negative doubles the bit patterns order as the
-// values, so the largest key is the largest magnitude, and the first lane holding it is the
-// first row on ties.  Each wavefront posts its candidate row (key, row index and the row's
-// kPanel entries) and lane cc posts row cc, in buffers alternating by column; one barrier, then
-// every wavefront reduces the posted keys the same way (the first wavefront on ties) and reads
-// the pivot row.  A buffer written at column cc is next written at column cc + 2, after the
-// barrier of column cc + 1 that every lane reaches only when done reading it.  A column without
-// a nonzero pivot has every candidate at key 1, so its pivot is row cc itself and nothing moves.
-__global__ __launch_bounds__(kLuThreads) void k_lu_panel(int64_t n, double* A, int64_t lda, int64_t j0, int nb,
-                                                         int32_t* ipiv, int32_t* info) {
-    constexpr int kWaves = kLuThreads / 64;
+struct PanelShared {
+    static constexpr int kWaves = kLuThreads / 64;
+    double row[2][kWaves + 1][kPanel];  // [buffer][wavefront candidates, then the diagonal row][entry]
+    uint64_t key[2][kWaves];
+    int idx[2][kWaves];
+};
+
+// Factors one panel of nb <= kPanel columns in one workgroup, a row per lane held in registers:
+// lane t0 + i has row j0 + i of the panel (lanes before t0 have none; the launch has whole
+// wavefronts).  Pivot search on the key bits(|a|) + 1 (0 for rows above the diagonal or past n):
+// for non-negative doubles the bit patterns order as the values, so the largest key is the
+// largest magnitude, and the first lane holding it is the first row on ties.  Each wavefront
+// posts its candidate row (key, lane and the row's kPanel entries) and the diagonal's lane posts
+// its row, in buffers alternating by column; one barrier, then every wavefront reduces the posted
+// keys the same way (the first wavefront on ties) and reads the pivot row.  A buffer written at
+// column cc is next written at column cc + 2, after the barrier of column cc + 1 that every lane
+// reaches only when done reading it.  A column without a nonzero pivot has every candidate at key
+// 1, so its pivot is the diagonal row itself and nothing moves.
+// The rows are rotated by one entry per column, so that the current column is always entry 0 and
+// one body serves every column.  Bound by a column's dependency chain (two reductions, an exchange
+// through LDS, a division), about 1 us with one wavefront or sixteen.
+__device__ __forceinline__ void lu_factor_rows(double (&p)[kPanel], int64_t n, int64_t j0, int nb, int t0,
+                                               PanelShared& sh, int32_t* ipiv, int32_t* info) {
+    constexpr int kWaves = PanelShared::kWaves;
     static_assert(kWaves <= 16, "the posted keys are reduced within one 16-lane row");
-    __shared__ double srow[2][kPanel][kWaves + 1];  // [buffer][column][wavefront candidates, then row cc]
-    __shared__ uint64_t skey[2][kWaves];
-    __shared__ int sidx[2][kWaves];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, nw = int(blockDim.x) >> 6;
-    const int64_t r = j0 + t;
-    const bool has = r < n;
-    int32_t piv = 0;          // lane cc: the pivot row of column j0 + cc
+    const int i = t - t0;  // row of the panel
+    const bool has = i >= 0 && j0 + i < n;
+    int32_t piv = 0;          // row cc's lane: the pivot row of column j0 + cc
     int first_singular = -1;  // uniform
-    double p[kPanel];
+#pragma unroll 1
+    for (int cc = 0; cc < nb; ++cc) {
+        const int b = cc & 1;
+        const uint64_t key = (has && i >= cc) ? uint64_t(__double_as_longlong(fabs(p[0]))) + 1 : 0;
+        uint64_t wmax;
+        const int lead = first_umax<4>(key, wmax);
+        if (lane == lead) {
+            sh.key[b][w] = wmax;
+            sh.idx[b][w] = i;
 #pragma unroll
-    for (int j = 0; j < kPanel; ++j) p[j] = (has && j < nb) ? A[r * lda + j0 + j] : 0.0;
-#pragma unroll
-    for (int cc = 0; cc < kPanel; ++cc) {
-        if (cc < nb) {  // uniform
-            const int b = cc & 1;
-            const uint64_t key = (has && t >= cc) ? uint64_t(__double_as_longlong(fabs(p[cc]))) + 1 : 0;
-            uint64_t wmax;
-            const int lead = first_umax<4>(key, wmax);
-            if (lane == lead) {
-                skey[b][w] = wmax;
-                sidx[b][w] = t;
-#pragma unroll
-                for (int j = 0; j < kPanel; ++j) srow[b][j][w] = p[j];
-            }
-            if (t == cc) {
-#pragma unroll
-                for (int j = 0; j < kPanel; ++j) srow[b][j][kWaves] = p[j];
-            }
-            __syncthreads();
-            uint64_t gmax;
-            const int ww = first_umax<1>(lane < nw ? skey[b][lane] : 0, gmax);
-            const int idx = sidx[b][ww];
-            const bool singular = gmax == 1;
-            if (t == cc) piv = int32_t(j0 + idx);
-            if (singular && first_singular < 0) first_singular = cc;
-            // rows cc and idx trade places
-            if (idx != cc && (t == cc || t == idx)) {
-                const int from = t == cc ? ww : kWaves;
-#pragma unroll
-                for (int j = 0; j < kPanel; ++j) p[j] = srow[b][j][from];
-            }
-            if (has && t > cc && !singular) {
-                p[cc] /= srow[b][cc][ww];
-#pragma unroll
-                for (int j = cc + 1; j < kPanel; ++j)
-                    if (j < nb) p[j] -= p[cc] * srow[b][j][ww];
-            }
+            for (int j = 0; j < kPanel; ++j) sh.row[b][w][j] = p[j];
         }
-    }
-    if (has) {
+        if (i == cc) {
 #pragma unroll
-        for (int j = 0; j < kPanel; ++j)
-            if (j < nb) A[r * lda + j0 + j] = p[j];
+            for (int j = 0; j < kPanel; ++j) sh.row[b][kWaves][j] = p[j];
+        }
+        __syncthreads();
+        uint64_t gmax;
+        const int ww = first_umax<1>(lane < nw ? sh.key[b][lane] : 0, gmax);
+        const int idx = sh.idx[b][ww];
+        double u[kPanel];  // the pivot row
+#pragma unroll
+        for (int j = 0; j < kPanel; ++j) u[j] = sh.row[b][ww][j];
+        const bool singular = gmax == 1;
+        if (i == cc) piv = int32_t(j0 + idx);
+        if (singular && first_singular < 0) first_singular = cc;
+        // rows cc and idx trade places
+        if (idx != cc && (i == cc || i == idx)) {
+            const int from = i == cc ? ww : kWaves;
+#pragma unroll
+            for (int j = 0; j < kPanel; ++j) p[j] = sh.row[b][from][j];
+        }
+        const bool below = has && i > cc && !singular;
+        const double l = p[0] / u[0];
+        const int live = nb - cc;  // entries 1 ... live - 1 are the columns still to come
+        const double first = below ? l : p[0];
+#pragma unroll
+        for (int j = 1; j < kPanel; ++j) {
+            const double x = p[j] - l * u[j];
+            p[j - 1] = (below && j < live) ? x : p[j];
+        }
+        p[kPanel - 1] = first;
+    }
+    // a short panel: the remaining rotations
+#pragma unroll 1
+    for (int cc = nb; cc < kPanel; ++cc) {
+        const double first = p[0];
+#pragma unroll
+        for (int j = 1; j < kPanel; ++j) p[j - 1] = p[j];
+        p[kPanel - 1] = first;
     }
     // The pivots and the status are written once at the end: a global store pending at a
     // barrier holds every wavefront there until the store completes.
-    if (t < nb) ipiv[j0 + t] = piv;
-    if (t == 0) {
+    if (i >= 0 && i < nb) ipiv[j0 + i] = piv;
+    if (i == 0) {
         if (j0 == 0) *info = 0;
         if (first_singular >= 0 && *info == 0) *info = int32_t(j0 + first_singular + 1);  // the first such column
     }
 }
 
-// One lane per column outside the panel: the panel's row exchanges, in order, and for the
-// columns right of the panel the block row of U by forward substitution with the panel's unit
-// lower block (staged in LDS).
-__global__ __launch_bounds__(256) void k_lu_swap_trsm(int64_t n, double* A, int64_t lda, int64_t j0, int nb,
-                                                      const int32_t* ipiv) {
-    __shared__ double sl[kPanel][kPanel];
-    for (int e = threadIdx.x; e < nb * nb; e += 256) sl[e / nb][e % nb] = A[(j0 + e / nb) * lda + j0 + e % nb];
-    __syncthreads();
-    const int64_t c = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (c >= n || (c >= j0 && c < j0 + nb)) return;
-    for (int cc = 0; cc < nb; ++cc) {
-        const int64_t k = j0 + cc, q = ipiv[k];
-        if (q != k) {
-            const double x = A[k * lda + c];
-            A[k * lda + c] = A[q * lda + c];
-            A[q * lda + c] = x;
-        }
+// The first panel.
+__global__ __launch_bounds__(kLuThreads) void k_lu_panel(int64_t n, double* A, int64_t lda, int nb, int32_t* ipiv,
+                                                         int32_t* info) {
+    __shared__ PanelShared sh;
+    const int64_t r = threadIdx.x;
+    double p[kPanel];
+#pragma unroll
+    for (int j = 0; j < kPanel; ++j) p[j] = (r < n && j < nb) ? A[r * lda + j] : 0.0;
+    lu_factor_rows(p, n, 0, nb, 0, sh, ipiv, info);
+    if (r < n) {
+#pragma unroll
+        for (int j = 0; j < kPanel; ++j)
+            if (j < nb) A[r * lda + j] = p[j];
     }
-    if (c < j0) return;
-    double x[kPanel];
-#pragma unroll
-    for (int i = 0; i < kPanel; ++i) x[i] = i < nb ? A[(j0 + i) * lda + c] : 0.0;
-#pragma unroll
-    for (int i = 1; i < kPanel; ++i) {
-        if (i < nb) {
-#pragma unroll
-            for (int k = 0; k < i; ++k) x[i] -= sl[i][k] * x[k];
-        }
-    }
-#pragma unroll
-    for (int i = 1; i < kPanel; ++i)
-        if (i < nb) A[(j0 + i) * lda + c] = x[i];
 }
 
-// Trailing update a_rc -= sum_k l_rk u_kc (k over the panel, in order), r, c >= j0 + nb:
-// 64 x 64 tiles, 4 x 4 entries per lane, the panel's L and U parts staged in LDS.
-__global__ __launch_bounds__(256) void k_lu_gemm(int64_t n, double* A, int64_t lda, int64_t j0, int nb) {
-    __shared__ double sL[64][kPanel + 1];
-    __shared__ double sU[kPanel][64];
-    const int64_t b0 = j0 + nb;
-    const int64_t r0 = b0 + int64_t(blockIdx.y) * 64, c0 = b0 + int64_t(blockIdx.x) * 64;
-    for (int e = threadIdx.x; e < 64 * kPanel; e += 256) {
-        const int i = e / kPanel, k = e % kPanel;
-        const int64_t r = r0 + i;
-        sL[i][k] = (r < n && k < nb) ? A[r * lda + j0 + k] : 0.0;
-        const int kk = e / 64, j = e % 64;
-        const int64_t c = c0 + j;
-        sU[kk][j] = (c < n && kk < nb) ? A[(j0 + kk) * lda + c] : 0.0;
+// One step after the panel at j0 (kPanel columns, or the last ones) has been factored: a
+// workgroup per strip of kPanel other columns, row j0 + t in lane t.  Every strip takes the
+// panel's row exchanges (each lane loads the row that they leave at its place); the strips right of
+// the panel solve for their part of the block row of U and take the panel's rank-kPanel update;
+// workgroup 0 has the strip right after the panel and goes on to factor it as the next panel, beside
+// the others' updates.  So a step is one launch whose length is the panel's (see
+// lu_factor_rows), where a launch each for the panel, the exchanges and the update took their sum:
+// 39 us per step of the 512-panel blade, now 26; the whole update, factorisation and solve
+// 1429 -> 1029 us (1024 panels 3480 -> 2770).
+__global__ __launch_bounds__(kLuThreads) void k_lu_step(int64_t n, double* A, int64_t lda, int64_t j0, int nb,
+                                                        int32_t* ipiv, int32_t* info) {
+    __shared__ PanelShared sh;
+    __shared__ double sl[kPanel][kPanel];  // the panel's unit lower block
+    __shared__ double su[kPanel][kPanel];  // the strip's rows of U
+    const int64_t j1 = j0 + nb;
+    const int64_t right = (n - j1 + kPanel - 1) / kPanel;  // strips right of the panel
+    const bool left = int64_t(blockIdx.x) >= right;
+    const int64_t c0 = left ? (int64_t(blockIdx.x) - right) * kPanel : j1 + int64_t(blockIdx.x) * kPanel;
+    const int64_t end = left ? j0 : n;
+    const int wd = int(end - c0 < kPanel ? end - c0 : kPanel);
+    const int t = threadIdx.x;
+    const int64_t r = j0 + t;
+    const bool has = r < n;
+    // the row that the exchanges (j0 + cc, ipiv[j0 + cc]), cc = 0, 1, ..., leave at row r
+    int64_t src = r;
+    for (int cc = nb - 1; cc >= 0; --cc) {
+        const int64_t k = j0 + cc, q = ipiv[k];
+        src = src == k ? q : (src == q ? k : src);
+    }
+    double p[kPanel], l[kPanel];
+#pragma unroll
+    for (int j = 0; j < kPanel; ++j) p[j] = (has && j < wd) ? A[src * lda + c0 + j] : 0.0;
+    if (left) {
+        __syncthreads();  // every row is read before any is written
+        if (has && src != r) {
+#pragma unroll
+            for (int j = 0; j < kPanel; ++j)
+                if (j < wd) A[r * lda + c0 + j] = p[j];
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < kPanel; ++k) l[k] = (has && k < nb) ? A[r * lda + j0 + k] : 0.0;
+    if (t < kPanel) {
+#pragma unroll
+        for (int j = 0; j < kPanel; ++j) {
+            su[t][j] = t < nb ? p[j] : 0.0;
+            sl[t][j] = t < nb ? l[j] : 0.0;
+        }
     }
     __syncthreads();
-    const int ty = threadIdx.x / 16, tx = threadIdx.x % 16;
-    double acc[4][4];
-    bool ok[4][4];
+    if (t < kPanel) {  // column t of the strip: forward substitution with the unit lower block
+        double x[kPanel];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+        for (int i = 0; i < kPanel; ++i) x[i] = su[i][t];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int64_t r = r0 + ty + 16 * a, c = c0 + tx + 16 * b;
-            ok[a][b] = r < n && c < n;
-            acc[a][b] = ok[a][b] ? A[r * lda + c] : 0.0;
+        for (int k = 0; k < kPanel; ++k)
+#pragma unroll
+            for (int i = k + 1; i < kPanel; ++i) x[i] -= sl[i][k] * x[k];
+#pragma unroll
+        for (int i = 0; i < kPanel; ++i) su[i][t] = x[i];
+    }
+    __syncthreads();
+    if (t < nb) {
+#pragma unroll
+        for (int j = 0; j < kPanel; ++j) p[j] = su[t][j];
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPanel; ++k)
+#pragma unroll
+            for (int j = 0; j < kPanel; ++j) p[j] -= l[k] * su[k][j];
+    }
+    if (blockIdx.x == 0) {
+        if (t < nb) {
+#pragma unroll
+            for (int j = 0; j < kPanel; ++j)
+                if (j < wd) A[r * lda + c0 + j] = p[j];
         }
-    for (int k = 0; k < nb; ++k)
+        lu_factor_rows(p, n, j1, wd, nb, sh, ipiv, info);
+        if (t < nb) return;
+    }
+    if (has) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) acc[a][b] -= sL[ty + 16 * a][k] * sU[k][tx + 16 * b];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            if (ok[a][b]) A[(r0 + ty + 16 * a) * lda + c0 + tx + 16 * b] = acc[a][b];
+        for (int j = 0; j < kPanel; ++j)
+            if (j < wd) A[r * lda + c0 + j] = p[j];
+    }
 }
 
 __global__ __launch_bounds__(kLuThreads) void k_lu_solve(int64_t n, const double* LU, int64_t lda,
@@ -410,60 +457,103 @@ __device__ __forceinline__ double lane_value(double v, int k) {
 // sb[r] -= sum_k LU[r][kb + k] sb[kb + k] (k < nbk <= 64) for rows r0 <= r < r1: eight lanes
 // per row, lane s taking the columns s, s + 8, ..., so that one load instruction of a wavefront
 // reads eight rows' consecutive 64-byte runs; the eight partial sums are added by a butterfly.
-__device__ __forceinline__ void lu_solve_rows(const double* LU, int64_t lda, double* sb, int64_t kb, int nbk,
-                                              int64_t r0, int64_t r1) {
-    const int g = threadIdx.x >> 3, sub = threadIdx.x & 7;
-    for (int64_t rb = r0; rb < r1; rb += kLuThreads / 8) {
-        const int64_t r = rb + g;  // uniform per eight lanes; the shuffles below run on all lanes
-        double v = 0.0;
-        if (r < r1) {
-            const double* row = LU + r * lda + kb;
+// The matrix entries do not depend on sb: the first kAhead passes' are loaded before the diagonal
+// block is solved (load) and used after it (apply).
+struct SolveRows {
+    static constexpr int kAhead = 3;
+    double a[kAhead][8];
+    __device__ __forceinline__ void load_row(double (&v)[8], const double* LU, int64_t lda, int64_t kb, int nbk,
+                                             int64_t r, int64_t r1) {
+        const int sub = threadIdx.x & 7;
+        const double* row = LU + r * lda + kb;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int k = sub + 8 * i;
-                if (k < nbk) v += row[k] * sb[kb + k];
-            }
-        }
-        v += __shfl_xor(v, 1, 64);
-        v += __shfl_xor(v, 2, 64);
-        v += __shfl_xor(v, 4, 64);
-        if (r < r1 && sub == 0) sb[r] -= v;
+        for (int i = 0; i < 8; ++i) v[i] = (r < r1 && sub + 8 * i < nbk) ? row[sub + 8 * i] : 0.0;
     }
-}
+    __device__ __forceinline__ void load(const double* LU, int64_t lda, int64_t kb, int nbk, int64_t r0, int64_t r1) {
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q)
+            load_row(a[q], LU, lda, kb, nbk, r0 + q * (kLuThreads / 8) + (threadIdx.x >> 3), r1);
+    }
+    __device__ __forceinline__ void add(const double (&v)[8], double* sb, const double (&x)[8], int64_t r,
+                                        int64_t r1) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += v[i] * x[i];
+        s += __shfl_xor(s, 1, 64);  // (on all lanes)
+        s += __shfl_xor(s, 2, 64);
+        s += __shfl_xor(s, 4, 64);
+        if (r < r1 && (threadIdx.x & 7) == 0) sb[r] -= s;
+    }
+    __device__ __forceinline__ void apply(const double* LU, int64_t lda, double* sb, int64_t kb, int nbk, int64_t r0,
+                                          int64_t r1) {
+        const int g = threadIdx.x >> 3, sub = threadIdx.x & 7;
+        double x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = sub + 8 * i < nbk ? sb[kb + sub + 8 * i] : 0.0;
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const int64_t rb = r0 + q * (kLuThreads / 8);
+            if (rb < r1) add(a[q], sb, x, rb + g, r1);  // uniform
+        }
+        for (int64_t rb = r0 + kAhead * (kLuThreads / 8); rb < r1; rb += kLuThreads / 8) {
+            double v[8];
+            load_row(v, LU, lda, kb, nbk, rb + g, r1);
+            add(v, sb, x, rb + g, r1);
+        }
+    }
+};
 
+// Bound by the serial chains of the diagonal blocks and the latency of the loads between them:
+// 194 us at n = 512 with the exchanges followed by one lane and the rows' loads after the diagonal
+// block, now 155.
 __global__ __launch_bounds__(kLuThreads) void k_lu_solve_blocked(int64_t n, const double* LU, int64_t lda,
                                                                  const int32_t* ipiv, double* b) {
     __shared__ double sb[kLuThreads];
     __shared__ double sd[64][65];
+    __shared__ int32_t sp[kLuThreads];
     const int t = threadIdx.x, lane = t & 63;
-    if (t < n) sb[t] = b[t];
+    SolveRows rows;
+    if (t < n) {
+        sb[t] = b[t];
+        // (an index outside the matrix exchanges nothing)
+        const int32_t q = ipiv[t];
+        sp[t] = q >= 0 && q < n ? q : t;
+    }
     __syncthreads();
-    if (t == 0)
-        for (int64_t k = 0; k < n; ++k) {
-            const int64_t p = ipiv[k];
-            if (p != k && p >= 0 && p < n) {
-                const double x = sb[k];
-                sb[k] = sb[p];
-                sb[p] = x;
-            }
+    // P b: the entry that the exchanges (k, ipiv[k]), k = 0, 1, ..., leave at position t, found by
+    // following them backwards
+    double pb = 0.0;
+    if (t < n) {
+        int at = t;
+        for (int k = int(n) - 1; k >= 0; --k) {
+            const int q = sp[k];
+            at = at == k ? q : (at == q ? k : at);
         }
+        pb = sb[at];
+    }
+    __syncthreads();
+    if (t < n) sb[t] = pb;
     __syncthreads();
     // L y = P b, unit diagonal, in blocks of 64 rows: one wavefront solves the diagonal block
     // (the solved entry broadcast from its lane), then all lanes update the rows below.
     for (int64_t kb = 0; kb < n; kb += 64) {
         const int nbk = int(n - kb < 64 ? n - kb : 64);
         for (int e = t; e < nbk * nbk; e += kLuThreads) sd[e / nbk][e % nbk] = LU[(kb + e / nbk) * lda + kb + e % nbk];
+        rows.load(LU, lda, kb, nbk, kb + nbk, n);
         __syncthreads();
         if (t < 64) {
             double y = lane < nbk ? sb[kb + lane] : 0.0;
+            double m = sd[lane][0];
             for (int k = 0; k < nbk; ++k) {
+                const double mk = m;
+                m = sd[lane][k + 1];  // the next column's entry, ahead of its use (column 64 is padding)
                 const double yk = lane_value(y, k);
-                if (lane > k && lane < nbk) y -= sd[lane][k] * yk;
+                if (lane > k && lane < nbk) y -= mk * yk;
             }
             if (lane < nbk) sb[kb + lane] = y;
         }
         __syncthreads();
-        lu_solve_rows(LU, lda, sb, kb, nbk, kb + nbk, n);
+        rows.apply(LU, lda, sb, kb, nbk, kb + nbk, n);
         __syncthreads();
     }
     // U x = y, the blocks from the last: the diagonal block, then the rows above
@@ -472,18 +562,24 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_solve_blocked(int64_t n, cons
         const int64_t kb = bi * 64;
         const int nbk = int(n - kb < 64 ? n - kb : 64);
         for (int e = t; e < nbk * nbk; e += kLuThreads) sd[e / nbk][e % nbk] = LU[(kb + e / nbk) * lda + kb + e % nbk];
+        rows.load(LU, lda, kb, nbk, 0, kb);
         __syncthreads();
         if (t < 64) {
             double y = lane < nbk ? sb[kb + lane] : 0.0;
+            double m = sd[lane][nbk - 1], d = sd[nbk - 1][nbk - 1];
             for (int k = nbk - 1; k >= 0; --k) {
-                if (lane == k) y /= sd[k][k];
-                const double xk = lane_value(y, k);
-                if (lane < k) y -= sd[lane][k] * xk;
+                const double mk = m, dk = d;
+                const int kn = k > 0 ? k - 1 : 0;
+                m = sd[lane][kn];
+                d = sd[kn][kn];
+                const double xk = lane_value(y, k) / dk;  // uniform
+                if (lane == k) y = xk;
+                if (lane < k) y -= mk * xk;
             }
             if (lane < nbk) sb[kb + lane] = y;
         }
         __syncthreads();
-        lu_solve_rows(LU, lda, sb, kb, nbk, 0, kb);
+        rows.apply(LU, lda, sb, kb, nbk, 0, kb);
         __syncthreads();
     }
     if (t < n) b[t] = sb[t];
@@ -678,22 +774,15 @@ hipError_t launch_lu_factor(int64_t n, double* A, int64_t lda, int32_t* ipiv, in
         return hipGetLastError();
     }
     hipError_t e;
+    auto lanes = [](int64_t rows) { return dim3(unsigned((rows + 63) / 64 * 64)); };
+    hipLaunchKernelGGL(k_lu_panel, dim3(1), lanes(n), 0, st, n, A, lda, int(n < kPanel ? n : kPanel), ipiv, info);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     for (int64_t j0 = 0; j0 < n; j0 += kPanel) {
         const int nb = int(n - j0 < kPanel ? n - j0 : kPanel);
-        const unsigned lanes = unsigned((n - j0 + 63) / 64 * 64);
-        hipLaunchKernelGGL(k_lu_panel, dim3(1), dim3(lanes), 0, st, n, A, lda, j0, nb, ipiv, info);
+        const unsigned strips = unsigned(j0 / kPanel + (n - j0 - nb + kPanel - 1) / kPanel);
+        if (strips == 0) break;
+        hipLaunchKernelGGL(k_lu_step, dim3(strips), lanes(n - j0), 0, st, n, A, lda, j0, nb, ipiv, info);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (n > nb) {
-            hipLaunchKernelGGL(k_lu_swap_trsm, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, n, A, lda, j0, nb,
-                               ipiv);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        const int64_t m = n - j0 - nb;
-        if (m > 0) {
-            const unsigned tiles = unsigned((m + 63) / 64);
-            hipLaunchKernelGGL(k_lu_gemm, dim3(tiles, tiles), dim3(256), 0, st, n, A, lda, j0, nb);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
     }
     return hipSuccess;
 }

@@ -216,3 +216,26 @@ def test_wake_convert_capacity_and_empty(gpu):
     _, _, _, c0 = vpm.vpm_wake_convert(_d64(np.zeros((3, 0))), _d64(np.zeros((3, 0))), _d64(np.zeros(0)),
                                        torch.zeros(0, dtype=torch.int32, device="cuda"), 2, 0.01, 0)
     assert int(c0.item()) == 0
+
+
+# one panel alone, one row or column past a panel, a strip and a wavefront, the largest blocked size
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 64, 65, 1023])
+def test_lu_at_panel_and_strip_edges(n, gpu):
+    rng = np.random.default_rng([47, n])
+    M = rng.normal(size=(n, n))
+    b = rng.normal(size=n)
+    say(f"lu edges n={n}")
+    Ad = _d64(M)
+    ipiv, info = vpm.vpm_lu_factor(Ad)
+    x = host(vpm.vpm_lu_solve(Ad, ipiv, _d64(b)))
+    F, q = host(Ad), host(ipiv).astype(np.int64)
+    assert int(info.item()) == 0
+    PM = M.copy()
+    for k in range(n):
+        PM[[k, q[k]]] = PM[[q[k], k]]
+    L, U = np.tril(F, -1) + np.eye(n), np.triu(F)
+    # backward error of an LU with |l| <= 1: n eps |L||U| entrywise
+    eps = np.finfo(np.float64).eps
+    assert np.abs(L).max() <= 1.0
+    assert np.all(np.abs(L @ U - PM) <= 2 * n * eps * (np.abs(L) @ np.abs(U)))
+    assert np.linalg.norm(M @ x - b) <= 4 * n * eps * np.linalg.norm(np.abs(L) @ np.abs(U)) * np.linalg.norm(x)
