@@ -531,12 +531,62 @@ template <typename T, int MODE, bool SYM, bool CHECK, bool NEAR>
 __device__ __forceinline__ void slice_tile(const typename SrcTile<T>::V4 (*lsrc)[256], const T* ls, int first, int step,
                                            int cnt, int64_t j0, const T (&xi)[3], const T (&gi)[3], T ngi1, T ngi2,
                                            T cut_i, int64_t ex, T* acc) {
-#pragma unroll 2
     for (int jj = first; jj < cnt; jj += step) {
         const typename SrcTile<T>::V4 p = lsrc[0][jj], q = lsrc[1][jj];
         pair_fwd<T, MODE, SYM, CHECK, NEAR>(p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w, ls + jj, xi[0], xi[1], xi[2],
                                             gi[0], gi[1], gi[2], ngi1, ngi2, cut_i, j0 + jj, ex, acc, acc);
     }
+}
+
+// Near tiles in FP64, where the in-core weights cost some ten far pairs and a wavefront runs them
+// for a source as soon as one lane is inside its core.  With `defer` a lane notes such sources in a
+// list of its own (list[k * 256]) and works the list off after the others, so that the wavefront
+// runs the in-core weights as often as its fullest lane has entries.  Particles without order have
+// a few lanes in a core at nearly every source and gain; along a filament the lanes are in a core
+// together or one lane is in most of them, and the lists are only extra work.  So a tile defers if
+// in the wavefront's last near tile no lane had more than kDeferShare / 8 of the sources that were
+// in the core of any lane.
+// Measured (us per call, all on the spot / this choice / all deferred): in a cube 4096 particles
+// 159 / 123 / 104, 20000 2605 / 1439 / 1650, 65536 27140 / 11310 / -; hover wakes 20000
+// 925 / 872 / 1104, 65536 7260 / 7370 / 8490.  In FP32 the in-core weights cost two far pairs
+// and lists lose in every wake (65536 hover particles 3020 on the spot, 3240 with lists for
+// sources in the core of less than 24 lanes): no choice there.
+constexpr int kDeferShare = 4;
+template <typename T, int MODE, bool SYM, bool CHECK>
+__device__ __forceinline__ void slice_near(const typename SrcTile<T>::V4 (*lsrc)[256], const T* ls, uint8_t* list,
+                                           bool& defer, int first, int step, int cnt, int64_t j0, const T (&xi)[3],
+                                           const T (&gi)[3], T ngi1, T ngi2, T cut_i, int64_t ex, T* acc) {
+    int mine = 0, any = 0;
+    int count = (cnt - first + step - 1) / step;
+    if (defer) {
+        for (int jj = first; jj < cnt; jj += step) {
+            const typename SrcTile<T>::V4 p = lsrc[0][jj], q = lsrc[1][jj];
+            const T rx = xi[0] - p.x, ryn = p.y - xi[1], rz = xi[2] - p.z;
+            const bool core = rx * rx + ryn * ryn + rz * rz < (SYM ? q.w + cut_i : q.w);
+            any += __ballot(core) != 0;
+            if (core) {
+                list[mine++ * 256] = uint8_t(jj);
+            } else {
+                pair_fwd<T, MODE, SYM, CHECK, false>(p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w, ls + jj, xi[0], xi[1],
+                                                     xi[2], gi[0], gi[1], gi[2], ngi1, ngi2, cut_i, j0 + jj, ex, acc,
+                                                     acc);
+            }
+        }
+        count = mine;
+    }
+    for (int k = 0; k < count; ++k) {
+        const int jj = defer ? list[k * 256] : first + k * step;
+        const typename SrcTile<T>::V4 p = lsrc[0][jj], q = lsrc[1][jj];
+        if (!defer) {
+            const T rx = xi[0] - p.x, ryn = p.y - xi[1], rz = xi[2] - p.z;
+            const bool core = rx * rx + ryn * ryn + rz * rz < (SYM ? q.w + cut_i : q.w);
+            any += __ballot(core) != 0;
+            mine += core;
+        }
+        pair_fwd<T, MODE, SYM, CHECK, true>(p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w, ls + jj, xi[0], xi[1], xi[2],
+                                            gi[0], gi[1], gi[2], ngi1, ngi2, cut_i, j0 + jj, ex, acc, acc);
+    }
+    defer = __ballot(mine * 8 > any * kDeferShare) == 0;
 }
 
 // Adds the per-chunk FP64 partials of every target and stores the result.  L targets per
@@ -591,9 +641,9 @@ __global__ __launch_bounds__(L * G) void k_pair_fwd_finish(FwdArgs a) {
 // The work per source tile of a wavefront is P pairs per lane, plus staging and two reductions.
 // Bound by VALU issue from about 5000 targets on, below by the latency of a tile (three barriers
 // and a load, 2 us).  Small target boxes also leave fewer tiles near: 65536 hover particles take
-// 3040 us in blocks of 64 and 3130 in blocks of 256, both with 16 chunks (FP64 7260 and 8970).
+// 3040 us in blocks of 64 and 3130 in blocks of 256, both with 16 chunks (FP64 7370 and 8970).
 // Measured (us per call, a target per lane with 256-source chunks / this form): 300 particles
-// 66 / 17, 1021 80 / 17, 2500 109 / 25, 4999 108 / 47; 4096 in a cube in FP64 282 / 159.
+// 66 / 17, 1021 80 / 17, 2500 109 / 25, 4999 108 / 47; 4096 in a cube in FP64 282 / 123.
 template <typename T, int MODE, bool SYM>
 __global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
     constexpr int WG = 256, kWaves = WG / 64;
@@ -603,6 +653,7 @@ __global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
     __shared__ V4 lsrc[2][WG];  // p and q of FwdBlock; later the other wavefronts' sums
     __shared__ T ls[WG];
     __shared__ T box[7 * kWaves];
+    __shared__ uint8_t lists[kComp ? 1 : 64][WG];  // (a slice has at most 64 sources of a tile)
     const T* __restrict__ xs = static_cast<const T*>(a.xs);
     const T* __restrict__ gs = static_cast<const T*>(a.gs);
     const T* __restrict__ ss = static_cast<const T*>(a.ss);
@@ -646,7 +697,8 @@ __global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
     T acc[kNacc], hi[kNacc], lo[kNacc];
 #pragma unroll
     for (int c = 0; c < kNacc; ++c) acc[c] = hi[c] = lo[c] = T(0);
-    int since = 0;  // sources in the FP32 sums since the last fold
+    int since = 0;       // sources in the FP32 sums since the last fold
+    bool defer = false;  // slice_near's choice
     for (int64_t j0 = s0; j0 < s1; j0 += WG) {
         const int cnt = int((s1 - j0) < WG ? (s1 - j0) : WG);
         __syncthreads();
@@ -679,11 +731,20 @@ __global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
                 d2 += gap * gap;
             }
             const bool near = d2 < (SYM ? tcut + bcut : tcut);
+            auto near_tile = [&](auto chk) {
+                if constexpr (kComp) {
+                    slice_tile<T, MODE, SYM, decltype(chk)::value, true>(lsrc, ls, slice, nslice, cnt, j0, xi, gi, ngi1,
+                                                                         ngi2, cut_i, ex, acc);
+                } else {
+                    slice_near<T, MODE, SYM, decltype(chk)::value>(lsrc, ls, &lists[0][tid], defer, slice, nslice, cnt,
+                                                                   j0, xi, gi, ngi1, ngi2, cut_i, ex, acc);
+                }
+            };
             if (check) {
-                if (near) slice_tile<T, MODE, SYM, true, true>(lsrc, ls, slice, nslice, cnt, j0, xi, gi, ngi1, ngi2, cut_i, ex, acc);
+                if (near) near_tile(std::integral_constant<bool, true>());
                 else slice_tile<T, MODE, SYM, true, false>(lsrc, ls, slice, nslice, cnt, j0, xi, gi, ngi1, ngi2, cut_i, ex, acc);
             } else {
-                if (near) slice_tile<T, MODE, SYM, false, true>(lsrc, ls, slice, nslice, cnt, j0, xi, gi, ngi1, ngi2, cut_i, ex, acc);
+                if (near) near_tile(std::integral_constant<bool, false>());
                 else slice_tile<T, MODE, SYM, false, false>(lsrc, ls, slice, nslice, cnt, j0, xi, gi, ngi1, ngi2, cut_i, ex, acc);
             }
             since += np;  // WG / nslice

@@ -293,6 +293,38 @@ def test_sliced_and_chunked_targets(kind, mode, ns, nt, gpu):
     assert d is None or rel_l2(host(d), do) <= TOL[kind]
 
 
+@pytest.mark.parametrize("mode", ["velocity", "transposed", "classical", "gradient"])
+@pytest.mark.parametrize("rule", [0, 1])
+@pytest.mark.parametrize("ns,nt", [(511, 67), (1300, 130), (2049, 3)])
+def test_in_core_sources_worked_off_after_a_tile(mode, rule, ns, nt, gpu):
+    """FP64 tiles whose in-core sources are scattered over the lanes put them off, tiles where the
+    lanes are in a core together do not, and a wavefront goes from one to the other: sources without
+    order first, then a bundle around the first targets, then without order again, ending in a
+    partial tile.  One chunk, so that every block sees all the tiles."""
+    import torch
+    rng = np.random.default_rng([41, ns, nt])
+    x, g, s = _random_set(ns, 43, spread=0.5)
+    y, gy, sy = _random_set(nt, 47, spread=0.5)
+    a, b = ns // 3, 2 * ns // 3
+    x[:, a:b] = y[:, :1] + 0.02 * s.mean() * rng.standard_normal((3, b - a))
+    s[::5] *= 4.0  # wide cores: sources inside the core of many lanes
+    ex = rng.integers(0, ns, nt)
+    y[:, ::3] = x[:, ex[::3]]
+    A = [dev_(v, "f64") for v in (x, g, s, y, gy, sy)]
+    E = torch.tensor(ex.astype(np.int32), device="cuda")
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    say(f"in-core lists {mode} rule {rule} {ns} -> {nt}")
+    sc = 1 if mode == "classical" else 0
+    uo, do = oracle.eval_pairs(x, g, s, x_tgt=y, gam_tgt=gy, sig_tgt=sy, excl=ex, scheme=sc, sigma_rule=rule)
+    if mode == "gradient":
+        u, d, _ = vpm.vpm_eval_velocity_gradient(*A, tgt_exclude=E, sigma_rule=rule, workspace=none)
+    else:
+        u, d = vpm.vpm_eval_velocity_stretching(*A, tgt_exclude=E, scheme=sc, sigma_rule=rule, workspace=none,
+                                                velocity_only=mode == "velocity")
+    assert rel_l2(host(u), uo) <= TOL["f64"]
+    assert d is None or rel_l2(host(d), do) <= TOL["f64"]
+
+
 @pytest.mark.parametrize("kind", KINDS)
 def test_permutation_invariance(kind, gpu):
     """Shuffling the particles changes every tile and the summation order; results agree to
