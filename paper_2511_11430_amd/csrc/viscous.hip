@@ -20,7 +20,7 @@
 //   1. k_tile_box + k_bbox: bounding box of the set;
 //   2. k_morton: 30-bit Morton code of each position on cubic cells of that box,
 //      key = code << 32 | index;
-//   3. bitonic sort of the keys (deterministic: the index breaks ties);
+//   3. bitonic sort of the keys, three levels a pass (deterministic: the index breaks ties);
 //   4. k_pack: one 12-value record per particle in sorted order
 //      (x, y, z, sigma^2/2 | omega = Gamma/V, V | (nu + nu_t)/2, 0, 0, 0);
 //   5. k_sub_box: bounding box and largest sigma^2/2 of every 64 records (and of every 256);
@@ -135,44 +135,96 @@ __global__ __launch_bounds__(256) void k_morton(const T* __restrict__ x, int64_t
     keys[p] = (uint64_t(code) << 32) | uint64_t(p);
 }
 
-// Bitonic sort of P (a power of two, >= 1024) keys, ascending.  Global step: pairs (i, i + j)
-// for j >= 1024; local steps: one workgroup sorts networks inside 1024 consecutive keys in LDS.
-__global__ __launch_bounds__(256) void k_bitonic_global(uint64_t* __restrict__ a, int64_t P, int64_t j, int64_t k) {
-    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= P / 2) return;
-    const int64_t i = 2 * j * (t / j) + (t % j);
-    const int64_t l = i + j;
-    const bool up = (i & k) == 0;
-    const uint64_t ai = a[i], al = a[l];
-    if ((ai > al) == up) {
-        a[i] = al;
-        a[l] = ai;
+// Bitonic sort of P (a power of two) distinct keys, ascending.  Stage s merges runs of 2^s keys by
+// the levels s - 1 ... 0; level l compares keys 2^l apart.  A pass takes three levels at once: a
+// thread holds the eight keys that these levels exchange in registers.  Levels below kSortLog run
+// inside one workgroup, on kSortTile consecutive keys, that changes its layout through LDS between
+// two passes; the levels above are launches of their own, up to three levels each.
+// Bound by latency: a launch above the tiles takes 4.7 us whether it does one level or three, and a
+// stage's tile launch 6.3 (at 131072 keys).  With one level a launch above 1024 keys and a barrier
+// for every level below, 100003 keys took 36 launches and 120 us, now 16 and 97; a million 66 and
+// 400, now 28 and 245.  Tiles of 4096 keys save three launches more and lose that in the first one
+// (66 levels on few workgroups: 23 us with 2048 keys, 35 with 4096).
+constexpr int kSortLog = 11, kSortTile = 1 << kSortLog, kSortWG = kSortTile / 8;
+
+// Index of register r of thread q when a pass's lowest level is lo.
+__device__ __forceinline__ int sort_index(int q, int lo, int r) {
+    return ((q >> lo) << (lo + 3)) + (r << lo) + (q & ((1 << lo) - 1));
+}
+
+__device__ __forceinline__ void sort_pair(uint64_t& a, uint64_t& b, bool up) {
+    const uint64_t x = a, y = b;
+    const bool swap = (x > y) == up;
+    a = swap ? y : x;
+    b = swap ? x : y;
+}
+
+// Levels [lo, lo + L) of stage s, as far as the stage has them, on the registers of a thread whose
+// first key's index has bit s equal to `down` (its bits [lo, lo + L) are zero).
+template <int L>
+__device__ __forceinline__ void sort_levels(uint64_t (&v)[1 << L], int down, int lo, int s) {
+#pragma unroll
+    for (int b = L - 1; b >= 0; --b) {
+        if (lo + b >= s) continue;
+#pragma unroll
+        for (int r = 0; r < 1 << L; ++r)
+            if (!(r >> b & 1)) sort_pair(v[r], v[r | 1 << b], down == (s < lo + L ? r >> (s - lo) & 1 : 0));
     }
 }
 
-__global__ __launch_bounds__(512) void k_bitonic_local(uint64_t* __restrict__ a, int64_t k_lo, int64_t k_hi,
-                                                       int64_t j_first) {
-    __shared__ uint64_t s[1024];
-    const int64_t base = int64_t(blockIdx.x) * 1024;
-    const int t = threadIdx.x;
-    s[t] = a[base + t];
-    s[t + 512] = a[base + t + 512];
-    for (int64_t k = k_lo; k <= k_hi; k <<= 1) {
-        for (int64_t j = (k == k_lo ? j_first : k >> 1); j > 0; j >>= 1) {
-            __syncthreads();
-            const int i = int(2 * j * (t / j) + (t % j));
-            const int l = i + int(j);
-            const bool up = ((base + i) & k) == 0;
-            const uint64_t ai = s[i], al = s[l];
-            if ((ai > al) == up) {
-                s[i] = al;
-                s[l] = ai;
+template <int L>
+__global__ __launch_bounds__(128) void k_sort_levels(uint64_t* __restrict__ a, int64_t P, int lo, int s) {
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t >= P >> L) return;
+    const int64_t i0 = ((t >> lo) << (lo + L)) + (t & ((int64_t(1) << lo) - 1));
+    uint64_t v[1 << L];
+#pragma unroll
+    for (int r = 0; r < 1 << L; ++r) v[r] = a[i0 + (int64_t(r) << lo)];
+    sort_levels<L>(v, int(i0 >> s & 1), lo, s);
+#pragma unroll
+    for (int r = 0; r < 1 << L; ++r) a[i0 + (int64_t(r) << lo)] = v[r];
+}
+
+// Stages s_lo ... s_hi, as far as their levels are below kSortLog; the stages begin with s_lo = 1 or
+// are the one stage above kSortLog.  Slots past the last key hold the largest value.
+__global__ __launch_bounds__(kSortWG) void k_sort_tile(uint64_t* __restrict__ a, int64_t P, int s_lo, int s_hi) {
+    __shared__ uint64_t keys[kSortTile + kSortTile / 8];  // (one key of padding in nine: no bank conflicts)
+    const int64_t base = int64_t(blockIdx.x) * kSortTile;
+    const int q = threadIdx.x;
+    const int tile = int(blockIdx.x);
+    int lo = s_lo == 1 ? 0 : kSortLog - 3;
+    uint64_t v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const int64_t i = base + sort_index(q, lo, r);
+        v[r] = i < P ? a[i] : ~0ull;
+    }
+    for (int s = s_lo; s <= s_hi; ++s) {
+        for (int g = (s < kSortLog ? s - 1 : kSortLog - 1) / 3 * 3; g >= 0; g -= 3) {
+            const int l = g < kSortLog - 3 ? g : kSortLog - 3;  // (level 8 twice in a row: no harm)
+            if (l != lo) {
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const int i = sort_index(q, lo, r);
+                    keys[i + (i >> 3)] = v[r];
+                }
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const int i = sort_index(q, l, r);
+                    v[r] = keys[i + (i >> 3)];
+                }
+                lo = l;
             }
+            sort_levels<3>(v, s < kSortLog ? sort_index(q, lo, 0) >> s & 1 : tile >> (s - kSortLog) & 1, lo, s);
         }
     }
-    __syncthreads();
-    a[base + t] = s[t];
-    a[base + t + 512] = s[t + 512];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const int64_t i = base + sort_index(q, 0, r);
+        if (i < P) a[i] = v[r];
+    }
 }
 
 template <typename T>
@@ -502,16 +554,23 @@ int64_t sort_len(int64_t n) {
 }
 
 hipError_t sort_keys(uint64_t* keys, int64_t P, hipStream_t st) {
-    hipLaunchKernelGGL(k_bitonic_local, dim3(unsigned(P / 1024)), dim3(512), 0, st, keys, int64_t(2), int64_t(1024),
-                       int64_t(1));
+    const unsigned tiles = unsigned((P + kSortTile - 1) / kSortTile);
+    int first = 1;
+    while (first < kSortLog && int64_t(1) << first < P) ++first;
+    hipLaunchKernelGGL(k_sort_tile, dim3(tiles), dim3(kSortWG), 0, st, keys, P, 1, first);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    for (int64_t k = 2048; k <= P; k <<= 1) {
-        for (int64_t j = k >> 1; j >= 1024; j >>= 1) {
-            hipLaunchKernelGGL(k_bitonic_global, dim3(unsigned(P / 2 / 256)), dim3(256), 0, st, keys, P, j, k);
+    for (int s = kSortLog + 1; int64_t(1) << s <= P; ++s) {
+        for (int top = s; top > kSortLog;) {
+            const int levels = top - kSortLog < 3 ? top - kSortLog : 3;
+            top -= levels;
+            const unsigned grid = unsigned(((P >> levels) + 127) / 128);
+            if (levels == 3) hipLaunchKernelGGL(k_sort_levels<3>, dim3(grid), dim3(128), 0, st, keys, P, top, s);
+            else if (levels == 2) hipLaunchKernelGGL(k_sort_levels<2>, dim3(grid), dim3(128), 0, st, keys, P, top, s);
+            else hipLaunchKernelGGL(k_sort_levels<1>, dim3(grid), dim3(128), 0, st, keys, P, top, s);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(k_bitonic_local, dim3(unsigned(P / 1024)), dim3(512), 0, st, keys, k, k, int64_t(512));
+        hipLaunchKernelGGL(k_sort_tile, dim3(tiles), dim3(kSortWG), 0, st, keys, P, s, s);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

@@ -97,6 +97,19 @@ def test_fmm_many_units_matches_oracle_fmm(kind, level, order, gpu):
         assert rel_l2(host(got), ref) <= TOL[kind]
 
 
+@pytest.mark.parametrize("kind", KINDS)
+# one tile of the sort, whole and with an empty part; one, two, three and four levels above the tile
+@pytest.mark.parametrize("n", [1023, 1025, 2048, 2049, 8191, 8193, 16385])
+def test_fmm_at_sort_sizes(kind, n, gpu):
+    x, g, s = _wake(n, kind)
+    order = np.random.default_rng([53, n]).permutation(x.shape[1])
+    x, g, s = x[:, order], g[:, order], s[order]
+    say(f"fmm sort {kind} n={n}")
+    u, d = vpm.vpm_fmm_eval(dev(x, kind), dev(g, kind), dev(s, kind), 6, 2)
+    uo, do = oracle.fmm(x, g, s, 6, 2)
+    assert rel_l2(host(u), uo) <= TOL[kind] and rel_l2(host(d), do) <= TOL[kind]
+
+
 def test_fmm_full_size_against_direct(gpu):
     """The 1,048,576-particle forward-flight wake at depth 6 (leaf width 6.5 sigma_max) and
     orders 12 and 18: the FP32C FMM against the FP64 oracle's direct sums at 512 sampled
