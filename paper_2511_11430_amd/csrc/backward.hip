@@ -22,7 +22,7 @@
 //   xbar_p += sum [(a+b) hA + tau c kA + (a'+b') hB + tau c' kB] r        (accumulator SR)
 //           + ub_p x sum gA Gamma_q                                         (A)
 //           + Gamma_p x sum (gB ub_q + hcs Gamma_q)                          (UW)
-//           + (sum hA tau) Sb_p - sum hB tau Sb_q                           (T, V)
+//           + sum tau (hA Sb_p - hB Sb_q)                                   (T)
 //   Gbar_p += (sum gA Gamma_q) x Sb_p + sum (gB (Z_q - R) + hcs v)           (A, Q)
 // Terms that are a per-particle vector times a sum over q are summed first and finished once
 // per particle, which is what keeps the pair cost near three forward pairs.  Outside every
@@ -78,25 +78,27 @@ __device__ __forceinline__ void core3(T s2, T isig, T cut, T Gf, T Hf, T Kf, T& 
     k = T(15) * Kn;
 }
 
-// Accumulator slots: 0-2 SR r, 3-5 A, 6-8 UW, 9-11 Q, and with stretching seeds 12-14 V, 15 T.
+// Accumulator slots: 0-2 SR r, 3-5 A, 6-8 UW, 9-11 Q, and with stretching seeds 12-14 T, or without
+// role B 12 sum hA tau (T is then that sum times Sb_p).
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
 struct Bwd {
     static constexpr bool kComp = std::is_same<T, float>::value;
-    static constexpr int kN = STR ? 16 : 12;
+    static constexpr int kN = STR ? (RB ? 15 : 13) : 12;
 
-    // Both roles with one set of weights (g, h, k): q1 = (Gamma_q, .), q2 = ub_q, q3 = Sb_q,
-    // q4 = Sb_q x Gamma_q (q3, q4 unused without stretching seeds).
+    // Both roles with one set of point-vortex weights, g and h = -3 g / s^2 (so k = -5 h / s^2):
+    // q1 = (Gamma_q, .), q2 = ub_q, q3 = Sb_q, q4 = Sb_q x Gamma_q (q3, q4 unused without stretching
+    // seeds).  Bound by VALU issue, so by the operations: 68 per pair, R on one chain
+    // with Z_q and one sum of tau (Sb_p - Sb_q).  With R and Z_q apart, k a weight of its own
+    // and the sums of hA tau and of hB tau Sb_q apart there were 73: 65536 hover particles 8410 us,
+    // now 8080, 200000 70.9 and 67.7 ms.
     static __device__ __forceinline__ void far_pair(const V4<T>& q1, const V4<T>& q2, const V4<T>& q3,
-                                                    const V4<T>& q4, T rx, T ry, T rz, T g, T h, T k,
+                                                    const V4<T>& q4, T rx, T ry, T rz, T rinv2, T g, T h,
                                                     const T (&gp)[3], const T (&up)[3], const T (&sp)[3],
                                                     const T (&ep)[3], T (&acc)[kN]) {
-        // v = Gamma_q x r,  R = r x ub_q
+        // v = Gamma_q x r,  R = r x ub_q (below)
         const T vx = q1.y * rz - q1.z * ry;
         const T vy = q1.z * rx - q1.x * rz;
         const T vz = q1.x * ry - q1.y * rx;
-        const T Rx = ry * q2.z - rz * q2.y;
-        const T Ry = rz * q2.x - rx * q2.z;
-        const T Rz = rx * q2.y - ry * q2.x;
         acc[3] += g * q1.x;
         acc[4] += g * q1.y;
         acc[5] += g * q1.z;
@@ -106,7 +108,9 @@ struct Bwd {
         T sr;
         if (STR) {
             // D = Z_q - R, so a' + b' = Gamma_p . D and the Q term is g D + hcc v
-            const T Dx = q4.x - Rx, Dy = q4.y - Ry, Dz = q4.z - Rz;
+            const T Dx = fma(rz, q2.y, fma(-ry, q2.z, q4.x));
+            const T Dy = fma(rx, q2.z, fma(-rz, q2.x, q4.y));
+            const T Dz = fma(ry, q2.x, fma(-rx, q2.y, q4.z));
             // s_ab = a + b + a' + b' = ub_p.v + Gamma_q.E_p + Gamma_p.D, one FMA chain
             T s_ab = up[0] * vx;
             s_ab = fma(up[1], vy, s_ab);
@@ -118,19 +122,19 @@ struct Bwd {
             s_ab = fma(gp[1], Dy, s_ab);
             s_ab = fma(gp[2], Dz, s_ab);
             // c + c' = (Sb_p - Sb_q) . r
-            T cc = (sp[0] - q3.x) * rx;
-            cc = fma(sp[1] - q3.y, ry, cc);
-            cc = fma(sp[2] - q3.z, rz, cc);
+            const T dx = sp[0] - q3.x, dy = sp[1] - q3.y, dz = sp[2] - q3.z;
+            T cc = dx * rx;
+            cc = fma(dy, ry, cc);
+            cc = fma(dz, rz, cc);
             T tau = gp[0] * vx;
             tau = fma(gp[1], vy, tau);
             tau = fma(gp[2], vz, tau);
-            sr = fma(k * tau, cc, h * s_ab);
             const T hcc = h * cc;
             const T ht = h * tau;
-            acc[15] += ht;
-            acc[12] += ht * q3.x;
-            acc[13] += ht * q3.y;
-            acc[14] += ht * q3.z;
+            sr = fma(T(-5) * rinv2, ht * cc, h * s_ab);
+            acc[12] += ht * dx;
+            acc[13] += ht * dy;
+            acc[14] += ht * dz;
             acc[6] += hcc * q1.x;
             acc[7] += hcc * q1.y;
             acc[8] += hcc * q1.z;
@@ -141,6 +145,9 @@ struct Bwd {
             acc[10] += hcc * vy;
             acc[11] += hcc * vz;
         } else {
+            const T Rx = ry * q2.z - rz * q2.y;
+            const T Ry = rz * q2.x - rx * q2.z;
+            const T Rz = rx * q2.y - ry * q2.x;
             T s_ab = up[0] * vx;
             s_ab = fma(up[1], vy, s_ab);
             s_ab = fma(up[2], vz, s_ab);
@@ -200,8 +207,8 @@ struct Bwd {
             if constexpr (!NEAR && !CHECK && RA && RB) {
                 // Outside every core both roles share (g, h, k): add the roles' terms before
                 // multiplying by the weights.
-                far_pair(q1, l2[jj], STR ? l3[jj] : q1, STR ? l4[jj] : q1, rx, ry, rz, gA, hA, kA, gp, up, sp, ep,
-                         acc);
+                far_pair(q1, l2[jj], STR ? l3[jj] : q1, STR ? l4[jj] : q1, rx, ry, rz, rinv2, gA, hA, gp, up, sp,
+                         ep, acc);
             } else {
                 pair_general(q1, jj, l2, l3, l4, rx, ry, rz, gA, hA, kA, gB, hB, kB, gp, up, sp, ep, acc);
             }
@@ -249,9 +256,16 @@ struct Bwd {
                     const T c = sp[0] * rx + sp[1] * ry + sp[2] * rz;
                     sr += b * hA + tau * c * kA;
                     hcs = hA * c;
-                    acc[15] += hA * tau;
+                    if constexpr (RB) {
+                        const T ht = hA * tau;
+                        acc[12] += ht * sp[0];
+                        acc[13] += ht * sp[1];
+                        acc[14] += ht * sp[2];
+                    } else {
+                        acc[12] += hA * tau;
+                    }
                 }
-                if (RB) {
+                if constexpr (RB) {
                     const V4<T> q3 = l3[jj];  // Sb_q
                     const V4<T> q4 = l4[jj];  // Z_q = Sb_q x Gamma_q
                     const T bp = gp[0] * q4.x + gp[1] * q4.y + gp[2] * q4.z;
@@ -259,9 +273,9 @@ struct Bwd {
                     sr += bp * hB + tau * cp * kB;
                     hcs += hB * cp;
                     const T ht = hB * tau;
-                    acc[12] += ht * q3.x;
-                    acc[13] += ht * q3.y;
-                    acc[14] += ht * q3.z;
+                    acc[12] -= ht * q3.x;
+                    acc[13] -= ht * q3.y;
+                    acc[14] -= ht * q3.z;
                     acc[9] += gB * q4.x;
                     acc[10] += gB * q4.y;
                     acc[11] += gB * q4.z;
@@ -485,7 +499,7 @@ __device__ __forceinline__ void backward_body(const BwdArgs& a, int64_t blk, int
     const double u0 = up[0], u1 = up[1], u2 = up[2];
     const double g0 = gp[0], g1 = gp[1], g2 = gp[2];
     const double s0 = sp[0], s1 = sp[1], s2 = sp[2];
-    // xbar = SR + ub_p x A + Gamma_p x UW + T Sb_p - V
+    // xbar = SR + ub_p x A + Gamma_p x UW + T
     double xb[3] = {t[0], t[1], t[2]};
     xb[0] += u1 * t[5] - u2 * t[4] + g1 * t[8] - g2 * t[7];
     xb[1] += u2 * t[3] - u0 * t[5] + g2 * t[6] - g0 * t[8];
@@ -493,9 +507,9 @@ __device__ __forceinline__ void backward_body(const BwdArgs& a, int64_t blk, int
     // Gbar = A x Sb_p + Q
     double gb[3] = {t[9], t[10], t[11]};
     if (STR) {
-        xb[0] += t[15] * s0 - t[12];
-        xb[1] += t[15] * s1 - t[13];
-        xb[2] += t[15] * s2 - t[14];
+        xb[0] += RB ? t[12] : t[12] * s0;
+        xb[1] += RB ? t[13] : t[12] * s1;
+        xb[2] += RB ? t[14] : t[12] * s2;
         gb[0] += t[4] * s2 - t[5] * s1;
         gb[1] += t[5] * s0 - t[3] * s2;
         gb[2] += t[3] * s1 - t[4] * s0;
@@ -539,7 +553,7 @@ __global__ __launch_bounds__(WG) void k_backward_f64(BwdArgs a, int lp) {
 // the same sums in a launch of its own and in a queue of many sets; blocks of 4 would take 1000
 // particles alone from 37 to 23 us but a queue of 300 sets of 64-600 from 150 to 490 us.
 // Measured (FP32, both roles, hover wake, us per call without and with the split): 1000
-// particles 393 / 37, 4999 1686 / 143, 16384 4970 / 659, 65536 17890 / 8170, 200000 83300 / 70200.
+// particles 393 / 37, 4999 1686 / 143, 16384 4970 / 659, 65536 17890 / 8080, 200000 83300 / 67700.
 constexpr int kSplitLpMin = 4, kSplitLpMax = 6, kNoSplitLp = 8;
 constexpr int64_t kSlots = 1024;
 __host__ __device__ inline int split_lp(int64_t nl) {
