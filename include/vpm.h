@@ -111,7 +111,7 @@ typedef struct vpm_options {
  *  workspace        device scratch of vpm_workspace_size(...) bytes.  Required for n_batch > 1
  *                   (work queue).  For n_batch == 1 it holds per-chunk partial sums when the
  *                   target set is too small to fill the GPU (the sources are then split into
- *                   chunks); without it (NULL or smaller) such a set runs unsplit, correct but
+ *                   chunks); a smaller one holds fewer chunks and NULL none, correct but
  *                   slower.  Must not overlap any other argument.
  * Returns VPM_OK or the first violated condition. */
 vpm_status vpm_eval_velocity_stretching(int32_t dtype, int32_t n_batch, const int64_t* src_off,
@@ -310,8 +310,9 @@ size_t vpm_fmm_workspace_size(int32_t dtype, int64_t n, int32_t level, int32_t o
  *  dgamma_bar NULL: only velocities are seeded (gamma_tgt may then be NULL).
  *  n_batch > 1: sets b = [src_off[b], src_off[b+1]) (targets by tgt_off, or the same sets
  *  with self) do not interact; one persistent launch per lane role pops (set, block) items in
- *  decreasing cost from a queue kept in the workspace, which must hold
- *  vpm_backward_workspace_size() bytes and is overwritten.  The classical scheme with
+ *  decreasing cost from a queue kept in the workspace, which should hold
+ *  vpm_backward_workspace_size() bytes and is overwritten (a smaller one takes fewer, larger
+ *  blocks, down to one per 256 particles, and is refused below that).  The classical scheme with
  *  stretching seeds runs three launches per set (its pair term is the transposed one with
  *  the target strength and its seed exchanged) and needs no workspace.
  * Gradient arrays are [3][ld_src] / [3][ld_tgt] and must not overlap inputs or the workspace.

@@ -138,9 +138,13 @@ int64_t backward_items(int32_t n_batch, const int64_t* off, int item_lp) {
     }
     return items;
 }
-int backward_item_lp(int32_t n_batch, const int64_t* off) {
+// A workspace of `room` bytes may hold fewer items than that (one sized for a larger batch of larger
+// sets does): the items then grow until they fit, 256 particles at most.  The results do not change.
+int backward_item_lp(int32_t n_batch, const int64_t* off, size_t room = SIZE_MAX) {
     int lp = kBwdItemLpMax;
-    while (lp > kBwdItemLpMin && backward_items(n_batch, off, lp) < kBwdItems) --lp;
+    while (lp > kBwdItemLpMin && backward_items(n_batch, off, lp) < kBwdItems &&
+           queue_layout_items(n_batch, backward_items(n_batch, off, lp - 1)).total <= room)
+        --lp;
     return lp;
 }
 // The larger of the two queues (source blocks, target blocks).
@@ -438,9 +442,9 @@ vpm_status classical_backward(int32_t dtype, bool sym, bool self, int64_t n_src,
 // the workspace and fills the GPU with resident workgroups.
 hipError_t backward_batched(int32_t dtype, int32_t n_batch, const int64_t* src_off, const int64_t* tgt_off,
                             bool role_a, bool role_b, bool stretch, bool sym, const vpm::BwdArgs& a,
-                            bool lane_is_tgt, void* workspace, hipStream_t st) {
+                            bool lane_is_tgt, void* workspace, size_t ws_bytes, hipStream_t st) {
     int64_t n_items = 0;
-    const int item_lp = backward_item_lp(n_batch, lane_is_tgt ? tgt_off : src_off);
+    const int item_lp = backward_item_lp(n_batch, lane_is_tgt ? tgt_off : src_off, ws_bytes);
     hipError_t e = stage_queue(n_batch, src_off, tgt_off, lane_is_tgt, item_lp, workspace, st, &n_items);
     if (e != hipSuccess || n_items == 0) return e;
     DeviceInfo di;
@@ -1052,8 +1056,9 @@ vpm_status vpm_backward(int32_t dtype, int32_t n_batch, const int64_t* src_off,
     }
     const bool classical = o.scheme == VPM_STRETCH_CLASSICAL && stretch;
     if (n_batch > 1 && !classical) {
-        const QueueLayout L = backward_queue_layout(n_batch, src_off, tgt_off);
-        if (!workspace || ws_bytes < L.total) return VPM_ERR_WORKSPACE;
+        const int64_t least = std::max(backward_items(n_batch, src_off, kBwdItemLpMax),
+                                       backward_items(n_batch, tgt_off, kBwdItemLpMax));
+        if (!workspace || ws_bytes < queue_layout_items(n_batch, least).total) return VPM_ERR_WORKSPACE;
         const Range rw = span(workspace, 1, int64_t(ws_bytes), int64_t(ws_bytes), 1);
         for (int i = 0; i < 4; ++i)
             if (overlap(rw, outs[i])) return VPM_ERR_ALIAS;
@@ -1093,7 +1098,7 @@ vpm_status vpm_backward(int32_t dtype, int32_t n_batch, const int64_t* src_off,
         a.xbar = x_src_bar; a.gbar = gamma_src_bar; a.ldg = ld_src; a.self = 1;
         if (n_batch == 1) return hip_status(vpm::launch_backward(dtype, true, true, stretch, sym, a, st));
         return hip_status(backward_batched(dtype, n_batch, src_off, tgt_off, true, true, stretch, sym, a, false,
-                                           workspace, st));
+                                           workspace, ws_bytes, st));
     }
     // Sources' gradients: lane = source (role B), loop = targets.
     a.xl = x_src; a.gl = gamma_src; a.sl = sigma_src; a.ubl = nullptr; a.sbl = nullptr;
@@ -1103,7 +1108,7 @@ vpm_status vpm_backward(int32_t dtype, int32_t n_batch, const int64_t* src_off,
     a.xbar = x_src_bar; a.gbar = gamma_src_bar; a.ldg = ld_src; a.self = 0;
     hipError_t e = n_batch == 1 ? vpm::launch_backward(dtype, false, true, stretch, sym, a, st)
                                 : backward_batched(dtype, n_batch, src_off, tgt_off, false, true, stretch, sym, a,
-                                                   false, workspace, st);
+                                                   false, workspace, ws_bytes, st);
     if (e != hipSuccess) return VPM_ERR_HIP;
     if (want_tgt) {
         // Targets' gradients: lane = target (role A), loop = sources.
@@ -1115,7 +1120,7 @@ vpm_status vpm_backward(int32_t dtype, int32_t n_batch, const int64_t* src_off,
         b.xbar = x_tgt_bar; b.gbar = gamma_tgt_bar; b.ldg = ld_tgt; b.self = 0;
         e = n_batch == 1 ? vpm::launch_backward(dtype, true, false, stretch, sym, b, st)
                          : backward_batched(dtype, n_batch, src_off, tgt_off, true, false, stretch, sym, b, true,
-                                            workspace, st);
+                                            workspace, ws_bytes, st);
         if (e != hipSuccess) return VPM_ERR_HIP;
     }
     return VPM_OK;

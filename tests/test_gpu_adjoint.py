@@ -117,6 +117,28 @@ def test_batched_vjp_equals_per_set_calls(kind, scheme, gpu):
 
 
 @pytest.mark.parametrize("kind", KINDS)
+def test_batched_vjp_in_a_smaller_queue(kind, gpu):
+    """A workspace sized for few large sets serves many small ones: the queue takes larger items, down
+    to 256 particles each, with the same bits; one item less than that is refused."""
+    import torch
+    rng = np.random.default_rng(59)
+    sizes = rng.integers(64, 600, 40)
+    off = [0] + [int(v) for v in np.cumsum(sizes)]
+    n = off[-1]
+    x, g, s, ub, sb = prepare([rng.uniform(-1, 1, (3, n)), rng.normal(size=(3, n)), rng.uniform(0.05, 0.1, n),
+                               rng.normal(size=(3, n)), rng.normal(size=(3, n))], kind)
+    A = [dev(v, kind) for v in (x, g, s, ub, sb)]
+    up = lambda b: (b + 255) // 256 * 256
+    least = 256 + 2 * up(8 * len(off)) + up(8 * int(sum((k + 255) // 256 for k in sizes)))
+    say(f"vjp queue {kind} {least}")
+    ref = vpm.vpm_backward(*A, src_off=off)
+    got = vpm.vpm_backward(*A, src_off=off, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(ref[0], got[0]) and torch.equal(ref[1], got[1])
+    with pytest.raises(vpm.VpmError):
+        vpm.vpm_backward(*A, src_off=off, workspace=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("kind", KINDS)
 # one block of a workgroup's particles and its neighbours at every block size the launch picks
 # (4, 8, 16, 32, 64 particles; 256 needs more than 150000), tile ends, a lone particle
 @pytest.mark.parametrize("n", [1, 3, 4, 5, 255, 256, 257, 2049, 5003, 9001, 16383, 20011, 50021])
