@@ -320,14 +320,18 @@ SplitPlan shape_split(int32_t dtype, int variant, int nacc, int64_t n_src, int64
 // below, slices are within 5 % either way (65536 hover particles 3040 us, 3130 with a target per
 // lane; flight 2990 and 2825) and their shorter FP32 sums hold the error down (7e-8 against 1.3e-7
 // with folds every 256 sources and 8.8e-8 every 128).  The gradient mode's 21 sums leave a slice
-// three wavefronts per SIMD, an eighth slower per pair than a target per lane.  Partial sums are held to kMaxPartials, and to `room` bytes.
+// three wavefronts per SIMD, an eighth slower per pair than a target per lane.
+// More than kPlainOnly targets fill the chip with a target per lane in either type, which has less
+// staging per pair (FP64 flight wakes, us, slices / a target per lane: 500000 338000 / 355000,
+// 1048576 1479000 / 1355000), and more than three rounds of blocks need no chunks (30000 sources on
+// a million points, FP64, 28600 / 26700).  Partial sums are held to kMaxPartials, and to `room` bytes.
 // Measured (us, shape_split / this rule): 10000 hover particles 132 / 115, 65536 3400 / 3040
 // (flight 3250 / 2990), 20000 in FP64 1297 / 923, 128 points of 262144 particles 331 / 41, 4096
 // points of 100000 281 / 232, 8000 points of a million 5050 / 3830.
 constexpr size_t kMaxPartials = size_t(128) << 20;
+constexpr int64_t kPlainFrom = 131072, kPlainOnly = 524288;
 SplitPlan auto_split(int32_t dtype, int nacc, int64_t n_src, int64_t n_tgt, size_t room) {
     constexpr int64_t kSlots = 1024, kTile = 170, kLatency = 400, kGroup = 300, kFinish = 1500;
-    constexpr int64_t kPlainFrom = 131072;
     const bool grad = nacc == vpm::nacc_of(vpm::kModeGradient);
     const int64_t pair = dtype == kDtypeF64 ? 60 : 30;
     if (room > kMaxPartials) room = kMaxPartials;
@@ -337,12 +341,15 @@ SplitPlan auto_split(int32_t dtype, int nacc, int64_t n_src, int64_t n_tgt, size
     double least = -1.0;
     for (int lp : {2, 3, 4, 5, 6, kPlainLp}) {
         if (lp == kPlainLp && dtype != kDtypeF64 && !grad && n_tgt <= kPlainFrom) continue;
+        if (lp != kPlainLp && n_tgt > kPlainOnly) continue;
         const int64_t blocks = (n_tgt + (int64_t(1) << lp) - 1) >> lp;
-        const int64_t per_pair = lp == kPlainLp ? (dtype == kDtypeF64 ? pair * 6 / 5 : pair)
-                                                : (dtype != kDtypeF64 && grad ? pair * 9 / 8 : pair);
+        int64_t per_pair = pair;
+        if (dtype == kDtypeF64) per_pair = lp == kPlainLp ? pair * 6 / 5 : pair;
+        else if (grad && lp != kPlainLp) per_pair = pair * 9 / 8;
         const int64_t tile = (per_pair << lp) + kTile;
+        const bool whole = lp == kPlainLp && blocks > 3 * kSlots;
         // 1, 2, 3, 4, 6, 8, 12, ... chunks
-        for (int64_t want = 1; want == 1 || n_src / want >= kMinChunk;
+        for (int64_t want = 1; want == 1 || (!whole && n_src / want >= kMinChunk);
              want += want == 1 || (want & (want - 1)) ? (want + 2) / 3 : want / 2) {
             const int64_t chunk = want == 1 ? n_src : ((n_src + want - 1) / want + 255) / 256 * 256;
             const int64_t nchunk = (n_src + chunk - 1) / chunk;
@@ -365,6 +372,12 @@ SplitPlan auto_split(int32_t dtype, int nacc, int64_t n_src, int64_t n_tgt, size
     }
     return best;
 }
+
+// The velocity alone, in FP32, on more points than slices are best for: the plan table's shapes and
+// their chunks.  A pair is two thirds of a stretching pair there and the shapes differ more by the
+// staging per pair than this count of instructions tells (us, this rule / the shapes: 5000 sources on
+// 200000 points 519 / 397, on 400000 958 / 789; 100000 on 200000 7850 / 8190).
+bool velocity_by_shape(int32_t dtype, int64_t n_tgt) { return dtype != kDtypeF64 && n_tgt > kPlainFrom; }
 
 // The same split with as many chunks as `bytes` of partial sums hold (none below two).
 SplitPlan fit_plan(SplitPlan p, int nacc, int64_t n_src, int64_t n_tgt, size_t bytes) {
@@ -526,7 +539,11 @@ size_t vpm_workspace_size(int32_t dtype, int32_t n_batch, const int64_t* src_off
         const int nacc = o.gradient ? vpm::nacc_of(vpm::kModeGradient) : vpm::nacc_of(vpm::kModeTransposed);
         if (o.variant > 0 && !o.gradient)
             return shape_split(dtype, o.variant - 1, nacc, src_off[1], tgt_off[1]).bytes;
-        return auto_split(dtype, nacc, src_off[1], tgt_off[1], kMaxPartials).bytes;
+        // (whether a call wants the velocity only, the options do not say)
+        const size_t bytes = auto_split(dtype, nacc, src_off[1], tgt_off[1], kMaxPartials).bytes;
+        if (o.gradient || !velocity_by_shape(dtype, tgt_off[1])) return bytes;
+        return std::max(bytes, shape_split(dtype, choose_variant(o, false, tgt_off[1]), nacc, src_off[1],
+                                           tgt_off[1]).bytes);
     }
     return queue_layout(n_batch, tgt_off, kMinTargetsPerBlock).total;
 }
@@ -645,15 +662,18 @@ vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, con
     if (n_batch == 1) {
         const size_t room = workspace ? ws_bytes : 0;
         SplitPlan sp;
-        if (o.variant > 0) {
-            sp = shape_split(dtype, variant, vpm::nacc_of(mode), n_src, n_tgt);
-            if (noalloc && sp.bytes > room) sp = fit_plan(sp, vpm::nacc_of(mode), n_src, n_tgt, room);
+        const bool by_shape = mode == vpm::kModeVelocity && velocity_by_shape(dtype, n_tgt);
+        if (o.variant > 0 || by_shape) {
+            // velocity only counts the nine sums of the stretching modes, as vpm_workspace_size does
+            const int nacc = vpm::nacc_of(by_shape ? vpm::kModeTransposed : mode);
+            sp = shape_split(dtype, variant, nacc, n_src, n_tgt);
+            if (noalloc && sp.bytes > room) sp = fit_plan(sp, nacc, n_src, n_tgt, room);
             if (sp.bytes > room) {
                 sp.nchunk = 1;
                 sp.chunk = n_src;
             }
         } else {
-            // velocity only counts the nine sums of the stretching modes, as vpm_workspace_size does
+            // (velocity only: nine sums here too)
             sp = auto_split(dtype, vpm::nacc_of(o.gradient ? vpm::kModeGradient : vpm::kModeTransposed), n_src, n_tgt,
                             room);
         }

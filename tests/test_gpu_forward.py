@@ -325,6 +325,27 @@ def test_in_core_sources_worked_off_after_a_tile(mode, rule, ns, nt, gpu):
     assert d is None or rel_l2(host(d), do) <= TOL["f64"]
 
 
+@pytest.mark.parametrize("kind,nt", [("f32c", 131072), ("f32c", 131073), ("f64", 524288), ("f64", 524289)])
+def test_many_targets_either_side_of_the_plain_kernel(kind, nt, gpu):
+    """Few sources on more targets than slices serve: velocity (with and without room for chunks) and
+    stretching at sampled targets."""
+    import torch
+    x, g, s = prepare(_random_set(2000, 61, spread=0.5), kind)
+    rng = np.random.default_rng([67, nt])
+    y, gy = prepare([rng.uniform(-0.5, 0.5, (3, nt)), rng.normal(0, 1e-3, (3, nt))], kind)
+    A = [dev_(v, kind) for v in (x, g, s)]
+    Y, GY = dev_(y, kind), dev_(gy, kind)
+    idx = np.unique(np.concatenate([[0, nt - 1], rng.integers(0, nt, 200)]))
+    say(f"many targets {kind} {nt}")
+    uo, do = oracle.eval_pairs(x, g, s, x_tgt=y[:, idx], gam_tgt=gy[:, idx])
+    u1, _ = vpm.vpm_eval_velocity_stretching(*A, Y)
+    u0, _ = vpm.vpm_eval_velocity_stretching(*A, Y, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    u2, d2 = vpm.vpm_eval_velocity_stretching(*A, Y, GY, None)
+    for u in (u0, u1, u2):
+        assert rel_l2(host(u)[:, idx], uo) <= TOL[kind]
+    assert rel_l2(host(d2)[:, idx], do) <= TOL[kind]
+
+
 @pytest.mark.parametrize("kind", KINDS)
 def test_permutation_invariance(kind, gpu):
     """Shuffling the particles changes every tile and the summation order; results agree to
