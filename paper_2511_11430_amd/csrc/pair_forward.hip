@@ -643,7 +643,7 @@ __global__ __launch_bounds__(L * G) void k_pair_fwd_finish(FwdArgs a) {
 // and a load, 2 us).  Small target boxes also leave fewer tiles near: 65536 hover particles take
 // 3040 us in blocks of 64 and 3130 in blocks of 256, both with 16 chunks (FP64 7370 and 8970).
 // Measured (us per call, a target per lane with 256-source chunks / this form): 300 particles
-// 66 / 17, 1021 80 / 17, 2500 109 / 25, 4999 108 / 47; 4096 in a cube in FP64 282 / 123.
+// 66 / 13, 1021 80 / 13, 2500 109 / 22, 4999 108 / 43; 4096 in a cube in FP64 282 / 120.
 template <typename T, int MODE, bool SYM>
 __global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
     constexpr int WG = 256, kWaves = WG / 64;
@@ -832,13 +832,15 @@ __global__ __launch_bounds__(WG) void k_pair_fwd_batched(FwdArgs a, BatchQueue b
 // ------------------------------------------------------------------ host-side launchers
 namespace {
 
-// Few targets have many chunks each and take 64 groups of lanes; many fill the chip with four.
+// Few targets have many chunks each and take 16 groups of lanes; many fill the chip with four.
+// (64 groups, workgroups of 1024 lanes: 4999 particles 47 us per call, now 43, 2500 25.6 and 22.4;
+// 128 points of 262144 particles the same, 41.)
 constexpr int64_t kFinishFew = 8192;
 template <typename T, int MODE>
 hipError_t launch_finish(const FwdArgs& a, hipStream_t st) {
     const int64_t nt = a.tgt_end - a.tgt_begin;
     if (nt <= kFinishFew)
-        hipLaunchKernelGGL((k_pair_fwd_finish<T, MODE, 16, 64>), dim3(unsigned((nt + 15) / 16)), dim3(1024), 0, st, a);
+        hipLaunchKernelGGL((k_pair_fwd_finish<T, MODE, 16, 16>), dim3(unsigned((nt + 15) / 16)), dim3(256), 0, st, a);
     else
         hipLaunchKernelGGL((k_pair_fwd_finish<T, MODE, 64, 4>), dim3(unsigned((nt + 63) / 64)), dim3(256), 0, st, a);
     return hipGetLastError();
