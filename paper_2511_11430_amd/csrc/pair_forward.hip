@@ -645,7 +645,7 @@ __global__ __launch_bounds__(L * G) void k_pair_fwd_finish(FwdArgs a) {
 // Measured (us per call, a target per lane with 256-source chunks / this form): 300 particles
 // 66 / 13, 1021 80 / 13, 2500 109 / 22, 4999 108 / 43; 4096 in a cube in FP64 282 / 120.
 template <typename T, int MODE, bool SYM>
-__global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
+__device__ __forceinline__ void slice_body(const FwdArgs& a, int64_t t0, int64_t s0, int64_t s1, int lp) {
     constexpr int WG = 256, kWaves = WG / 64;
     constexpr bool kComp = std::is_same<T, float>::value;
     constexpr int kNacc = nacc_of(MODE);
@@ -663,15 +663,9 @@ __global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
     const T far2 = T(Prec<T>::kFarRho2);
     const int tid = threadIdx.x;
     const int np = 1 << lp, slice = tid >> lp, nslice = WG >> lp;
-    const int64_t t0 = a.tgt_begin + (int64_t(blockIdx.x) << lp);
     const int64_t t = t0 + (tid & (np - 1));
     const bool valid = t < a.tgt_end;
     const int64_t tt = valid ? t : t0;
-    int64_t s0 = a.src_begin, s1 = a.src_end;
-    if (a.nchunk > 1) {
-        s0 += int64_t(blockIdx.y) * a.chunk;
-        s1 = s0 + a.chunk < s1 ? s0 + a.chunk : s1;
-    }
     const T xi[3] = {xt[tt], xt[a.ldt + tt], xt[2 * a.ldt + tt]};
     T gi[3] = {T(0), T(0), T(0)};
     if (MODE != kModeVelocity) {
@@ -802,6 +796,33 @@ __global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
     }
 }
 
+template <typename T, int MODE, bool SYM>
+__global__ __launch_bounds__(256) void k_pair_fwd_slice(FwdArgs a, int lp) {
+    int64_t s0 = a.src_begin, s1 = a.src_end;
+    if (a.nchunk > 1) {
+        s0 += int64_t(blockIdx.y) * a.chunk;
+        s1 = s0 + a.chunk < s1 ? s0 + a.chunk : s1;
+    }
+    slice_body<T, MODE, SYM>(a, a.tgt_begin + (int64_t(blockIdx.x) << lp), s0, s1, lp);
+}
+
+// Many sets in sliced blocks: workgroup i runs item i, and the items are in decreasing cost order,
+// so that the workgroups that start last are the shortest.  An item of the 256-target kernel is a
+// large share of a batch whose sets are few or uneven (50000 particles: 12 ms beside four other
+// wavefronts on a SIMD), and the last ones ran with most of the chip idle.
+// Measured (us per call, queue of 256-target blocks / this): 64 sets of 512-50000 particles 14260 /
+// 13490, 4 of 20000-60000 9350 / 6630, 64 of 256-2000 434 / 118 (FP64 2120 / 290), 300 of 64-600
+// 151 / 78, 16 of 5000-30000 in FP64 26600 / 13000.
+template <typename T, int MODE, bool SYM>
+__global__ __launch_bounds__(256) void k_pair_fwd_slice_sets(FwdArgs a, BatchQueue q, int lp) {
+    const int2 it = q.items[blockIdx.x];
+    a.src_begin = q.src_off[it.x];
+    a.src_end = q.src_off[it.x + 1];
+    a.tgt_begin = q.tgt_off[it.x];
+    a.tgt_end = q.tgt_off[it.x + 1];
+    slice_body<T, MODE, SYM>(a, a.tgt_begin + (int64_t(it.y) << lp), a.src_begin, a.src_end, lp);
+}
+
 // Persistent workgroups over a queue of (set, target block) items in decreasing cost order.
 // Every workgroup leaves the loop once the shared counter passes the item count.
 template <typename T, int K, int WG, int MODE, bool SYM, int U>
@@ -860,7 +881,12 @@ hipError_t launch_one(const FwdArgs& a, const BatchQueue* bq, int grid, hipStrea
 }
 
 template <typename T, int MODE, bool SYM>
-hipError_t launch_slice(const FwdArgs& a, int lp, hipStream_t st) {
+hipError_t launch_slice(const FwdArgs& a, const BatchQueue* bq, int lp, hipStream_t st) {
+    if (bq) {
+        hipLaunchKernelGGL((k_pair_fwd_slice_sets<T, MODE, SYM>), dim3(unsigned(bq->n_items)), dim3(256), 0, st, a, *bq,
+                           lp);
+        return hipGetLastError();
+    }
     const int64_t nt = a.tgt_end - a.tgt_begin;
     const unsigned grid = unsigned((nt + (int64_t(1) << lp) - 1) >> lp);
     const unsigned ny = a.nchunk > 1 ? unsigned(a.nchunk) : 1u;
@@ -871,20 +897,20 @@ hipError_t launch_slice(const FwdArgs& a, int lp, hipStream_t st) {
 }
 
 template <typename T>
-hipError_t launch_slice_mode(int mode, bool sym, const FwdArgs& a, int lp, hipStream_t st) {
+hipError_t launch_slice_mode(int mode, bool sym, const FwdArgs& a, const BatchQueue* bq, int lp, hipStream_t st) {
     switch (mode) {
         case kModeTransposed:
-            return sym ? launch_slice<T, kModeTransposed, true>(a, lp, st)
-                       : launch_slice<T, kModeTransposed, false>(a, lp, st);
+            return sym ? launch_slice<T, kModeTransposed, true>(a, bq, lp, st)
+                       : launch_slice<T, kModeTransposed, false>(a, bq, lp, st);
         case kModeClassical:
-            return sym ? launch_slice<T, kModeClassical, true>(a, lp, st)
-                       : launch_slice<T, kModeClassical, false>(a, lp, st);
+            return sym ? launch_slice<T, kModeClassical, true>(a, bq, lp, st)
+                       : launch_slice<T, kModeClassical, false>(a, bq, lp, st);
         case kModeVelocity:
-            return sym ? launch_slice<T, kModeVelocity, true>(a, lp, st)
-                       : launch_slice<T, kModeVelocity, false>(a, lp, st);
+            return sym ? launch_slice<T, kModeVelocity, true>(a, bq, lp, st)
+                       : launch_slice<T, kModeVelocity, false>(a, bq, lp, st);
         default:
-            return sym ? launch_slice<T, kModeGradient, true>(a, lp, st)
-                       : launch_slice<T, kModeGradient, false>(a, lp, st);
+            return sym ? launch_slice<T, kModeGradient, true>(a, bq, lp, st)
+                       : launch_slice<T, kModeGradient, false>(a, bq, lp, st);
     }
 }
 
@@ -953,10 +979,11 @@ hipError_t launch_pair_fwd(int dtype, int variant, int mode, bool sym, const Fwd
     }
 }
 
-hipError_t launch_pair_fwd_slice(int dtype, int mode, bool sym, const FwdArgs& a, int lp, hipStream_t st) {
+hipError_t launch_pair_fwd_slice(int dtype, int mode, bool sym, const FwdArgs& a, const BatchQueue* bq, int lp,
+                                 hipStream_t st) {
     if (lp < 0 || lp > 6) return hipErrorInvalidValue;
-    return dtype == kDtypeF64 ? launch_slice_mode<double>(mode, sym, a, lp, st)
-                              : launch_slice_mode<float>(mode, sym, a, lp, st);
+    return dtype == kDtypeF64 ? launch_slice_mode<double>(mode, sym, a, bq, lp, st)
+                              : launch_slice_mode<float>(mode, sym, a, bq, lp, st);
 }
 
 int pair_fwd_occupancy(int dtype, int variant, int mode, bool sym, bool batched) {

@@ -121,6 +121,31 @@ QueueLayout queue_layout(int32_t n_batch, const int64_t* tgt_off, int64_t per_bl
     return queue_layout_items(n_batch, count_blocks(n_batch, tgt_off, per_block));
 }
 
+// Targets per item (log2) of many sets in sliced blocks, or kPlainLp where the queue's 256-target
+// blocks do: those serve while the largest of them is less than a third of the work that falls to
+// each of about kSlots resident workgroups, so that the last ones leave little of the chip idle
+// (32 sets of 20000-60000 particles are near the line: 39.4 ms in blocks, 39.8 in slices), and where
+// every set is a tile or less and there are enough of them (1000 sets of 50-200: 92 us, 100).
+// Fewer than 64 targets per item while that gives less than kSliceItems items.
+constexpr int kPlainLp = 8;
+int batch_slice_lp(int32_t n_batch, const int64_t* src_off, const int64_t* tgt_off) {
+    constexpr double kSlots = 1024.0;
+    constexpr int64_t kSliceItems = 2048;
+    double all = 0.0, largest = 0.0;
+    for (int32_t b = 0; b < n_batch; ++b) {
+        const double ns = double(src_off[b + 1] - src_off[b]);
+        const int64_t nt = tgt_off[b + 1] - tgt_off[b];
+        all += ns * double(nt);
+        largest = std::max(largest, ns * double(std::min<int64_t>(nt, 256)));
+    }
+    if (3.0 * largest <= all / kSlots) return kPlainLp;
+    if (largest <= 256.0 * 256.0 && 2.0 * double(count_blocks(n_batch, tgt_off, 256)) >= kSlots)
+        return kPlainLp;
+    int lp = 6;
+    while (lp > 4 && count_blocks(n_batch, tgt_off, int64_t(1) << lp) < kSliceItems) --lp;
+    return lp;
+}
+
 // Adjoint of many sets.  A queue item is 2^item_lp particles of a set, or the set's own block
 // where that is larger (backward_split_lp): 256 particles, and fewer while that leaves less than
 // kBwdItems items, which is two for each of the chip's resident workgroups.  Measured (FP32, us
@@ -274,7 +299,6 @@ int64_t targets_per_block(int32_t dtype, int variant) {
 // How one set of targets is spread over the chip: blocks of 2^lp targets in the sliced form
 // (lp <= 6) or of one or two targets per lane (lp = kPlainLp), and the sources in nchunk chunks
 // (multiples of 256) whose partial sums go to the workspace.  Depends only on sizes.
-constexpr int kPlainLp = 8;
 struct SplitPlan {
     int lp = kPlainLp;
     int64_t nchunk = 1, chunk = 0;
@@ -444,7 +468,7 @@ vpm_status classical_backward(int32_t dtype, bool sym, bool self, int64_t n_src,
     fo.self = self ? 1 : 0;
     const int mode = fwd_mode(fo, true);
     const int lp = auto_split(dtype, vpm::nacc_of(mode), n_src, n_tgt, 0).lp;  // (no workspace here)
-    if (lp != kPlainLp) return hip_status(vpm::launch_pair_fwd_slice(dtype, mode, sym, f, lp, st));
+    if (lp != kPlainLp) return hip_status(vpm::launch_pair_fwd_slice(dtype, mode, sym, f, nullptr, lp, st));
     const int variant = choose_variant(fo, false, n_tgt);
     const int64_t per_block = targets_per_block(dtype, variant);
     const int64_t grid = (n_tgt + per_block - 1) / per_block;
@@ -545,7 +569,9 @@ size_t vpm_workspace_size(int32_t dtype, int32_t n_batch, const int64_t* src_off
         return std::max(bytes, shape_split(dtype, choose_variant(o, false, tgt_off[1]), nacc, src_off[1],
                                            tgt_off[1]).bytes);
     }
-    return queue_layout(n_batch, tgt_off, kMinTargetsPerBlock).total;
+    const size_t plain = queue_layout(n_batch, tgt_off, kMinTargetsPerBlock).total;
+    const int lp = o.variant > 0 ? kPlainLp : batch_slice_lp(n_batch, src_off, tgt_off);
+    return lp == kPlainLp ? plain : std::max(plain, queue_layout(n_batch, tgt_off, int64_t(1) << lp).total);
 }
 
 }  // extern "C"
@@ -657,7 +683,7 @@ vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, con
     a.chunk = n_src;
     a.nchunk = 1;
     const int mode = fwd_mode(o, stretch);
-    const int64_t per_block = targets_per_block(dtype, variant);
+    int64_t per_block = targets_per_block(dtype, variant);
 
     if (n_batch == 1) {
         const size_t room = workspace ? ws_bytes : 0;
@@ -682,12 +708,18 @@ vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, con
             a.chunk = sp.chunk;
             a.nchunk = int32_t(sp.nchunk);
         }
-        if (sp.lp != kPlainLp) return hip_status(vpm::launch_pair_fwd_slice(dtype, mode, sym, a, sp.lp, st));
+        if (sp.lp != kPlainLp) return hip_status(vpm::launch_pair_fwd_slice(dtype, mode, sym, a, nullptr, sp.lp, st));
         const int64_t grid = (n_tgt + per_block - 1) / per_block;
         return hip_status(vpm::launch_pair_fwd(dtype, variant, mode, sym, a, nullptr, int(grid), st));
     }
 
     // Batched: LPT-ordered (set, block) items, staged into the workspace with the counter.
+    // (a workspace that holds the queue of plain blocks only gets those)
+    int slice_lp = o.variant > 0 ? kPlainLp : batch_slice_lp(n_batch, src_off, tgt_off);
+    if (slice_lp != kPlainLp) {
+        if (queue_layout(n_batch, tgt_off, int64_t(1) << slice_lp).total > ws_bytes) slice_lp = kPlainLp;
+        else per_block = int64_t(1) << slice_lp;
+    }
     struct Item {
         int b, blk;
         int64_t cost;
@@ -717,10 +749,6 @@ vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, con
     DeviceInfo di;
     e = device_info(di);
     if (e != hipSuccess) return VPM_ERR_HIP;
-    int occ = vpm::pair_fwd_occupancy(dtype, variant, mode, sym, true);
-    if (occ < 1) occ = 1;
-    int64_t grid = int64_t(di.cus) * occ;
-    if (grid > int64_t(items.size())) grid = int64_t(items.size());
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     vpm::BatchQueue q;
     q.counter = reinterpret_cast<int*>(ws);
@@ -728,6 +756,11 @@ vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, con
     q.src_off = reinterpret_cast<const int64_t*>(ws + L.off_src);
     q.tgt_off = reinterpret_cast<const int64_t*>(ws + L.off_tgt);
     q.n_items = int(items.size());
+    if (slice_lp != kPlainLp) return hip_status(vpm::launch_pair_fwd_slice(dtype, mode, sym, a, &q, slice_lp, st));
+    int occ = vpm::pair_fwd_occupancy(dtype, variant, mode, sym, true);
+    if (occ < 1) occ = 1;
+    int64_t grid = int64_t(di.cus) * occ;
+    if (grid > int64_t(items.size())) grid = int64_t(items.size());
     return hip_status(vpm::launch_pair_fwd(dtype, variant, mode, sym, a, &q, int(grid), st));
 }
 

@@ -71,7 +71,8 @@ hipError_t launch_pair_fwd(int dtype, int variant, int mode, bool sym, const Fwd
                            const BatchQueue* bq, int grid, hipStream_t st);
 // Sliced form (one set): blocks of 2^lp <= 64 targets whose lanes share the sources; a.nchunk > 1
 // also splits the sources into chunks, as in launch_pair_fwd.
-hipError_t launch_pair_fwd_slice(int dtype, int mode, bool sym, const FwdArgs& a, int lp, hipStream_t st);
+hipError_t launch_pair_fwd_slice(int dtype, int mode, bool sym, const FwdArgs& a, const BatchQueue* bq, int lp,
+                                 hipStream_t st);
 // Scratch of the no-allocation entry point: a file-scope device array of this many bytes
 // (noalloc.hip); noalloc_scratch returns its address on the current device.
 constexpr size_t kNoAllocScratchBytes = size_t(32) << 20;

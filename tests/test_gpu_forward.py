@@ -347,6 +347,36 @@ def test_many_targets_either_side_of_the_plain_kernel(kind, nt, gpu):
 
 
 @pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("mode", ["velocity", "transposed", "gradient"])
+# few uneven sets in blocks of 16, sets around block and tile edges with an empty one, and a batch in
+# blocks of 64; each also with room for the queue of plain blocks only
+@pytest.mark.parametrize("sizes", [(300, 5), (1, 0, 63, 64, 65, 255, 257, 3), (9000,) * 12 + (700, 129)])
+def test_batched_slices(kind, mode, sizes, gpu):
+    import torch
+    off = [0] + [int(v) for v in np.cumsum(sizes)]
+    x, g, s = prepare(_random_set(off[-1], 71, spread=0.5), kind)
+    A = [dev_(v, kind) for v in (x, g, s)]
+    up = lambda b: (b + 255) // 256 * 256
+    plain = 256 + 2 * up(8 * len(off)) + up(8 * int(sum((k + 127) // 128 for k in sizes)))
+    say(f"batched slices {kind} {mode} {sizes[:3]}")
+    for ws in (None, torch.empty(plain, dtype=torch.uint8, device="cuda")):
+        if mode == "gradient":
+            u, d, _ = vpm.vpm_eval_velocity_gradient(*A, src_off=off, workspace=ws)
+        else:
+            u, d = vpm.vpm_eval_velocity_stretching(*A, src_off=off, workspace=ws, velocity_only=mode == "velocity")
+        U, D = host(u), None if d is None else host(d)
+        for b in sorted({0, 1, len(sizes) - 2, len(sizes) - 1}):
+            q = slice(off[b], off[b + 1])
+            if sizes[b] < 2:
+                assert not U[:, q].any()
+                continue
+            idx = np.unique(np.concatenate([[0, sizes[b] - 1], np.random.default_rng(b).integers(0, sizes[b], 60)]))
+            uo, do = oracle.eval_pairs(x[:, q], g[:, q], s[q], x_tgt=x[:, q][:, idx], gam_tgt=g[:, q][:, idx], excl=idx)
+            assert rel_l2(U[:, q][:, idx], uo) <= TOL[kind]
+            assert D is None or rel_l2(D[:, q][:, idx], do) <= TOL[kind]
+
+
+@pytest.mark.parametrize("kind", KINDS)
 def test_permutation_invariance(kind, gpu):
     """Shuffling the particles changes every tile and the summation order; results agree to
     rounding (also a guard against LDS races: a missing barrier would not reproduce)."""
