@@ -53,6 +53,12 @@ struct BatchQueue {
     int n_items;
 };
 
+// Items (set, block) of a batched launch in decreasing cost (lanes x (loop-set size + 1)), those of equal
+// cost in the order of sets and blocks: per_block[b] lanes to a block of set b, the last one shorter.
+// Written to out unless that is null; returns their number.  Host only.
+int64_t queue_items(int32_t n_batch, const int64_t* lane_off, const int64_t* loop_off, const int64_t* per_block,
+                    int2* out);
+
 struct FwdVariant {
     int k;       // targets per lane
     int wg;      // workgroup size
