@@ -97,7 +97,8 @@ def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
     torch = _torch()
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # (not a public name)
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
 def _offsets(off):
