@@ -45,6 +45,7 @@
 // unroll requests of the loops around that call as not honoured.
 #pragma clang diagnostic ignored "-Wpass-failed"
 #include "vpm_internal.h"
+#include "wave_sync.h"
 
 namespace vpm {
 
@@ -843,11 +844,11 @@ __global__ __launch_bounds__(64 * kM2lWaves) void k_fmm_m2l_wave(FmmLevel lv, co
             for (int d = 0; d < 3; ++d) acc[j][d] = 0.0;
         for (int e = wave; e < nlist; e += kM2lWaves) {
             const double* D = dtab + int64_t(__builtin_amdgcn_readfirstlane(list_off[e])) * nt;
-            __builtin_amdgcn_wave_barrier();  // every lane is done with the previous interaction's grid
+            wave_sync();  // every lane is done with the previous interaction's grid
 #pragma unroll
             for (int j = 0; j < SLOTS; ++j)
                 if (lane + 64 * j < nt) sDg[nb[j]] = D[lane + 64 * j] * sc[deg[j]];
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             const int src = __builtin_amdgcn_readfirstlane(list_src[e]);
             const CDouble M0 = (CDouble)(lv.M + int64_t(src) * 3 * nt);
             // 8 steps per batch of scalar loads, which may read up to 7 terms past a lane's
@@ -1466,7 +1467,7 @@ __global__ __launch_bounds__(64 * NW, (GRAD && std::is_same<T, float>::value) ? 
             sl.q[lane] = gsq[j0 + lane];
             sl.w[lane] = gsw[j0 + lane];
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         const CT ub = ubox + 8 * int64_t(u);
         T d2 = T(0);
         for (int d = 0; d < 3; ++d) {
@@ -1491,7 +1492,7 @@ __global__ __launch_bounds__(64 * NW, (GRAD && std::is_same<T, float>::value) ? 
                 near_pair<T, CLASSICAL, GRAD, true>(xi, yi, zi, gxi, gyi, gzi, ngyi, ngzi, sl.p[jj], sl.q[jj],
                                                     sl.w + jj, acc);
         }
-        __builtin_amdgcn_wave_barrier();  // every lane is done with the slot before it is refilled
+        wave_sync();  // every lane is done with the slot before it is refilled
         // FP32 sums run over at most kFoldUnits units
         if constexpr (kComp) {
             if (++folded == kFoldUnits || k + NW >= total) {

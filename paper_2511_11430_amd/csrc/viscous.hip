@@ -40,6 +40,7 @@
 
 #include "device_math.h"
 #include "vpm_internal.h"
+#include "wave_sync.h"
 
 namespace vpm {
 
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(64 * NW) void k_pse(PseArgs a) {
                     buf[lane][1] = r[1];
                     buf[lane][2] = r[2];
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_sync();
                 for (int jj = 0; jj < cnt; ++jj) {
                     const V4 q0 = buf[jj][0];
                     const T rx = xi - q0.x, ry = yi - q0.y, rz = zi - q0.z;
@@ -403,7 +404,7 @@ __global__ __launch_bounds__(64 * NW) void k_pse(PseArgs a) {
                         acc[2] += w * (q1.z - wzi);
                     }
                 }
-                __builtin_amdgcn_wave_barrier();  // every lane is done with the slot before it is refilled
+                wave_sync();  // every lane is done with the slot before it is refilled
                 if constexpr (kComp) {
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
