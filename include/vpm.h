@@ -507,7 +507,9 @@ vpm_status vpm_variant_info(int32_t k, int32_t* targets_per_lane, int32_t* workg
  * n_batch sets with offsets src_off (host int64[n_batch+1]), x, gamma, sigma [3][ld] — with
  * HIP events on `stream`, reps timed runs each after one untimed run, keeps the fastest
  * (minimum over the runs) and records it in the plan for launches of that many targets
- * (single-set or batched, as vpm_set_plan).  u_scratch, dgamma_scratch [3][ld] receive
+ * (single-set or batched, as vpm_set_plan) if it is more than 1 % faster than the library's own
+ * spread of these sets over the GPU, timed last.  Otherwise such launches keep the library's spread,
+ * with the recorded shape where that has whole targets per lane.  u_scratch, dgamma_scratch [3][ld] receive
  * results and are overwritten; workspace as for vpm_eval_velocity_stretching (required when
  * n_batch > 1).  variant_out (host, may be NULL) receives the chosen variant (1-based), ms_out
  * (host float[vpm_variant_count()], may be NULL) each shape's best time in ms.  A setup call:
@@ -520,9 +522,12 @@ vpm_status vpm_autotune(int32_t dtype, int32_t n_batch, const int64_t* src_off, 
 
 /* Kernel-shape plan used when opt->variant is 0 (FP32C only): for target counts in
  * [n_lo, n_hi] (rounded out to powers of two), single-set (batched = 0) or batched
- * (batched = 1, counted over all sets) launches use variant k (0 restores the default, 1).
- * Written by the tuner; process-wide, thread-safe.  vpm_get_plan returns the variant a
- * launch of n targets would use. */
+ * (batched = 1, counted over all sets) launches use variant k as they use opt->variant; 0
+ * restores the default, the library's own spread (blocks of a few targets whose lanes share the
+ * sources, or a shape of its choice, by a rule on the sizes).  The gradient mode has one shape
+ * and takes no plan.  Written by the tuner; process-wide, thread-safe.  vpm_get_plan returns the
+ * variant a launch of n targets uses, without a plan the one it uses where the library's spread
+ * has whole targets per lane. */
 vpm_status vpm_set_plan(int32_t dtype, int32_t batched, int64_t n_lo, int64_t n_hi, int32_t variant);
 int32_t vpm_get_plan(int32_t dtype, int32_t batched, int64_t n);
 

@@ -847,7 +847,8 @@ def vpm_check_inputs(x, gamma, sigma, *, workspace=None, stream=None):
 def vpm_autotune(x, gamma, sigma, *, src_off=None, reps=3, u_scratch=None, dgamma_scratch=None, workspace=None,
                  stream=None):
     """Times every FP32C kernel shape on these particles (self evaluation; src_off: many sets)
-    inside the library and records the fastest in its plan.  Returns (variant, [ms per shape])."""
+    inside the library and records the fastest as the plan if it beats the library's own spread.
+    Returns (variant, [ms per shape])."""
     torch = _torch()
     lib = _lib.load()
     n = x.shape[1]
@@ -860,9 +861,11 @@ def vpm_autotune(x, gamma, sigma, *, src_off=None, reps=3, u_scratch=None, dgamm
         dgamma_scratch = torch.empty_like(x)
     off = [0, n] if src_off is None else list(src_off)
     so = _offsets(off)
-    if workspace is None and len(off) > 2:
-        workspace = torch.empty(max(vpm_workspace_size(F32C, off), 1), dtype=torch.uint8, device=x.device)
     nv = vpm_variant_count()
+    if workspace is None:
+        # (as the evaluations have it: one set's shapes are timed with their source chunks)
+        need = max(vpm_workspace_size(F32C, off, variant=v) for v in range(nv + 1))
+        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=x.device)
     ms = (ctypes.c_float * nv)()
     v = ctypes.c_int32()
     st = lib.vpm_autotune(F32C, len(off) - 1, so, _p(x), _p(gamma), _p(sigma), _ld(x), _p(u_scratch),

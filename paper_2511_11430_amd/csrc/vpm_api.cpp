@@ -269,10 +269,16 @@ hipError_t stage_and_copy(const std::vector<unsigned char>& blob, void* dst, hip
 }
 
 // ------------------------------------------------------------------ kernel-shape plans
-// Tuned FP32C kernel shape per (single set / batched, ceil(log2(targets))) bucket, written by
-// vpm_set_plan (the tuner); 0 = not set, then the built-in choice.  Guarded by g_mutex.
+// FP32C kernel shape per (single set / batched, ceil(log2(targets))) bucket, 0 = the built-in choice, and
+// whether launches of that size take it as they take a caller's opt->variant (vpm_set_plan, and the
+// tuner where a shape beat the library's own spread) or only where the library's spread has a target
+// or two per lane.  Guarded by g_mutex.
 constexpr int kPlanBuckets = 40;
-int g_plan[2][kPlanBuckets] = {};
+struct Plan {
+    int shape = 0;
+    bool holds = false;
+};
+Plan g_plan[2][kPlanBuckets];
 
 int plan_bucket(int64_t n) {
     int b = 0;
@@ -280,12 +286,16 @@ int plan_bucket(int64_t n) {
     return b;
 }
 
+// A tuned shape takes the place of the library's own spread where it is faster by more than the timings
+// of one launch differ.
+constexpr float kTuneGain = 0.99f;
+
 // 0-based variant for an FP32C launch when the caller leaves opt->variant at 0.  The gradient
 // mode has a single shape.
-// Built-in choice without a tuned plan (what the tuner picks on MI355X): (1, 256, 4) below 16K
-// targets and (1, 512, 2) above for one set; (1, 128, 2) for batches.
+// Built-in choice without a tuned plan: (1, 256, 4) below 16K targets and (1, 512, 2) above for one set;
+// (1, 256, 2) for batches (the 64 uneven wakes of 2.8 million particles 180 ms, (1, 128, 2) 184).
 int default_variant(bool batched, int64_t n_tgt) {
-    if (batched) return 5;
+    if (batched) return 1;
     return n_tgt <= 16384 ? 2 : 7;
 }
 
@@ -293,8 +303,19 @@ int choose_variant(const vpm_options& o, bool batched, int64_t n_tgt) {
     if (o.gradient) return vpm::kGradientVariant;
     if (o.variant > 0) return o.variant - 1;
     std::lock_guard<std::mutex> lock(g_mutex);
-    const int v = g_plan[batched ? 1 : 0][plan_bucket(n_tgt)];
+    const int v = g_plan[batched ? 1 : 0][plan_bucket(n_tgt)].shape;
     return v > 0 ? v - 1 : default_variant(batched, n_tgt);
+}
+
+// Whether choose_variant's shape is one that the caller asked for, in the options or in the plan: the
+// launch then has that shape's blocks and chunks, and not the library's own spread (auto_split,
+// batch_slice_lp).
+bool caller_shape(int32_t dtype, const vpm_options& o, bool batched, int64_t n_tgt) {
+    if (o.gradient) return false;
+    if (o.variant > 0) return true;
+    if (dtype != kDtypeF32C) return false;
+    std::lock_guard<std::mutex> lock(g_mutex);
+    return g_plan[batched ? 1 : 0][plan_bucket(n_tgt)].holds;
 }
 
 int fwd_mode(const vpm_options& o, bool stretch) {
@@ -553,7 +574,7 @@ vpm_status vpm_set_plan(int32_t dtype, int32_t batched, int64_t n_lo, int64_t n_
     if (variant < 0 || variant > vpm::kNumF32Variants) return VPM_ERR_ENUM;
     if (n_lo < 0 || n_hi < n_lo) return VPM_ERR_SIZE;
     std::lock_guard<std::mutex> lock(g_mutex);
-    for (int b = plan_bucket(n_lo); b <= plan_bucket(n_hi); ++b) g_plan[batched][b] = variant;
+    for (int b = plan_bucket(n_lo); b <= plan_bucket(n_hi); ++b) g_plan[batched][b] = {variant, variant > 0};
     return VPM_OK;
 }
 
@@ -573,8 +594,8 @@ size_t vpm_workspace_size(int32_t dtype, int32_t n_batch, const int64_t* src_off
     if (check_options(o) != VPM_OK) return 0;
     if (n_batch == 1) {
         const int nacc = o.gradient ? vpm::nacc_of(vpm::kModeGradient) : vpm::nacc_of(vpm::kModeTransposed);
-        if (o.variant > 0 && !o.gradient)
-            return shape_split(dtype, o.variant - 1, nacc, src_off[1], tgt_off[1]).bytes;
+        if (caller_shape(dtype, o, false, tgt_off[1]))
+            return shape_split(dtype, choose_variant(o, false, tgt_off[1]), nacc, src_off[1], tgt_off[1]).bytes;
         // (whether a call wants the velocity only, the options do not say)
         const size_t bytes = auto_split(dtype, nacc, src_off[1], tgt_off[1], kMaxPartials).bytes;
         if (o.gradient || !velocity_by_shape(dtype, tgt_off[1])) return bytes;
@@ -582,7 +603,7 @@ size_t vpm_workspace_size(int32_t dtype, int32_t n_batch, const int64_t* src_off
                                            tgt_off[1]).bytes);
     }
     const size_t plain = queue_layout(n_batch, tgt_off, kMinTargetsPerBlock).total;
-    const int lp = o.variant > 0 ? kPlainLp : batch_slice_lp(n_batch, src_off, tgt_off);
+    const int lp = caller_shape(dtype, o, true, tgt_off[n_batch]) ? kPlainLp : batch_slice_lp(n_batch, src_off, tgt_off);
     return lp == kPlainLp ? plain : std::max(plain, queue_layout(n_batch, tgt_off, int64_t(1) << lp).total);
 }
 
@@ -591,12 +612,13 @@ size_t vpm_workspace_size(int32_t dtype, int32_t n_batch, const int64_t* src_off
 namespace {
 
 // Shared body of vpm_eval_velocity_stretching (grad_out == nullptr, o.gradient == 0) and
-// vpm_eval_velocity_gradient (o.gradient == 1).
+// vpm_eval_velocity_gradient (o.gradient == 1).  own_spread: the library's own spread, whatever the plan says.
 vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, const int64_t* tgt_off,
                      const void* x_src, const void* gamma_src, const void* sigma_src, int64_t ld_src,
                      const void* x_tgt, const void* gamma_tgt, const void* sigma_tgt, int64_t ld_tgt,
                      const int32_t* tgt_exclude, void* u_out, void* dgamma_out, void* grad_out, int64_t ld_out,
-                     vpm_options o, void* workspace, size_t ws_bytes, void* stream, bool noalloc = false) {
+                     vpm_options o, void* workspace, size_t ws_bytes, void* stream, bool noalloc = false,
+                     bool own_spread = false) {
     if (!dtype_ok(dtype)) return VPM_ERR_DTYPE;
     if (n_batch < 1) return VPM_ERR_SIZE;
     vpm_status s = check_options(o);
@@ -649,6 +671,7 @@ vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, con
     if (overlap(ru, rd) || overlap(ru, rj) || overlap(rd, rj)) return VPM_ERR_ALIAS;
 
     const int variant = choose_variant(o, n_batch > 1, n_tgt);
+    const bool as_asked = !own_spread && caller_shape(dtype, o, n_batch > 1, n_tgt);
     if (workspace && ws_bytes > 0) {
         const Range rw = span(workspace, 1, int64_t(ws_bytes), int64_t(ws_bytes), 1);
         if (overlap(rw, ru) || overlap(rw, rd) || overlap(rw, rj)) return VPM_ERR_ALIAS;
@@ -701,7 +724,7 @@ vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, con
         const size_t room = workspace ? ws_bytes : 0;
         SplitPlan sp;
         const bool by_shape = mode == vpm::kModeVelocity && velocity_by_shape(dtype, n_tgt);
-        if (o.variant > 0 || by_shape) {
+        if (as_asked || by_shape) {
             // velocity only counts the nine sums of the stretching modes, as vpm_workspace_size does
             const int nacc = vpm::nacc_of(by_shape ? vpm::kModeTransposed : mode);
             sp = shape_split(dtype, variant, nacc, n_src, n_tgt);
@@ -727,7 +750,7 @@ vpm_status eval_impl(int32_t dtype, int32_t n_batch, const int64_t* src_off, con
 
     // Batched: LPT-ordered (set, block) items, staged into the workspace with the counter.
     // (a workspace that holds the queue of plain blocks only gets those)
-    int slice_lp = o.variant > 0 ? kPlainLp : batch_slice_lp(n_batch, src_off, tgt_off);
+    int slice_lp = as_asked ? kPlainLp : batch_slice_lp(n_batch, src_off, tgt_off);
     if (slice_lp != kPlainLp) {
         if (queue_layout(n_batch, tgt_off, int64_t(1) << slice_lp).total > ws_bytes) slice_lp = kPlainLp;
         else per_block = int64_t(1) << slice_lp;
@@ -1308,48 +1331,55 @@ vpm_status vpm_autotune(int32_t dtype, int32_t n_batch, const int64_t* src_off, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     vpm_options o = default_options();
     o.self = 1;
-    // every shape once (validation, first-launch costs), then reps timed runs of each
-    for (int v = 1; v <= vpm::kNumF32Variants; ++v) {
+    const bool batched = n_batch > 1;
+    const int bucket = plan_bucket(n);
+    auto run = [&](int v) {  // shape v, 0 = the library's own spread
         o.variant = v;
-        s = eval_impl(dtype, n_batch, src_off, nullptr, x, gamma, sigma, ld, nullptr, nullptr, nullptr, 0, nullptr,
-                      u_scratch, dgamma_scratch, nullptr, ld, o, workspace, ws_bytes, stream);
-        if (s != VPM_OK) return s;
-    }
+        return eval_impl(dtype, n_batch, src_off, nullptr, x, gamma, sigma, ld, nullptr, nullptr, nullptr, 0, nullptr,
+                         u_scratch, dgamma_scratch, nullptr, ld, o, workspace, ws_bytes, stream, false, v == 0);
+    };
+    // every shape once (validation, first-launch costs), then reps timed runs of each
+    for (int v = 1; v <= vpm::kNumF32Variants; ++v)
+        if ((s = run(v)) != VPM_OK) return s;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
         if (e0) (void)hipEventDestroy(e0);
         return VPM_ERR_HIP;
     }
-    float best_ms[vpm::kNumF32Variants];
-    s = VPM_OK;
-    for (int v = 1; v <= vpm::kNumF32Variants && s == VPM_OK; ++v) {
-        o.variant = v;
-        float best = -1.0f;
-        for (int r = 0; r < reps && s == VPM_OK; ++r) {
-            if (hipEventRecord(e0, st) != hipSuccess) { s = VPM_ERR_HIP; break; }
-            s = eval_impl(dtype, n_batch, src_off, nullptr, x, gamma, sigma, ld, nullptr, nullptr, nullptr, 0,
-                          nullptr, u_scratch, dgamma_scratch, nullptr, ld, o, workspace, ws_bytes, stream);
-            if (s != VPM_OK) break;
+    auto time = [&](int v, float& best) {
+        best = -1.0f;
+        for (int r = 0; r < reps; ++r) {
+            if (hipEventRecord(e0, st) != hipSuccess) return VPM_ERR_HIP;
+            const vpm_status rs = run(v);
+            if (rs != VPM_OK) return rs;
             float ms = 0.0f;
             if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
-                s = VPM_ERR_HIP;
-                break;
-            }
+                hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
+                return VPM_ERR_HIP;
             if (best < 0.0f || ms < best) best = ms;
         }
-        best_ms[v - 1] = best;
+        return VPM_OK;
+    };
+    float best_ms[vpm::kNumF32Variants], own_ms = 0.0f;
+    for (int v = 1; v <= vpm::kNumF32Variants && s == VPM_OK; ++v) s = time(v, best_ms[v - 1]);
+    int pick = 1;
+    if (s == VPM_OK) {
+        for (int v = 2; v <= vpm::kNumF32Variants; ++v)
+            if (best_ms[v - 1] < best_ms[pick - 1]) pick = v;
+        Plan before;
+        {
+            std::lock_guard<std::mutex> lock(g_mutex);
+            before = g_plan[batched][bucket];
+            g_plan[batched][bucket] = {pick, false};  // (where the library's spread is a target per lane, this shape)
+        }
+        if ((s = run(0)) == VPM_OK) s = time(0, own_ms);
+        std::lock_guard<std::mutex> lock(g_mutex);
+        if (s != VPM_OK) g_plan[batched][bucket] = before;
+        else g_plan[batched][bucket].holds = best_ms[pick - 1] < kTuneGain * own_ms;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (s != VPM_OK) return s;
-    int pick = 1;
-    for (int v = 2; v <= vpm::kNumF32Variants; ++v)
-        if (best_ms[v - 1] < best_ms[pick - 1]) pick = v;
-    {
-        std::lock_guard<std::mutex> lock(g_mutex);
-        g_plan[n_batch > 1 ? 1 : 0][plan_bucket(n)] = pick;
-    }
     if (variant_out) *variant_out = pick;
     if (ms_out)
         for (int v = 0; v < vpm::kNumF32Variants; ++v) ms_out[v] = best_ms[v];

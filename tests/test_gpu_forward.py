@@ -467,6 +467,56 @@ def test_autotune_times_every_shape_and_sets_the_plan(gpu):
         tune.apply_cache()
 
 
+def _small_batch():
+    wakes = W.config5(n_wakes=6, scale=0.02)
+    off = [0]
+    for w in wakes:
+        off.append(off[-1] + w["x"].shape[1])
+    return [dev_(np.concatenate([W.to_f32(w[k]) for w in wakes], -1), "f32c") for k in ("x", "gamma", "sigma")], off
+
+
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("variant", [1, 4, 8])
+def test_a_plan_is_used_as_the_variant(batched, variant, gpu):
+    """Launches of the sizes that a plan was set for run in its shape: the bits of opt->variant."""
+    import torch
+    from paper_2511_11430_amd import tune
+    if batched:
+        A, off = _small_batch()
+    else:
+        c = W.config3(n=3001)
+        A, off = [dev_(W.to_f32(c[k]), "f32c") for k in ("x", "gamma", "sigma")], [0, 3001]
+    say(f"plan batched={batched} variant={variant}")
+    try:
+        asked = vpm.vpm_eval_velocity_stretching(*A, src_off=off, variant=variant)
+        vpm.vpm_set_plan(int(batched), off[-1], off[-1], variant)
+        got = vpm.vpm_eval_velocity_stretching(*A, src_off=off)
+        assert torch.equal(got[0], asked[0]) and torch.equal(got[1], asked[1])
+    finally:
+        vpm.vpm_set_plan(int(batched), off[-1], off[-1], 0)
+        tune.apply_cache()
+
+
+def test_the_tuner_leaves_the_faster_spread(gpu):
+    """1021 particles take several times as long in any shape as in sliced blocks: after the tuner, which
+    records the fastest shape, such launches still have the library's spread (the same bits)."""
+    import torch
+    from paper_2511_11430_amd import tune
+    c = W.config3(n=1021)
+    A = [dev_(W.to_f32(c[k]), "f32c") for k in ("x", "gamma", "sigma")]
+    say("tuner on 1021 particles")
+    try:
+        vpm.vpm_set_plan(0, 1021, 1021, 0)
+        before = vpm.vpm_eval_velocity_stretching(*A)
+        best, _ = vpm.vpm_autotune(*A, reps=5)
+        after = vpm.vpm_eval_velocity_stretching(*A)
+        assert vpm.vpm_get_plan(0, 1021) == best
+        assert torch.equal(before[0], after[0]) and torch.equal(before[1], after[1])
+    finally:
+        vpm.vpm_set_plan(0, 1021, 1021, 0)
+        tune.apply_cache()
+
+
 @pytest.mark.parametrize("form", [0, 1, 2, 3, 4])
 def test_fma_chain_calibration_kernel(form, gpu):
     """The calibration kernel reports the FMA instruction count it issues and computes the
