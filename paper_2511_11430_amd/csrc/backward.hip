@@ -31,8 +31,8 @@
 // scales by 1/(4 pi) at the end.  Per-particle sums are FP32 tile partials folded into two-sum
 // pairs (VPM_F32C) or plain FP64 (VPM_F64).
 //
-// Bound by VALU issue.  Sets too small to fill the chip with a particle per lane (below about
-// 262144) give several lanes to a particle, each taking a slice of every staged tile (split_lp).
+// Bound by VALU issue.  Sets too small to fill the chip well with a particle per lane (below about a
+// million) give several lanes to a particle, each taking a slice of every staged tile (split_lp).
 #include <hip/hip_runtime.h>
 
 #include "device_math.h"
@@ -543,27 +543,42 @@ __global__ __launch_bounds__(WG) void k_backward_f64(BwdArgs a, int lp) {
     backward_body<T, WG, RA, RB, STR, SYM>(a, blockIdx.x, 0, a.nl, 0, a.no, lp);
 }
 
-// Particles per workgroup (log2; 8 = no split) of a lane set of nl particles.  A wavefront's work
-// per staged tile is P pairs per lane (about 80 VALU instructions each) and about 230
-// instructions' worth of staging, box reduction, folds and waiting.  kSlots workgroups are
-// resident on the chip (four wavefronts per SIMD); fewer than that run each wavefront faster, so
-// x = nl / P / kSlots rounds take 0.6 + 0.4 x below one and x + 0.1 from there (fitted to the
-// times of P = 4 ... 256 at 1000-200000 particles).  Without the split a set of fewer than 262144
-// particles leaves SIMDs with one wavefront or none.  A function of nl alone, so that a set gets
-// the same sums in a launch of its own and in a queue of many sets; blocks of 4 would take 1000
-// particles alone from 37 to 23 us but a queue of 300 sets of 64-600 from 150 to 490 us.
+// Particles per workgroup (log2; 8 = no split) of a lane set of nl particles over a loop set of no.  In
+// units of which a pair takes 80 (VALU instructions in FP32, half as many in FP64): a staged tile takes
+// 230 for staging, box reduction, folds and waiting, a workgroup 1200 (FP64 750) for its beginning and
+// its sums' end.  kSlots workgroups are resident on the chip (four wavefronts per SIMD); fewer than that run
+// each wavefront faster, so x = nl / P / kSlots rounds take 0.6 + 0.4 x or x + 0.1, whichever is more
+// (fitted to the times of P = 16 ... 256 at 1000-200000 particles).  The boxes of 256 particles are near
+// more tiles than those of 64 (a pair 81), and in FP64, where an in-core pair alone on its SIMD takes 130,
+// a block among the loop set lasts at least as long as its pairs with a tile.
+// So sets of more than 26000 particles run in blocks of 32, of more than 72000 in blocks of 64, and a
+// particle per lane is left to more than 940000 (both roles: 600000 hover particles in blocks of 64 558
+// ms, 256 590, FP64 1146 and 1178; two million 5980 and 5770) and to few loop particles, whose tile is less
+// work than the workgroup itself (262144 lanes over 2 targets, velocity only: 26 us in blocks of 64, 11;
+// FP32 over 128: 49 and 36, FP64 71 and 144).
+// A function of the two sizes and the type alone, so that a set gets the same sums in a launch of its own
+// and in a queue of many sets; blocks of 4 would take 1000 particles alone from 37 to 23 us but a queue of
+// 300 sets of 64-600 from 150 to 490 us.
 // Measured (FP32, both roles, hover wake, us per call without and with the split): 1000
 // particles 393 / 37, 4999 1686 / 143, 16384 4970 / 659, 65536 17890 / 8080, 200000 83300 / 67700.
 constexpr int kSplitLpMin = 4, kSplitLpMax = 6, kNoSplitLp = 8;
 constexpr int64_t kSlots = 1024;
-__host__ __device__ inline int split_lp(int64_t nl) {
+__host__ __device__ inline int split_lp(int64_t nl, int64_t no, bool f64) {
+    if (no > (1 << 20)) no = 1 << 20;  // (the products fit 64 bits; a million are many tiles already)
+    const int64_t tiles = (no + 255) >> 8, first = no < 256 ? no : 256;
     int best = kNoSplitLp;
     int64_t least = 0;
     for (int lp = kNoSplitLp; lp >= kSplitLpMin; --lp) {
         if (lp > kSplitLpMax && lp != kNoSplitLp) continue;
-        const int64_t wgs = (nl + (int64_t(1) << lp) - 1) >> lp;
-        const int64_t rounds = wgs < kSlots ? (6 * kSlots + 4 * wgs) / 10 : wgs + kSlots / 10;
-        const int64_t cost = rounds * ((int64_t(80) << lp) + 230);
+        // in sixteenths of a workgroup, the last one not rounded up
+        const int64_t wgs = nl >> (lp - 4), slots = 16 * kSlots;
+        const int64_t below = (6 * slots + 4 * wgs) / 10, above = wgs + slots / 10;
+        const int64_t rounds = below > above ? below : above;
+        // a lane's pairs, of the whole tiles and of the last one
+        const int64_t pairs = ((no >> 8) << lp) + ((((no & 255) << lp) + 255) >> 8);
+        int64_t cost = rounds * ((f64 ? 750 : 1200) + 230 * tiles + (lp == kNoSplitLp ? 81 : 80) * pairs);
+        const int64_t alone = f64 ? slots * 130 * (((first << lp) + 255) >> 8) : 0;
+        if (alone > cost) cost = alone;
         if (lp == kNoSplitLp || cost < least) {
             best = lp;
             least = cost;
@@ -600,7 +615,7 @@ __device__ __forceinline__ void backward_queue(const BwdArgs& a, const BatchQueu
         const int64_t lb = uniform_i64(lo[set]), nl = uniform_i64(lo[set + 1]) - lb;
         const int64_t ob = uniform_i64(oo[set]), no = uniform_i64(oo[set + 1]) - ob;
         // the item's particles, in the blocks that a launch for this set alone would have
-        const int lp = split_lp(nl);
+        const int lp = split_lp(nl, no, std::is_same<T, double>::value);
         const int more = item_lp > lp ? item_lp - lp : 0;
         const int64_t b0 = nth << more;
         for (int k = 0; k < (1 << more) && ((b0 + k) << lp) < nl; ++k)
@@ -620,7 +635,7 @@ __global__ __launch_bounds__(WG) void k_backward_batched_f64(BwdArgs a, BatchQue
 template <typename T, int WG, bool RA, bool RB, bool STR, bool SYM>
 void launch_k(const BwdArgs& a, hipStream_t st) {
     static_assert(WG == 1 << kNoSplitLp, "without a split a particle per lane");
-    const int lp = split_lp(a.nl);
+    const int lp = split_lp(a.nl, a.no, std::is_same<T, double>::value);
     const unsigned grid = unsigned((a.nl + (int64_t(1) << lp) - 1) >> lp);
     if constexpr (std::is_same<T, float>::value)
         hipLaunchKernelGGL((k_backward_f32<T, WG, RA, RB, STR, SYM>), dim3(grid), dim3(WG), 0, st, a, lp);
@@ -681,7 +696,7 @@ hipError_t launch_t(bool ra, bool rb, bool stretch, bool sym, const BwdArgs& a, 
 
 }  // namespace
 
-int backward_split_lp(int64_t nl) { return split_lp(nl); }
+int backward_split_lp(int64_t nl, int64_t no, bool f64) { return split_lp(nl, no, f64); }
 
 hipError_t launch_backward(int dtype, bool role_a, bool role_b, bool stretch, bool sym,
                            const BwdArgs& a, hipStream_t st) {

@@ -180,42 +180,44 @@ int batch_slice_lp(int32_t n_batch, const int64_t* src_off, const int64_t* tgt_o
 // 512-20000 11550 / 10000.
 constexpr int64_t kBwdItems = 2048;
 constexpr int kBwdItemLpMax = 8, kBwdItemLpMin = 4;
-int64_t backward_items(int32_t n_batch, const int64_t* off, int item_lp) {
+int64_t backward_items(bool f64, int32_t n_batch, const int64_t* lane, const int64_t* loop, int item_lp) {
     int64_t items = 0;
     for (int32_t b = 0; b < n_batch; ++b) {
-        const int64_t n = off[b + 1] - off[b];
-        const int lp = std::max(item_lp, vpm::backward_split_lp(n));
+        const int64_t n = lane[b + 1] - lane[b];
+        const int lp = std::max(item_lp, vpm::backward_split_lp(n, loop[b + 1] - loop[b], f64));
         items += (n + (int64_t(1) << lp) - 1) >> lp;
     }
     return items;
 }
 // A workspace of `room` bytes may hold fewer items than that (one sized for a larger batch of larger
 // sets does): the items then grow until they fit, 256 particles at most.  The results do not change.
-int backward_item_lp(int32_t n_batch, const int64_t* off, size_t room = SIZE_MAX) {
+int backward_item_lp(bool f64, int32_t n_batch, const int64_t* lane, const int64_t* loop, size_t room = SIZE_MAX) {
     int lp = kBwdItemLpMax;
-    while (lp > kBwdItemLpMin && backward_items(n_batch, off, lp) < kBwdItems &&
-           queue_layout_items(n_batch, backward_items(n_batch, off, lp - 1)).total <= room)
+    while (lp > kBwdItemLpMin && backward_items(f64, n_batch, lane, loop, lp) < kBwdItems &&
+           queue_layout_items(n_batch, backward_items(f64, n_batch, lane, loop, lp - 1)).total <= room)
         --lp;
     return lp;
 }
 // The larger of the two queues (source blocks, target blocks).
-QueueLayout backward_queue_layout(int32_t n_batch, const int64_t* src_off, const int64_t* tgt_off) {
-    return queue_layout_items(n_batch,
-                              std::max(backward_items(n_batch, src_off, backward_item_lp(n_batch, src_off)),
-                                       backward_items(n_batch, tgt_off, backward_item_lp(n_batch, tgt_off))));
+QueueLayout backward_queue_layout(bool f64, int32_t n_batch, const int64_t* src_off, const int64_t* tgt_off) {
+    auto items = [&](const int64_t* lane, const int64_t* loop) {
+        return backward_items(f64, n_batch, lane, loop, backward_item_lp(f64, n_batch, lane, loop));
+    };
+    return queue_layout_items(n_batch, std::max(items(src_off, tgt_off), items(tgt_off, src_off)));
 }
 
 hipError_t stage_and_copy(const std::vector<unsigned char>& blob, void* dst, hipStream_t st);
 
 // Stages the LPT-ordered (set, block) items of the adjoint's lane sets (cost: lane count x
 // loop-set size) with both offset tables into the workspace; returns the item count.
-hipError_t stage_queue(int32_t n_batch, const int64_t* src_off, const int64_t* tgt_off, bool lane_is_tgt,
+hipError_t stage_queue(bool f64, int32_t n_batch, const int64_t* src_off, const int64_t* tgt_off, bool lane_is_tgt,
                        int item_lp, void* workspace, hipStream_t st, int64_t* n_items) {
     const int64_t* lane = lane_is_tgt ? tgt_off : src_off;
     const int64_t* loop = lane_is_tgt ? src_off : tgt_off;
     std::vector<int64_t> per_block(n_batch);
     for (int32_t b = 0; b < n_batch; ++b)
-        per_block[b] = int64_t(1) << std::max(item_lp, vpm::backward_split_lp(lane[b + 1] - lane[b]));
+        per_block[b] = int64_t(1) << std::max(item_lp, vpm::backward_split_lp(lane[b + 1] - lane[b],
+                                                                              loop[b + 1] - loop[b], f64));
     *n_items = vpm::queue_items(n_batch, lane, loop, per_block.data(), nullptr);
     if (*n_items == 0) return hipSuccess;
     const QueueLayout L = queue_layout_items(n_batch, *n_items);
@@ -514,8 +516,10 @@ hipError_t backward_batched(int32_t dtype, int32_t n_batch, const int64_t* src_o
                             bool role_a, bool role_b, bool stretch, bool sym, const vpm::BwdArgs& a,
                             bool lane_is_tgt, void* workspace, size_t ws_bytes, hipStream_t st) {
     int64_t n_items = 0;
-    const int item_lp = backward_item_lp(n_batch, lane_is_tgt ? tgt_off : src_off, ws_bytes);
-    hipError_t e = stage_queue(n_batch, src_off, tgt_off, lane_is_tgt, item_lp, workspace, st, &n_items);
+    const bool f64 = dtype == kDtypeF64;
+    const int item_lp = backward_item_lp(f64, n_batch, lane_is_tgt ? tgt_off : src_off,
+                                         lane_is_tgt ? src_off : tgt_off, ws_bytes);
+    hipError_t e = stage_queue(f64, n_batch, src_off, tgt_off, lane_is_tgt, item_lp, workspace, st, &n_items);
     if (e != hipSuccess || n_items == 0) return e;
     DeviceInfo di;
     e = device_info(di);
@@ -1126,8 +1130,8 @@ vpm_status vpm_backward(int32_t dtype, int32_t n_batch, const int64_t* src_off,
     }
     const bool classical = o.scheme == VPM_STRETCH_CLASSICAL && stretch;
     if (n_batch > 1 && !classical) {
-        const int64_t least = std::max(backward_items(n_batch, src_off, kBwdItemLpMax),
-                                       backward_items(n_batch, tgt_off, kBwdItemLpMax));
+        const int64_t least = std::max(count_blocks(n_batch, src_off, int64_t(1) << kBwdItemLpMax),
+                                       count_blocks(n_batch, tgt_off, int64_t(1) << kBwdItemLpMax));
         if (!workspace || ws_bytes < queue_layout_items(n_batch, least).total) return VPM_ERR_WORKSPACE;
         const Range rw = span(workspace, 1, int64_t(ws_bytes), int64_t(ws_bytes), 1);
         for (int i = 0; i < 4; ++i)
@@ -1201,7 +1205,7 @@ size_t vpm_backward_workspace_size(int32_t dtype, int32_t n_batch, const int64_t
     if (n_batch == 1) return 0;
     if (!tgt_off) tgt_off = src_off;
     if (check_offsets(n_batch, tgt_off) != VPM_OK) return 0;
-    return backward_queue_layout(n_batch, src_off, tgt_off).total;
+    return backward_queue_layout(dtype == kDtypeF64, n_batch, src_off, tgt_off).total;
 }
 
 // State arrays may be FP64 while F and the evaluation copies are FP32 (mixed program);

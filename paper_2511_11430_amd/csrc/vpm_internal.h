@@ -152,12 +152,12 @@ struct BwdArgs {
     int32_t self;  // loop set == lane set, skip j == i
 };
 // Workgroup size of the adjoint kernel, and log2 of the particles that one workgroup takes of a
-// lane set of nl particles.
+// lane set of nl particles over a loop set of no.
 constexpr int kBwdWG = 256;
-int backward_split_lp(int64_t nl);
+int backward_split_lp(int64_t nl, int64_t no, bool f64);
 // Persistent launch over a queue of (set, lane block) items (lane_is_tgt: the lane set of set
 // b is its target range, the loop set its source range); item (b, k) is the k-th block of
-// 2^max(item_lp, backward_split_lp(set size)) particles; grid = resident workgroups.
+// 2^max(item_lp, backward_split_lp of the set) particles; grid = resident workgroups.
 hipError_t launch_backward_batched(int dtype, bool role_a, bool role_b, bool stretch, bool sym, const BwdArgs& a,
                                    const BatchQueue& q, int item_lp, int grid, int lane_is_tgt, hipStream_t st);
 int backward_occupancy(int dtype, bool role_a, bool role_b, bool stretch, bool sym);
