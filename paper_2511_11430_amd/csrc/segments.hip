@@ -17,6 +17,7 @@
 // multiply-adds, and the sums hold u_y and u_z negated until the epilogue.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device_math.h"
@@ -436,21 +437,22 @@ __device__ __forceinline__ void add_cross(double* J, const double* w) {
     J[7] += w[0];
 }
 
-// A lane's share of a tile: 256 / LPT consecutive segments, started at a rotated place so that the
-// lanes' LDS reads fall into different banks.  Consecutive segments are mostly the edges of one
-// ring, whose contributions largely cancel: dealt out one by one, every lane sums edges that do
-// not, with several times the rounding error.
-template <int LPT>
-__device__ __forceinline__ int share_index(int part, int i) {
-    constexpr int C = 256 / LPT;
-    return part * C + ((i + part * C / 16) & (C - 1));
+// A lane's share of a tile of cnt segments: the per = ceil(cnt / LPT) consecutive ones from part * per
+// on (the last lanes' may be short or empty), so a tile takes `per` steps of every wavefront however
+// few segments it has.  It starts at a rotated place, so that the lanes' LDS reads fall into different
+// banks: lanes whose shares begin a multiple of 16 records apart start at different records.
+// Consecutive segments are mostly the edges of one ring, whose contributions largely cancel: dealt
+// out one by one, every lane sums edges that do not, with several times the rounding error.
+__device__ __forceinline__ int share_start(int part, int per) {
+    const int even = per & -per;
+    return (part * even >> 4) & (even - 1);
 }
 // FP32 sums run over at most 64 segments between folds.
 template <int LPT>
 constexpr int kFoldTiles = LPT > 4 ? LPT / 4 : 1;
 
 // LPT lanes per target (neighbouring lanes of one wavefront) split each staged tile of segments
-// between them (share_index); their sums are added in FP64 by a butterfly before the write, so a
+// between them (share_start); their sums are added in FP64 by a butterfly before the write, so a
 // launch with few targets still has several wavefronts per SIMD.  Bound by VALU issue: 83
 // instructions per pair (FP32, exponent 2; 100 with grad D and c x r0 formed apart and the nine
 // products of [r0]x summed).  J = [sum f r0]x + sum c g^T.
@@ -481,8 +483,9 @@ __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
         __syncthreads();
         stage_segments<T, WG, VN>(a, j0, cnt, l0, l1, l2);
         __syncthreads();
-        for (int i = 0; i < WG / LPT; ++i) {
-            const int jj = share_index<LPT>(part, i);
+        const int per = (cnt + LPT - 1) / LPT, j_end = part * per + per;
+        int jj = part * per + share_start(part, per);
+        for (int i = 0; i < per; ++i, jj = jj + 1 < j_end ? jj + 1 : j_end - per) {
             if (jj >= cnt) continue;
             const V4<T> p = l0[jj];
             const V4<T> q = l1[jj];
@@ -603,8 +606,9 @@ __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
         __syncthreads();
         stage_segments<T, WG, VN>(a, j0, cnt, l0, l1, l2);
         __syncthreads();
-        for (int i = 0; i < WG / LPT; ++i) {
-            const int jj = share_index<LPT>(part, i);
+        const int per = (cnt + LPT - 1) / LPT, j_end = part * per + per;
+        int jj = part * per + share_start(part, per);
+        for (int i = 0; i < per; ++i, jj = jj + 1 < j_end ? jj + 1 : j_end - per) {
             if (jj >= cnt) continue;
             const V4<T> p = l0[jj];
             const V4<T> q = l1[jj];
@@ -700,23 +704,31 @@ hipError_t launch_grad_t(const SegArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Lanes per target of the gradient and adjoint kernels: 4, 16 or 64.  A workgroup then stages a
-// tile of 256 segments (about 150 VALU instructions per wavefront with the folds) for 256 / LPT
-// targets, and each of its lanes runs 256 / LPT pairs of `per_pair` instructions; about kSegSlots
-// workgroups are resident (four wavefronts per SIMD), so a launch takes
-// ceil(LPT n / 256 / kSegSlots) rounds of that.
-// Measured (4096 segments, exponent 2, FP32, us): adjoint with one lane per target at every size /
-// now: 1000 targets 1914 / 46, 16384 1921 / 335, 100003 2425 /
-// 1943, 400000 7984 / 6932; gradient with 16 lanes up to 16384 targets, 4 up to 196608, 1 above /
-// now: 1000 73 / 29, 16384 168 / 138, 100003 960 / 710, 400000 3585 / 2718.
+// Lanes per target of the gradient and adjoint kernels: 1, 4, 16 or 64.  In VALU instructions of a
+// wavefront: a workgroup begins and ends in `ends` (loads, stores, the butterfly's FP64 shuffles), stages each
+// tile of up to 256 segments in 150 and then runs the tile's pairs, ceil(segments / LPT) of per_pair per lane,
+// for 256 / LPT targets.  About kSegSlots workgroups are resident (four wavefronts per SIMD), fewer run
+// each wavefront faster, so x rounds take 0.45 + 0.7 x or x + 0.35, whichever is more.  One lane per target is
+// for at most 64 segments, the longest FP32 sums of the adjoint.
+// Measured (FP32, exponent 2, us; by the targets alone, with every tile run as a whole one / now): gradient
+// 100003 targets x 16 segments 65 / 13, 100003 x 300 109 / 72, 400000 x 64 238 / 60, 400000 x 300 401 /
+// 221, 100003 x 4096 704 / 721; adjoint 20000 x 64 49 / 16, 100003 x 64 222 / 40, 100003 x 4096
+// 1916 / 1817, 400000 x 300 931 / 499, 400000 x 4096 6860 / 6660.  Of the four the pick is the fastest or
+// within 5 %, but for gradients of 5000 x 1000 (27, 25) and 20000 x 257 (24, 21).
 constexpr int64_t kSegSlots = 1024;
-constexpr int kGradPairOps = 120, kVjpPairOps = 300, kSegStageOps = 150;
-int lanes_per_target(int64_t n_tgt, int per_pair) {
+constexpr int kGradPairOps = 100, kVjpPairOps = 260, kSegStageOps = 150;
+constexpr int64_t kSegOneLane = 64;
+int lanes_per_target(int64_t n_tgt, int64_t n_seg, int per_pair) {
+    n_seg = std::min<int64_t>(n_seg, 1 << 20);  // (the products fit 64 bits)
+    constexpr int kEnds[4] = {900, 1000, 1500, 1600};
     int best = 0;
     int64_t least = 0;
-    for (int lpt = 4; lpt <= 64; lpt *= 4) {
-        const int64_t per = 256 / lpt, wgs = (n_tgt + per - 1) / per;
-        const int64_t cost = (wgs + kSegSlots - 1) / kSegSlots * (per * per_pair + kSegStageOps);
+    for (int k = n_seg <= kSegOneLane ? 0 : 1; k < 4; ++k) {
+        const int lpt = 1 << (2 * k);
+        const int64_t per = 256 / lpt, wgs = 16 * n_tgt / per, slots = 16 * kSegSlots;  // (in sixteenths)
+        const int64_t below = (45 * slots + 70 * wgs) / 100, above = wgs + 35 * slots / 100;
+        const int64_t tiles = (n_seg + 255) / 256, pairs = n_seg / 256 * per + (n_seg % 256 + lpt - 1) / lpt;
+        const int64_t cost = std::max(below, above) / 16 * (kEnds[k] + kSegStageOps * tiles + per_pair * pairs);
         if (best == 0 || cost < least) {
             best = lpt;
             least = cost;
@@ -727,7 +739,8 @@ int lanes_per_target(int64_t n_tgt, int per_pair) {
 
 template <typename T>
 hipError_t launch_grad_split(const SegArgs& a, hipStream_t st) {
-    switch (lanes_per_target(a.n_tgt, kGradPairOps)) {
+    switch (lanes_per_target(a.n_tgt, a.n_seg, kGradPairOps)) {
+        case 1: return launch_grad_t<T, 256, 1>(a, st);
         case 4: return launch_grad_t<T, 256, 4>(a, st);
         case 16: return launch_grad_t<T, 256, 16>(a, st);
         default: return launch_grad_t<T, 256, 64>(a, st);
@@ -751,7 +764,8 @@ hipError_t launch_vjp_t(const SegArgs& a, hipStream_t st) {
 
 template <typename T>
 hipError_t launch_vjp_split(const SegArgs& a, hipStream_t st) {
-    switch (lanes_per_target(a.n_tgt, kVjpPairOps)) {
+    switch (lanes_per_target(a.n_tgt, a.n_seg, kVjpPairOps)) {
+        case 1: return launch_vjp_t<T, 256, 1>(a, st);
         case 4: return launch_vjp_t<T, 256, 4>(a, st);
         case 16: return launch_vjp_t<T, 256, 16>(a, st);
         default: return launch_vjp_t<T, 256, 64>(a, st);

@@ -166,3 +166,53 @@ def test_segments_gradient_and_vjp_at_split_sizes(kind, n, n_seg, gpu):
     xb, gb = vpm.vpm_segments_backward(*D, 0.02, 2, dev(ub, kind), dev(db, kind), gamma_tgt=dev(g, kind))
     xo, go = oracle.segments_vjp(a, b, gs, x, 0.02, 2, ub, db, g)
     assert rel_l2(host(xb), xo) <= TOL[kind] and rel_l2(host(gb), go) <= TOL[kind]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+# one, four, sixteen and sixty-four lanes per target with shares that do not divide the tile, lanes without
+# a segment, and a last tile of one, five and 188 segments
+@pytest.mark.parametrize("n,n_seg", [(20011, 3), (200003, 64), (17001, 100), (33001, 261), (16390, 700), (30011, 1025),
+                                     (3001, 517), (300, 1)])
+def test_segments_gradient_and_vjp_with_partly_filled_tiles(kind, n, n_seg, gpu):
+    a, b, gs, x, g, ub, db = _case(kind, n=n, seed=11)
+    a, b, gs = a[:, :n_seg], b[:, :n_seg], gs[:n_seg]
+    D = [dev(v, kind) for v in (a, b, gs, x)]
+    idx = np.unique(np.concatenate([[0, n - 1], np.random.default_rng(n).integers(0, n, 500)]))
+    say(f"segments partly filled tiles {kind} n={n} n_seg={n_seg}")
+    u, J, _ = vpm.vpm_eval_segments_gradient(*D, 0.02, 2)
+    assert rel_l2(host(u)[:, idx], oracle.segments(a, b, gs, x[:, idx], 0.02, 2)) <= TOL[kind]
+    assert rel_l2(host(J)[:, idx], oracle.segments_gradient(a, b, gs, x[:, idx], 0.02, 2).reshape(9, -1)) <= TOL[kind]
+    xb, gb = vpm.vpm_segments_backward(*D, 0.02, 2, dev(ub, kind), dev(db, kind), gamma_tgt=dev(g, kind))
+    xo, go = oracle.segments_vjp(a, b, gs, x[:, idx], 0.02, 2, ub[:, idx], db[:, idx], g[:, idx])
+    assert rel_l2(host(xb)[:, idx], xo) <= TOL[kind] and rel_l2(host(gb)[:, idx], go) <= TOL[kind]
+
+
+@pytest.mark.parametrize("what", ["gradient", "adjoint"])
+def test_segments_cost_falls_with_their_number(what, gpu):
+    """A tile of 64 segments is a quarter of the work of a whole one of 256 (400000 targets; with shares
+    cut for whole tiles the two took the same time)."""
+    import torch
+    c = W.config2(n=65536)
+    x = dev(np.tile(c["x"], 7)[:, :400000], "f32c")
+    g, ub = torch.randn_like(x), torch.randn_like(x)
+    out = [torch.zeros_like(x), torch.zeros_like(x), torch.zeros((9, x.shape[1]), device="cuda")]
+
+    def ms(n_seg):
+        S = [dev(np.ascontiguousarray(c[k][..., :n_seg]), "f32c") for k in ("seg_a", "seg_b", "seg_gamma")]
+        best = float("inf")
+        for _ in range(6):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(10):
+                if what == "gradient":
+                    vpm.vpm_eval_segments_gradient(*S, x, 0.02, 2, gamma_tgt=g, u_out=out[0], dgamma_out=out[1],
+                                                   grad_out=out[2])
+                else:
+                    vpm.vpm_segments_backward(*S, x, 0.02, 2, ub, ub, gamma_tgt=g, x_bar=out[0], gamma_bar=out[1])
+            t1.record()
+            t1.synchronize()
+            best = min(best, t0.elapsed_time(t1) / 10)
+        return best
+    few, whole = ms(64), ms(256)
+    say(f"segments {what}: 64 {few:.3f} ms, 256 {whole:.3f} ms")
+    assert few < 0.6 * whole
