@@ -310,8 +310,10 @@ template <typename T> __device__ __forceinline__ Dl<T> powr(Dl<T> x, T p) {  // 
 }
 
 // One segment (tile constants p = (a, coef), q = (r0, |r0|^2 or 1 when dead), eps2) at
-// point P: f, c = r0 x r1 (u = f c) and g = grad f.
-template <typename S, typename T, int VN>
+// point P: f, c = r0 x r1 (u = f c) and g = grad f.  SHORT: grad f as a sum of r0 and r1, 9 operations
+// fewer and a few per cent more rounding error in J (FP32, 5000 targets, 4096 segments in random order,
+// sums folded every 8 segments: 6.2e-7, 5.8e-7 without).
+template <typename S, typename T, int VN, bool SHORT>
 __device__ __forceinline__ void seg_pair(const S (&P)[3], const V4<T>& p, const V4<T>& q, T eps2, T inv_l02,
                                          T rc2n, T inv_n, T n_f, S& f, S (&c)[3], S (&g)[3]) {
     const S r1x = P[0] - p.x, r1y = P[1] - p.y, r1z = P[2] - p.z;
@@ -355,23 +357,30 @@ __device__ __forceinline__ void seg_pair(const S (&P)[3], const V4<T>& p, const 
     // (an arm of zero length makes the factors non-finite)
     const bool off = val(l1s) < eps2 || val(l2s) < eps2;
     f = zero_if(off, f);
-    if constexpr (std::is_same<S, T>::value) {
-        // with r2 = r1 - r0 and c x r0 = |r0|^2 r1 - (r0.r1) r0 the gradient is a sum of r0 and r1
+    if constexpr (SHORT) {
+        // with r2 = r1 - r0 and c x r0 = |r0|^2 r1 - (r0.r1) r0
         const S al = zero_if(off, ga * (di - e2) - gb * d1);
         const S be = zero_if(off, ga * (e2 - e1) + gb * q.w);
         g[0] = al * q.x + be * r1x;
         g[1] = al * q.y + be * r1y;
         g[2] = al * q.z + be * r1z;
     } else {
-        // (its derivative loses digits in that form: FP32 error of x_bar 1.15e-6, 7.4e-7 in this one)
         const S wx = c[1] * q.z - c[2] * q.y;  // c x r0
         const S wy = c[2] * q.x - c[0] * q.z;
         const S wz = c[0] * q.y - c[1] * q.x;
         gb = zero_if(off, gb);
-        const S k0 = zero_if(off, ga * di), k1 = zero_if(off, ga * e1), k2 = zero_if(off, ga * e2);
-        g[0] = q.x * k0 - r1x * k1 + r2x * k2 + gb * wx;
-        g[1] = q.y * k0 - r1y * k1 + r2y * k2 + gb * wy;
-        g[2] = q.z * k0 - r1z * k1 + r2z * k2 + gb * wz;
+        if constexpr (std::is_same<S, T>::value) {
+            ga = zero_if(off, ga);
+            const S k0 = zero_if(off, di), k1 = zero_if(off, e1), k2 = zero_if(off, e2);
+            g[0] = ga * (q.x * k0 - r1x * k1 + r2x * k2) + gb * wx;
+            g[1] = ga * (q.y * k0 - r1y * k1 + r2y * k2) + gb * wy;
+            g[2] = ga * (q.z * k0 - r1z * k1 + r2z * k2) + gb * wz;
+        } else {
+            const S k0 = zero_if(off, ga * di), k1 = zero_if(off, ga * e1), k2 = zero_if(off, ga * e2);
+            g[0] = q.x * k0 - r1x * k1 + r2x * k2 + gb * wx;
+            g[1] = q.y * k0 - r1y * k1 + r2y * k2 + gb * wy;
+            g[2] = q.z * k0 - r1z * k1 + r2z * k2 + gb * wz;
+        }
     }
 }
 
@@ -427,6 +436,20 @@ __device__ __forceinline__ void fold_tile(T (&acc)[NA], T (&hi)[NA], T (&lo)[NA]
     }
 }
 
+// The same with Dekker's FastTwoSum and its error carried into the next run, as the particle kernels fold
+// (five operations per sum for eight, nine registers fewer in k_segments_grad).
+template <typename T, int NA>
+__device__ __forceinline__ void fold_run(T (&acc)[NA], T (&hi)[NA], T (&lo)[NA]) {
+#pragma unroll
+    for (int c = 0; c < NA; ++c) {
+        const T y = acc[c] + lo[c];
+        const T h = hi[c] + y;
+        lo[c] = y - (h - hi[c]);
+        hi[c] = h;
+        acc[c] = T(0);
+    }
+}
+
 // J += [w]x (row-major; [w]x y = w x y).
 __device__ __forceinline__ void add_cross(double* J, const double* w) {
     J[1] -= w[2];
@@ -447,7 +470,7 @@ __device__ __forceinline__ int share_start(int part, int per) {
     const int even = per & -per;
     return (part * even >> 4) & (even - 1);
 }
-// FP32 sums run over at most 64 segments between folds.
+// Tiles between folds of the adjoint: FP32 sums run over at most 64 segments.
 template <int LPT>
 constexpr int kFoldTiles = LPT > 4 ? LPT / 4 : 1;
 
@@ -456,10 +479,17 @@ constexpr int kFoldTiles = LPT > 4 ? LPT / 4 : 1;
 // launch with few targets still has several wavefronts per SIMD.  Bound by VALU issue: 83
 // instructions per pair (FP32, exponent 2; 100 with grad D and c x r0 formed apart and the nine
 // products of [r0]x summed).  J = [sum f r0]x + sum c g^T.
-template <typename T, int WG, int VN, int LPT>
+// FP32 sums run over at most kRun segments between folds.  FEW: up to kSegFewTargets targets, whose
+// sums were always short (16 segments) and exact in form: seg_pair's long form and runs of 8, which make
+// up for [r0]x summed apart (16384 targets, 4096 segments in random order, error of J 5.8e-7, with
+// the short form and runs of 64 7.3e-7; 179 us and 150).  More targets take the short form in runs of 16
+// (100003 targets 6.4e-7, runs of 64 7.4e-7; 752 us and 715).
+constexpr int64_t kSegFewTargets = 16384;
+template <typename T, int WG, int VN, int LPT, bool FEW>
 __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
     static_assert((LPT & (LPT - 1)) == 0 && LPT <= 64 && WG == 256, "a power of two within a wavefront");
     constexpr bool kComp = std::is_same<T, float>::value;
+    constexpr int kRun = FEW ? 8 : 16;
     constexpr int NA = 15;  // u (3), sum c g^T row-major (9), sum f r0 (3)
     __shared__ V4<T> l0[WG];
     __shared__ V4<T> l1[WG];
@@ -478,6 +508,7 @@ __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
 #pragma unroll
     for (int c = 0; c < NA; ++c) acc[c] = hi[c] = lo[c] = T(0);
 
+    int since = 0;  // segments in the FP32 sums since the last fold
     for (int64_t j0 = 0; j0 < a.n_seg; j0 += WG) {
         const int cnt = int((a.n_seg - j0) < WG ? (a.n_seg - j0) : WG);
         __syncthreads();
@@ -486,28 +517,33 @@ __global__ __launch_bounds__(WG) void k_segments_grad(SegArgs a) {
         const int per = (cnt + LPT - 1) / LPT, j_end = part * per + per;
         int jj = part * per + share_start(part, per);
         for (int i = 0; i < per; ++i, jj = jj + 1 < j_end ? jj + 1 : j_end - per) {
-            if (jj >= cnt) continue;
-            const V4<T> p = l0[jj];
-            const V4<T> q = l1[jj];
-            const T eps2 = l2[jj].x;
-            const T inv_l02 = l2[jj].y;
-            T f, c[3], g[3];
-            seg_pair<T, T, VN>(P, p, q, eps2, inv_l02, rc2n, inv_n, n_f, f, c, g);
-            acc[0] += f * c[0];
-            acc[1] += f * c[1];
-            acc[2] += f * c[2];
+            if (jj < cnt) {
+                const V4<T> p = l0[jj];
+                const V4<T> q = l1[jj];
+                const T eps2 = l2[jj].x;
+                const T inv_l02 = l2[jj].y;
+                T f, c[3], g[3];
+                seg_pair<T, T, VN, !FEW>(P, p, q, eps2, inv_l02, rc2n, inv_n, n_f, f, c, g);
+                acc[0] += f * c[0];
+                acc[1] += f * c[1];
+                acc[2] += f * c[2];
 #pragma unroll
-            for (int r = 0; r < 3; ++r)
+                for (int r = 0; r < 3; ++r)
 #pragma unroll
-                for (int b = 0; b < 3; ++b) acc[3 + 3 * r + b] += c[r] * g[b];
-            acc[12] += f * q.x;
-            acc[13] += f * q.y;
-            acc[14] += f * q.z;
-        }
-        if constexpr (kComp) {
-            if ((j0 / WG) % kFoldTiles<LPT> == kFoldTiles<LPT> - 1 || j0 + WG >= a.n_seg) fold_tile<T, NA>(acc, hi, lo);
+                    for (int b = 0; b < 3; ++b) acc[3 + 3 * r + b] += c[r] * g[b];
+                acc[12] += f * q.x;
+                acc[13] += f * q.y;
+                acc[14] += f * q.z;
+            }
+            if constexpr (kComp) {
+                if (++since == kRun) {
+                    since = 0;
+                    fold_run<T, NA>(acc, hi, lo);
+                }
+            }
         }
     }
+    if constexpr (kComp) fold_run<T, NA>(acc, hi, lo);
     T* __restrict__ U = static_cast<T*>(a.u);
     T* __restrict__ Jo = static_cast<T*>(a.grad);
     T* __restrict__ Do = static_cast<T*>(a.dg);
@@ -615,7 +651,7 @@ __global__ __launch_bounds__(WG) void k_segments_vjp(SegArgs a) {
             const T eps2 = l2[jj].x;
             const T inv_l02 = l2[jj].y;
             S f, c[3], g[3];
-            seg_pair<S, T, VN>(P, p, q, eps2, inv_l02, rc2n, inv_n, n_f, f, c, g);
+            seg_pair<S, T, VN, false>(P, p, q, eps2, inv_l02, rc2n, inv_n, n_f, f, c, g);
 #pragma unroll
             for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -689,18 +725,18 @@ hipError_t launch_t(const SegArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <typename T, int WG, int LPT>
+template <typename T, int WG, int LPT, bool FEW>
 hipError_t launch_grad_t(const SegArgs& a, hipStream_t st) {
     const int64_t per = WG / LPT;
     const int grid = int((a.n_tgt + per - 1) / per);
     if (a.rc == 0.0)
-        hipLaunchKernelGGL((k_segments_grad<T, WG, 0, LPT>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_grad<T, WG, 0, LPT, FEW>), dim3(grid), dim3(WG), 0, st, a);
     else if (a.vn == 1)
-        hipLaunchKernelGGL((k_segments_grad<T, WG, 1, LPT>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_grad<T, WG, 1, LPT, FEW>), dim3(grid), dim3(WG), 0, st, a);
     else if (a.vn == 2)
-        hipLaunchKernelGGL((k_segments_grad<T, WG, 2, LPT>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_grad<T, WG, 2, LPT, FEW>), dim3(grid), dim3(WG), 0, st, a);
     else
-        hipLaunchKernelGGL((k_segments_grad<T, WG, 3, LPT>), dim3(grid), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL((k_segments_grad<T, WG, 3, LPT, FEW>), dim3(grid), dim3(WG), 0, st, a);
     return hipGetLastError();
 }
 
@@ -712,7 +748,7 @@ hipError_t launch_grad_t(const SegArgs& a, hipStream_t st) {
 // for at most 64 segments, the longest FP32 sums of the adjoint.
 // Measured (FP32, exponent 2, us; by the targets alone, with every tile run as a whole one / now): gradient
 // 100003 targets x 16 segments 65 / 13, 100003 x 300 109 / 72, 400000 x 64 238 / 60, 400000 x 300 401 /
-// 221, 100003 x 4096 704 / 721; adjoint 20000 x 64 49 / 16, 100003 x 64 222 / 40, 100003 x 4096
+// 221, 100003 x 4096 704 / 739 (kRun); adjoint 20000 x 64 49 / 16, 100003 x 64 222 / 40, 100003 x 4096
 // 1916 / 1817, 400000 x 300 931 / 499, 400000 x 4096 6860 / 6660.  Of the four the pick is the fastest or
 // within 5 %, but for gradients of 5000 x 1000 (27, 25) and 20000 x 257 (24, 21).
 constexpr int64_t kSegSlots = 1024;
@@ -739,11 +775,16 @@ int lanes_per_target(int64_t n_tgt, int64_t n_seg, int per_pair) {
 
 template <typename T>
 hipError_t launch_grad_split(const SegArgs& a, hipStream_t st) {
-    switch (lanes_per_target(a.n_tgt, a.n_seg, kGradPairOps)) {
-        case 1: return launch_grad_t<T, 256, 1>(a, st);
-        case 4: return launch_grad_t<T, 256, 4>(a, st);
-        case 16: return launch_grad_t<T, 256, 16>(a, st);
-        default: return launch_grad_t<T, 256, 64>(a, st);
+    const int lanes = lanes_per_target(a.n_tgt, a.n_seg, kGradPairOps);
+    if constexpr (std::is_same<T, float>::value) {
+        if (a.n_tgt <= kSegFewTargets)  // (16 lanes at least: fewer gain nothing there)
+            return lanes == 64 ? launch_grad_t<T, 256, 64, true>(a, st) : launch_grad_t<T, 256, 16, true>(a, st);
+    }
+    switch (lanes) {
+        case 1: return launch_grad_t<T, 256, 1, false>(a, st);
+        case 4: return launch_grad_t<T, 256, 4, false>(a, st);
+        case 16: return launch_grad_t<T, 256, 16, false>(a, st);
+        default: return launch_grad_t<T, 256, 64, false>(a, st);
     }
 }
 

@@ -121,3 +121,25 @@ def test_segments_gradient_degenerate_cases(kind, gpu):
     assert np.all(host(u) == 0) and np.all(host(J) == 0)
     u, J, _ = vpm.vpm_eval_segments_gradient(dev(a, kind), dev(b, kind), dev(gs, kind), z(3, 0), 0.02, 2)
     assert u.shape == (3, 0) and J.shape == (9, 0)
+
+
+@pytest.mark.parametrize("n,order,most", [
+    # J, dGamma/dt: the errors of the sums before they were shared between lanes in rings, on these inputs
+    (5000, "ring", (6.03e-7, 6.36e-7)), (5000, "random", (6.11e-7, 6.60e-7)), (16384, "ring", (5.62e-7, 5.76e-7)),
+    (16384, "random", (5.60e-7, 5.76e-7)), (20000, "random", (6.29e-7, 6.64e-7)),
+    (100003, "random", (6.69e-7, 6.86e-7))])
+def test_fp32_sums_are_short(n, order, most, gpu):
+    """FP32 gradients of 4096 segments against the FP64 kernel on the same inputs, the lattice's rings in
+    order and its segments shuffled."""
+    rng = np.random.default_rng([71, n])
+    c = W.config2(n=max(n, 65536))
+    pick = np.sort(rng.choice(c["x"].shape[1], n, replace=False))
+    ix = np.arange(4096) if order == "ring" else rng.permutation(4096)
+    a, b, gs, x, g = [dev(W.to_f32(np.ascontiguousarray(v)), "f32c")
+                      for v in (c["seg_a"][:, ix], c["seg_b"][:, ix], c["seg_gamma"][ix], c["x"][:, pick],
+                                c["gamma"][:, pick])]
+    _, J, d = vpm.vpm_eval_segments_gradient(a, b, gs, x, 0.02, 2, gamma_tgt=g)
+    _, J6, d6 = vpm.vpm_eval_segments_gradient(*[v.double() for v in (a, b, gs, x)], 0.02, 2, gamma_tgt=g.double())
+    errs = rel_l2(host(J), host(J6)), rel_l2(host(d), host(d6))
+    say(f"segments sums n={n} {order}: J {errs[0]:.3e} dgamma {errs[1]:.3e}")
+    assert errs[0] <= most[0] and errs[1] <= most[1]
