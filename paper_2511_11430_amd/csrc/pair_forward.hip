@@ -636,14 +636,18 @@ __global__ __launch_bounds__(L * G) void k_pair_fwd_finish(FwdArgs a) {
 // slice, slice + 256 / P, ...).  The slices' sums are added in FP64, by shuffles within a
 // wavefront and through LDS across wavefronts, in a fixed order; with nchunk > 1 the workgroup
 // sees one chunk of the sources and leaves partial sums for k_pair_fwd_finish.
-// FP32 sums run over at most 256 sources between folds; near tiles, whose terms are large, are
-// folded at once (at most 64 terms of a near tile per sum, so they need no second set of sums).
+// FP32 sums run over at most kFoldEvery sources between folds; near tiles, whose terms are large, are
+// folded at once (at most 64 terms of a near tile per sum, so they need no second set of sums).  128 as in the
+// kernel with a target per lane at these sizes: with 256 the error of dGamma of 65536 hover particles was
+// 1.48e-7, of 131072 1.25e-7, now 1.38 and 1.09 (a target per lane 1.42 and 1.26), in the same time (2939 us,
+// 2949).
 // The work per source tile of a wavefront is P pairs per lane, plus staging and two reductions.
 // Bound by VALU issue from about 5000 targets on, below by the latency of a tile (three barriers
 // and a load, 2 us).  Small target boxes also leave fewer tiles near: 65536 hover particles take
 // 3040 us in blocks of 64 and 3130 in blocks of 256, both with 16 chunks (FP64 7370 and 8970).
 // Measured (us per call, a target per lane with 256-source chunks / this form): 300 particles
 // 66 / 13, 1021 80 / 13, 2500 109 / 22, 4999 108 / 43; 4096 in a cube in FP64 282 / 120.
+constexpr int kFoldEvery = 128;
 template <typename T, int MODE, bool SYM>
 __device__ __forceinline__ void slice_body(const FwdArgs& a, int64_t t0, int64_t s0, int64_t s1, int lp) {
     constexpr int WG = 256, kWaves = WG / 64;
@@ -743,7 +747,7 @@ __device__ __forceinline__ void slice_body(const FwdArgs& a, int64_t t0, int64_t
             }
             since += np;  // WG / nslice
             if constexpr (kComp) {
-                if (near || since >= WG || j0 + WG >= s1) {
+                if (near || since >= kFoldEvery || j0 + WG >= s1) {
                     since = 0;
 #pragma unroll
                     for (int c = 0; c < kNacc; ++c) {  // as FwdBlock::fold

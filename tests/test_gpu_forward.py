@@ -467,6 +467,19 @@ def test_autotune_times_every_shape_and_sets_the_plan(gpu):
         tune.apply_cache()
 
 
+@pytest.mark.parametrize("n,most", [(65536, 1.42e-7), (100003, 1.345e-7)])
+def test_fp32_sums_are_short(n, most, gpu):
+    """FP32 stretching of a hover wake against the FP64 kernel on the same inputs: no further off than with a
+    target per lane and a fold every 128 sources (the bounds, measured)."""
+    c = W.config4(n=n)
+    A = [dev_(W.to_f32(c[k]), "f32c") for k in ("x", "gamma", "sigma")]
+    _, d = vpm.vpm_eval_velocity_stretching(*A)
+    _, d6 = vpm.vpm_eval_velocity_stretching(*[a.double() for a in A])
+    err = rel_l2(host(d), host(d6))
+    say(f"hover {n}: dgamma FP32 against FP64 {err:.3e}")
+    assert err <= most
+
+
 def _small_batch():
     wakes = W.config5(n_wakes=6, scale=0.02)
     off = [0]
