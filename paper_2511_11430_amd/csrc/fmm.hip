@@ -1788,7 +1788,7 @@ hipError_t run_fmm(int64_t n, const T* x, const T* g, const T* sg, int64_t ld, i
                        unit_leaf, unit_t0, unit0, item_counts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // one workgroup per unit of a moderately occupied tree; further units are taken in strides
-    const int64_t near_grid = std::min<int64_t>(y.units_cap, n / kUnit + kCellBlocks);
+    const int64_t near_grid = std::min(std::min<int64_t>(y.units_cap, n / kUnit + kCellBlocks), kMaxGroups256);
     hipLaunchKernelGGL((k_fmm_unit_box<T, V4>), dim3(unsigned(std::min<int64_t>((y.units_cap + 3) / 4, 4096))), dim3(256),
                        0, st, item_counts + 1, unit_leaf, unit_t0, lv[level].pstart, sp, sq, ubox);
     if ((e = hipGetLastError()) != hipSuccess) return e;

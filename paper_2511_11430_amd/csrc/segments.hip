@@ -745,7 +745,8 @@ hipError_t launch_grad_t(const SegArgs& a, hipStream_t st) {
 // tile of up to 256 segments in 150 and then runs the tile's pairs, ceil(segments / LPT) of per_pair per lane,
 // for 256 / LPT targets.  About kSegSlots workgroups are resident (four wavefronts per SIMD), fewer run
 // each wavefront faster, so x rounds take 0.45 + 0.7 x or x + 0.35, whichever is more.  One lane per target is
-// for at most 64 segments, the longest FP32 sums of the adjoint.
+// for at most 64 segments, the longest FP32 sums of the adjoint, and for the targets that one launch cannot
+// give four.
 // Measured (FP32, exponent 2, us; by the targets alone, with every tile run as a whole one / now): gradient
 // 100003 targets x 16 segments 65 / 13, 100003 x 300 109 / 72, 400000 x 64 238 / 60, 400000 x 300 401 /
 // 221, 100003 x 4096 704 / 739 (kRun); adjoint 20000 x 64 49 / 16, 100003 x 64 222 / 40, 100003 x 4096
@@ -754,28 +755,9 @@ hipError_t launch_grad_t(const SegArgs& a, hipStream_t st) {
 constexpr int64_t kSegSlots = 1024;
 constexpr int kGradPairOps = 100, kVjpPairOps = 260, kSegStageOps = 150;
 constexpr int64_t kSegOneLane = 64;
-int lanes_per_target(int64_t n_tgt, int64_t n_seg, int per_pair) {
-    n_seg = std::min<int64_t>(n_seg, 1 << 20);  // (the products fit 64 bits)
-    constexpr int kEnds[4] = {900, 1000, 1500, 1600};
-    int best = 0;
-    int64_t least = 0;
-    for (int k = n_seg <= kSegOneLane ? 0 : 1; k < 4; ++k) {
-        const int lpt = 1 << (2 * k);
-        const int64_t per = 256 / lpt, wgs = 16 * n_tgt / per, slots = 16 * kSegSlots;  // (in sixteenths)
-        const int64_t below = (45 * slots + 70 * wgs) / 100, above = wgs + 35 * slots / 100;
-        const int64_t tiles = (n_seg + 255) / 256, pairs = n_seg / 256 * per + (n_seg % 256 + lpt - 1) / lpt;
-        const int64_t cost = std::max(below, above) / 16 * (kEnds[k] + kSegStageOps * tiles + per_pair * pairs);
-        if (best == 0 || cost < least) {
-            best = lpt;
-            least = cost;
-        }
-    }
-    return best;
-}
-
 template <typename T>
 hipError_t launch_grad_split(const SegArgs& a, hipStream_t st) {
-    const int lanes = lanes_per_target(a.n_tgt, a.n_seg, kGradPairOps);
+    const int lanes = segment_lanes(a.n_tgt, a.n_seg, kGradPairOps);
     if constexpr (std::is_same<T, float>::value) {
         if (a.n_tgt <= kSegFewTargets)  // (16 lanes at least: fewer gain nothing there)
             return lanes == 64 ? launch_grad_t<T, 256, 64, true>(a, st) : launch_grad_t<T, 256, 16, true>(a, st);
@@ -805,7 +787,7 @@ hipError_t launch_vjp_t(const SegArgs& a, hipStream_t st) {
 
 template <typename T>
 hipError_t launch_vjp_split(const SegArgs& a, hipStream_t st) {
-    switch (lanes_per_target(a.n_tgt, a.n_seg, kVjpPairOps)) {
+    switch (segment_lanes(a.n_tgt, a.n_seg, kVjpPairOps)) {
         case 1: return launch_vjp_t<T, 256, 1>(a, st);
         case 4: return launch_vjp_t<T, 256, 4>(a, st);
         case 16: return launch_vjp_t<T, 256, 16>(a, st);
@@ -814,6 +796,27 @@ hipError_t launch_vjp_split(const SegArgs& a, hipStream_t st) {
 }
 
 }  // namespace
+
+int segment_lanes(int64_t n_tgt, int64_t n_seg, int per_pair) {
+    n_seg = std::min<int64_t>(n_seg, 1 << 20);  // (the products fit 64 bits)
+    constexpr int kEnds[4] = {900, 1000, 1500, 1600};
+    int best = 0;
+    int64_t least = 0;
+    const bool one_lane = n_seg <= kSegOneLane || n_tgt > 64 * kMaxGroups256;
+    for (int k = one_lane ? 0 : 1; k < 4; ++k) {
+        const int lpt = 1 << (2 * k);
+        const int64_t per = 256 / lpt, wgs = 16 * n_tgt / per, slots = 16 * kSegSlots;  // (in sixteenths)
+        const int64_t below = (45 * slots + 70 * wgs) / 100, above = wgs + 35 * slots / 100;
+        if (k > 0 && (n_tgt + per - 1) / per > kMaxGroups256) break;
+        const int64_t tiles = (n_seg + 255) / 256, pairs = n_seg / 256 * per + (n_seg % 256 + lpt - 1) / lpt;
+        const int64_t cost = std::max(below, above) / 16 * (kEnds[k] + kSegStageOps * tiles + per_pair * pairs);
+        if (best == 0 || cost < least) {
+            best = lpt;
+            least = cost;
+        }
+    }
+    return best;
+}
 
 hipError_t launch_segments_gradient(int dtype, const SegArgs& a, hipStream_t st) {
     if (a.n_tgt == 0) return hipSuccess;

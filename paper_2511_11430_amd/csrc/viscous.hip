@@ -300,6 +300,9 @@ __global__ __launch_bounds__(256) void k_sub_box(const PseRec<T>* __restrict__ r
 }
 
 constexpr int64_t kPseFewGroups = 1024;
+// 64-target groups of one launch (a launch of four wavefronts per group of more than 2^30 particles would be
+// refused; the end of a launch this long costs nothing).
+constexpr int64_t kPseLaunchGroups = int64_t(1) << 18;
 
 struct PseArgs {
     const void* rec;
@@ -307,6 +310,7 @@ struct PseArgs {
     const void* tile;
     const uint64_t* keys;
     int64_t begin, n;
+    int64_t group0;  // the launch's first group
     void* dg;
     int64_t ldo;
     int32_t accumulate;
@@ -332,7 +336,7 @@ __global__ __launch_bounds__(64 * NW) void k_pse(PseArgs a) {
     __shared__ V4 lrec[NW][64][3];
     const T far2 = T(Prec<T>::kFarRho2);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-    const int64_t p0 = int64_t(blockIdx.x) * 64;
+    const int64_t p0 = (a.group0 + int64_t(blockIdx.x)) * 64;
     const int lane = threadIdx.x & 63;
     const int64_t p = p0 + lane;
     const bool valid = p < a.n;
@@ -540,11 +544,15 @@ hipError_t pse_set(int64_t begin, int64_t end, const T* x, const T* g, const T* 
     a.accumulate = accumulate;
     // four wavefronts per 64 targets; sixteen while that leaves the chip short of wavefronts
     const int64_t groups = (n + 63) / 64;
-    if (groups < kPseFewGroups)
-        hipLaunchKernelGGL((k_pse<T, 16>), dim3(unsigned(groups)), dim3(1024), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_pse<T, 4>), dim3(unsigned(groups)), dim3(256), 0, st, a);
-    return hipGetLastError();
+    for (a.group0 = 0; a.group0 < groups; a.group0 += kPseLaunchGroups) {
+        const unsigned grid = unsigned(groups - a.group0 < kPseLaunchGroups ? groups - a.group0 : kPseLaunchGroups);
+        if (groups < kPseFewGroups)
+            hipLaunchKernelGGL((k_pse<T, 16>), dim3(grid), dim3(1024), 0, st, a);
+        else
+            hipLaunchKernelGGL((k_pse<T, 4>), dim3(grid), dim3(256), 0, st, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 }  // namespace
 

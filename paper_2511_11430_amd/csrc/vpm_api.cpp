@@ -168,6 +168,7 @@ int batch_slice_lp(int32_t n_batch, const int64_t* src_off, const int64_t* tgt_o
     if (largest <= 256.0 * 256.0 && 2.0 * double(count_blocks(n_batch, tgt_off, 256)) >= kSlots)
         return kPlainLp;
     int lp = 6;
+    if (count_blocks(n_batch, tgt_off, 64) > vpm::kMaxGroups256) return kPlainLp;
     while (lp > 4 && count_blocks(n_batch, tgt_off, int64_t(1) << lp) < kSliceItems) --lp;
     return lp;
 }

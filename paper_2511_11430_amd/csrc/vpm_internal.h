@@ -53,6 +53,8 @@ struct BatchQueue {
     int n_items;
 };
 
+// Most workgroups of 256 lanes in one launch (HIP refuses 2^32 lanes and more).
+constexpr int64_t kMaxGroups256 = (int64_t(1) << 24) - 1;
 // Items (set, block) of a batched launch in decreasing cost (lanes x (loop-set size + 1)), those of equal
 // cost in the order of sets and blocks: per_block[b] lanes to a block of set b, the last one shorter.
 // Written to out unless that is null; returns their number.  Host only.
@@ -124,6 +126,9 @@ size_t fmm_workspace(int64_t n, int level, int order, int dtype);
 hipError_t launch_fmm(int dtype, int64_t n, const void* x, const void* g, const void* sg, int64_t ld, int level,
                       int order, int classical, void* u, void* dg, void* grad, int64_t ldo, void* ws,
                       hipStream_t st);
+// Lanes per target (1, 4, 16 or 64) of the segments' gradient and adjoint, a pair of which takes per_pair
+// VALU instructions.
+int segment_lanes(int64_t n_tgt, int64_t n_seg, int per_pair);
 hipError_t launch_segments_gradient(int dtype, const SegArgs& a, hipStream_t st);
 hipError_t launch_segments_vjp(int dtype, const SegArgs& a, hipStream_t st);
 

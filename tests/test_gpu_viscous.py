@@ -262,3 +262,21 @@ def test_diffusion_at_group_sizes(kind, n, gpu):
     idx = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 300)]))
     ref = oracle.pse(x, g, s, vol, W.NU_AIR, nut, targets=idx)
     assert rel_l2(host(d)[:, idx], ref) <= TOL[kind]
+
+
+def test_diffusion_in_more_than_one_launch(gpu):
+    """More target groups than one launch takes (2^18 of 64): random targets of a scattered set, and the last
+    ones of the sorted order, which the second launch has."""
+    n = 17_000_003
+    rng = np.random.default_rng(47)
+    x = rng.uniform(0.0, 1.0, (3, n))
+    g, s = rng.normal(0, 1e-6, (3, n)), np.full(n, 7e-4)
+    x, g, s, vol = prepare([x, g, s, np.full(n, 1.0 / n)], "f32c")
+    say(f"diffusion n={n}")
+    d = vpm.vpm_eval_diffusion(dev(x, "f32c"), dev(g, "f32c"), dev(s, "f32c"), dev(vol, "f32c"), W.NU_AIR)
+    # the last of the Morton order lie at the far corner
+    last = np.argsort(x.sum(0))[-40:]
+    idx = np.unique(np.concatenate([[0, n - 1], last, rng.integers(0, n, 60)]))
+    ref = oracle.pse(x, g, s, vol, W.NU_AIR, targets=idx)
+    assert rel_l2(host(d)[:, idx], ref) <= TOL["f32c"]
+    assert rel_l2(host(d)[:, last], oracle.pse(x, g, s, vol, W.NU_AIR, targets=last)) <= TOL["f32c"]
