@@ -185,3 +185,48 @@ def test_fmm_velocity_gradient_full_size(gpu):
     en = rel_l2(host(nut_f), host(nut_d))
     say(f"fmm 1M with gradient: {ms:.1f} ms; J vs direct {ej:.2e}; Vreman nu_t {en:.2e}")
     assert ej <= 3e-4 and en <= 3e-4
+
+
+def _helix(n):
+    """Particles along a helix, most of them alone in a cell of the deepest grid (1024 per axis)."""
+    t = (np.arange(n) + 0.5) / n
+    rng = np.random.default_rng(n)
+    x = np.stack([0.5 * np.cos(6 * np.pi * t), 0.5 * np.sin(6 * np.pi * t), t - 0.5])
+    return x, rng.normal(0, 1e-3, (3, n)), rng.uniform(1e-4, 2e-4, n)
+
+
+def _cube(n):
+    rng = np.random.default_rng(n)
+    return rng.uniform(-1.0, 1.0, (3, n)), rng.normal(0, 1e-3, (3, n)), rng.uniform(0.005, 0.01, n)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("scheme", [vpm.TRANSPOSED, vpm.CLASSICAL])
+# more occupied cells on several levels, work items and 64-particle units than the launches have workgroups
+# (4096, and 16384 wavefronts for the units' boxes): every kernel takes further ones in strides
+@pytest.mark.parametrize("make,n,level,order", [(_cube, 20001, 6, 3), (_helix, 9001, 10, 7)])
+def test_fmm_of_more_cells_than_workgroups(kind, scheme, make, n, level, order, gpu):
+    x, g, s = prepare(make(n), kind)
+    lo, hi = x.min(1), x.max(1)
+    half = (hi - lo).max() / 2
+    cell = np.floor((x - ((lo + hi) / 2 - half)[:, None]) / (2 * half / 2 ** level)).clip(0, 2 ** level - 1)
+    leaves = len(np.unique(cell, axis=1).T)
+    say(f"fmm many cells {kind} {make.__name__} level={level} order={order}: {leaves} leaves")
+    assert leaves > (16384 if make is _cube else 8000)
+    u, d, J = vpm.vpm_fmm_eval(dev(x, kind), dev(g, kind), dev(s, kind), level, order, scheme=scheme, want_grad=True)
+    uo, do, Jo = oracle.fmm(x, g, s, level, order, scheme, want_grad=True)
+    assert rel_l2(host(u), uo) <= TOL[kind] and rel_l2(host(d), do) <= TOL[kind]
+    assert rel_l2(host(J).reshape(9, -1), Jo.reshape(9, -1)) <= TOL[kind]
+    u, d = vpm.vpm_fmm_eval(dev(x, kind), dev(g, kind), dev(s, kind), level, order, scheme=scheme)
+    assert rel_l2(host(u), uo) <= TOL[kind] and rel_l2(host(d), do) <= TOL[kind]
+
+
+def test_high_order_fmm_of_more_cells_than_workgroups(gpu):
+    """The same for the M2L of orders from 13 on (the oracle takes most of the time: one evaluation, at inputs
+    that both types hold)."""
+    x, g, s = prepare(_helix(4601), "f32c")
+    say("fmm many cells, order 13")
+    uo, do = oracle.fmm(x, g, s, 10, 13)
+    for kind in KINDS:
+        u, d = vpm.vpm_fmm_eval(dev(x, kind), dev(g, kind), dev(s, kind), 10, 13)
+        assert rel_l2(host(u), uo) <= TOL[kind] and rel_l2(host(d), do) <= TOL[kind]

@@ -206,6 +206,7 @@ def test_batched_persistent_matches_single_launches(kind, gpu):
         u1, d1 = vpm.vpm_eval_velocity_stretching(X[:, lo:hi].contiguous(), G[:, lo:hi].contiguous(),
                                                   S[lo:hi].contiguous())
         # same kernel shape and summation order: equal to rounding of the per-target epilogue
+        # (that was before sliced blocks; a batch and a set of its own now differ in blocks and chunks as well)
         tight = 1e-14 if kind == "f64" else 1e-6
         assert rel_l2(U[:, lo:hi], host(u1)) <= tight and rel_l2(D[:, lo:hi], host(d1)) <= tight
         x, g, s = xs[w]
@@ -350,6 +351,7 @@ def test_many_targets_either_side_of_the_plain_kernel(kind, nt, gpu):
 @pytest.mark.parametrize("mode", ["velocity", "transposed", "gradient"])
 # few uneven sets in blocks of 16, sets around block and tile edges with an empty one, and a batch in
 # blocks of 64; each also with room for the queue of plain blocks only
+# (by the present rule the last one has blocks of 32: blocks of 64 have a test of their own below)
 @pytest.mark.parametrize("sizes", [(300, 5), (1, 0, 63, 64, 65, 255, 257, 3), (9000,) * 12 + (700, 129)])
 def test_batched_slices(kind, mode, sizes, gpu):
     import torch
@@ -374,6 +376,19 @@ def test_batched_slices(kind, mode, sizes, gpu):
             uo, do = oracle.eval_pairs(x[:, q], g[:, q], s[q], x_tgt=x[:, q][:, idx], gam_tgt=g[:, q][:, idx], excl=idx)
             assert rel_l2(U[:, q][:, idx], uo) <= TOL[kind]
             assert D is None or rel_l2(D[:, q][:, idx], do) <= TOL[kind]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("mode", ["velocity", "transposed", "gradient"])
+def test_batched_slices_of_64_targets(kind, mode, gpu):
+    """A batch large enough for items of 64 targets (the ones of test_batched_slices have 16, 16 and 32), as the
+    workspace it asks for shows."""
+    sizes = (9000,) * 15 + (700, 129)
+    off = [0] + [int(v) for v in np.cumsum(sizes)]
+    up = lambda b: (b + 255) // 256 * 256
+    assert vpm.vpm_workspace_size(vpm.F64 if kind == "f64" else vpm.F32C, off) == \
+        256 + 2 * up(8 * len(off)) + up(8 * sum((k + 63) // 64 for k in sizes))
+    test_batched_slices(kind, mode, sizes, gpu)
 
 
 @pytest.mark.parametrize("kind", KINDS)
