@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -275,13 +276,13 @@ hipError_t stage_and_copy(const std::vector<unsigned char>& blob, void* dst, hip
 // FP32C kernel shape per (single set / batched, ceil(log2(targets))) bucket, 0 = the built-in choice, and
 // whether launches of that size take it as they take a caller's opt->variant (vpm_set_plan, and the
 // tuner where a shape beat the library's own spread) or only where the library's spread has a target
-// or two per lane.  Guarded by g_mutex.
+// or two per lane.  (Each entry is read and written whole, without a lock: every call looks twice.)
 constexpr int kPlanBuckets = 40;
 struct Plan {
-    int shape = 0;
-    bool holds = false;
+    int16_t shape;
+    bool holds;
 };
-Plan g_plan[2][kPlanBuckets];
+std::atomic<Plan> g_plan[2][kPlanBuckets];
 
 int plan_bucket(int64_t n) {
     int b = 0;
@@ -305,8 +306,7 @@ int default_variant(bool batched, int64_t n_tgt) {
 int choose_variant(const vpm_options& o, bool batched, int64_t n_tgt) {
     if (o.gradient) return vpm::kGradientVariant;
     if (o.variant > 0) return o.variant - 1;
-    std::lock_guard<std::mutex> lock(g_mutex);
-    const int v = g_plan[batched ? 1 : 0][plan_bucket(n_tgt)].shape;
+    const int v = g_plan[batched ? 1 : 0][plan_bucket(n_tgt)].load().shape;
     return v > 0 ? v - 1 : default_variant(batched, n_tgt);
 }
 
@@ -316,9 +316,7 @@ int choose_variant(const vpm_options& o, bool batched, int64_t n_tgt) {
 bool caller_shape(int32_t dtype, const vpm_options& o, bool batched, int64_t n_tgt) {
     if (o.gradient) return false;
     if (o.variant > 0) return true;
-    if (dtype != kDtypeF32C) return false;
-    std::lock_guard<std::mutex> lock(g_mutex);
-    return g_plan[batched ? 1 : 0][plan_bucket(n_tgt)].holds;
+    return dtype == kDtypeF32C && g_plan[batched ? 1 : 0][plan_bucket(n_tgt)].load().holds;
 }
 
 int fwd_mode(const vpm_options& o, bool stretch) {
@@ -578,8 +576,8 @@ vpm_status vpm_set_plan(int32_t dtype, int32_t batched, int64_t n_lo, int64_t n_
     if (batched != 0 && batched != 1) return VPM_ERR_ENUM;
     if (variant < 0 || variant > vpm::kNumF32Variants) return VPM_ERR_ENUM;
     if (n_lo < 0 || n_hi < n_lo) return VPM_ERR_SIZE;
-    std::lock_guard<std::mutex> lock(g_mutex);
-    for (int b = plan_bucket(n_lo); b <= plan_bucket(n_hi); ++b) g_plan[batched][b] = {variant, variant > 0};
+    for (int b = plan_bucket(n_lo); b <= plan_bucket(n_hi); ++b)
+        g_plan[batched][b].store({int16_t(variant), variant > 0});
     return VPM_OK;
 }
 
@@ -1371,16 +1369,11 @@ vpm_status vpm_autotune(int32_t dtype, int32_t n_batch, const int64_t* src_off, 
     if (s == VPM_OK) {
         for (int v = 2; v <= vpm::kNumF32Variants; ++v)
             if (best_ms[v - 1] < best_ms[pick - 1]) pick = v;
-        Plan before;
-        {
-            std::lock_guard<std::mutex> lock(g_mutex);
-            before = g_plan[batched][bucket];
-            g_plan[batched][bucket] = {pick, false};  // (where the library's spread is a target per lane, this shape)
-        }
+        // (where the library's spread is a target per lane, it has this shape)
+        const Plan before = g_plan[batched][bucket].exchange({int16_t(pick), false});
         if ((s = run(0)) == VPM_OK) s = time(0, own_ms);
-        std::lock_guard<std::mutex> lock(g_mutex);
-        if (s != VPM_OK) g_plan[batched][bucket] = before;
-        else g_plan[batched][bucket].holds = best_ms[pick - 1] < kTuneGain * own_ms;
+        if (s != VPM_OK) g_plan[batched][bucket].store(before);
+        else g_plan[batched][bucket].store({int16_t(pick), best_ms[pick - 1] < kTuneGain * own_ms});
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
