@@ -376,8 +376,11 @@ SplitPlan shape_split(int32_t dtype, int variant, int nacc, int64_t n_src, int64
 // pair in a core is a call, the 256-target blocks pay a fifth for the tiles that are near them and
 // not near 64-target blocks.  In FP32 a target per lane is left to more than kPlainFrom targets:
 // below, slices are within 5 % either way (65536 hover particles 3040 us, 3130 with a target per
-// lane; flight 2990 and 2825) and their shorter FP32 sums hold the error down (7e-8 against 1.3e-7
-// with folds every 256 sources and 8.8e-8 every 128).  The gradient mode's 21 sums leave a slice
+// lane; flight 2990 and 2825) and their shorter FP32 sums hold the error down (65536 hover particles, both
+// folded every 128 sources: u 5.0e-8, 8.7e-8 with a target per lane, dGamma 1.38e-7 and 1.42e-7).  A velocity
+// pair is shorter, and targets that lie close together gain nothing from small boxes: 8000 neighbouring points
+// of a million particles take 3840 us in slices and 3450 with a target per lane, 8000 spread over the
+// wake 4480 and 6690.  The gradient mode's 21 sums leave a slice
 // three wavefronts per SIMD, an eighth slower per pair than a target per lane.
 // More than kPlainOnly targets fill the chip with a target per lane in either type, which has less
 // staging per pair (FP64 flight wakes, us, slices / a target per lane: 500000 338000 / 355000,
